@@ -208,7 +208,6 @@ int build_adjoint_bank(setd_ctx* c, hipStream_t s) {
       const int n = c->dims[mu];
       const size_t pb = packed_bytes(n, SETD_PREC_F64);
       const size_t nn = (size_t)n * n;
-      const bool rowmajor = mu == 0;   // layout the forward kernels read for this direction
       std::vector<double> scal;
       for (int e = 0; e < 5; ++e)
         for (int t = 0; t < T; ++t)
@@ -226,19 +225,18 @@ int build_adjoint_bank(setd_ctx* c, hipStream_t s) {
         for (int t = 0; t < T; ++t) {
           const int k = e * T + t;
           const int li = c->sp[kBankEll[e]].ell_i[t];
-          // the transpose of M packed in one layout is M packed in the other
           c->bankT[cc][e][t][mu] = q;
-          SETD_TRY(pack_matrix_f64(outs[k * 3 + li], n, 1.0, !rowmajor, (double*)q, s));
+          SETD_TRY(pack_matrix_f64(outs[k * 3 + li], n, 1.0, true, (double*)q, s));
           q += pb;
           // phi_{l-1} - l phi_l
           SETD_HIP(hipMemcpyAsync(tmp.p, outs[k * 3 + li - 1], nn * sizeof(double), hipMemcpyDeviceToDevice, s));
           SETD_TRY(launch_axpby(outs[k * 3 + li], (double*)tmp.p, (int64_t)nn, -(double)li, 1.0, s));
           c->dbank[cc][e][t][mu] = q;
-          SETD_TRY(pack_matrix_f64((const double*)tmp.p, n, 1.0, rowmajor, (double*)q, s));
+          SETD_TRY(pack_matrix_f64((const double*)tmp.p, n, 1.0, false, (double*)q, s));
           q += pb;
         }
       c->ApkT[cc][mu] = q;
-      SETD_TRY(pack_matrix_f64((const double*)A.p, n, 1.0, !rowmajor, (double*)q, s));
+      SETD_TRY(pack_matrix_f64((const double*)A.p, n, 1.0, true, (double*)q, s));
       q += pb;
       SETD_HIP(hipStreamSynchronize(s));   // A, raw and tmp are released at scope exit
     }
@@ -293,8 +291,8 @@ int sigma_chains_d3(const int* dims, SigmaChain* ch, int nch, double* const* E, 
   const int64_t N = (int64_t)dims[0] * dims[1] * dims[2];
   std::vector<ModeJob> jobs;
   for (int k = 0; k < nch; ++k) {
-    jobs.push_back(mk_job(ch[k].V, ch[k].P[0], 1.0, ch[k].A0, nullptr, 1, dims[0], N / dims[0]));
-    jobs.push_back(mk_job(ch[k].V, ch[k].dP[0], 1.0, ch[k].A1, nullptr, 1, dims[0], N / dims[0]));
+    jobs.push_back(mk_job(ch[k].V, ch[k].P[0], ch[k].scale, ch[k].A0, nullptr, 1, dims[0], N / dims[0]));
+    jobs.push_back(mk_job(ch[k].V, ch[k].dP[0], ch[k].scale, ch[k].A1, nullptr, 1, dims[0], N / dims[0]));
   }
   SETD_TRY(launch_f64_jobs(jobs, true, s));
   for (int k = 0; k < nch; ++k) {
@@ -314,10 +312,10 @@ int sigma_chains_d3(const int* dims, SigmaChain* ch, int nch, double* const* E, 
       ModeJob jb{};
       jb.nterms = T;
       for (int t = 0; t < T; ++t) {
-        const SigmaChain& q = ch[o * T + t];
+        const SigmaChain& q = ch[o * T + t];   // s_t is in the mode-1 partials
         jb.X[t] = pass == 0 ? q.B1 : q.B0;
         jb.P[t] = pass == 0 ? q.P[2] : q.dP[2];
-        jb.scale[t] = q.scale;
+        jb.scale[t] = 1.0;
       }
       jb.Y = E[o];
       jb.base = pass == 0 ? Ebase[o] : E[o];

@@ -43,10 +43,9 @@ struct Inst {
 };
 
 // A set of packed matrices shared by every (instance, component, direction)
-// with the same matrix A, the same phi scalars and the same packing.
+// with the same matrix A and the same phi scalars.
 struct PackedSet {
   int n = 0;
-  bool rowmajor = false;
   std::vector<double> key;   // A (n*n) followed by the scalars
   uint64_t hash = 0;
   size_t offset = 0;         // bytes into bank_mem
@@ -129,19 +128,18 @@ const void* packed(const setd_batch* B, int set, int k) {
   return (const char*)B->bank_mem.p + S.offset + (size_t)k * packed_bytes(S.n, SETD_PREC_F64);
 }
 
-// Finds or adds the packed set for (n, A, scalars, layout).
-int find_set(setd_batch* B, int n, bool rowmajor, const std::vector<double>& Ah, const std::vector<double>& scal,
+// Finds or adds the packed set for (n, A, scalars).
+int find_set(setd_batch* B, int n, const std::vector<double>& Ah, const std::vector<double>& scal,
              int count, const double* A_dev) {
   std::vector<double> key(Ah);
   key.insert(key.end(), scal.begin(), scal.end());
-  const uint64_t h = fnv(key.data(), key.size(), 1469598103934665603ull ^ (uint64_t)n ^ (rowmajor ? 1ull << 40 : 0));
+  const uint64_t h = fnv(key.data(), key.size(), 1469598103934665603ull ^ (uint64_t)n);
   for (size_t k = 0; k < B->sets.size(); ++k) {
     const PackedSet& S = B->sets[k];
-    if (S.hash == h && S.n == n && S.rowmajor == rowmajor && S.key == key) return (int)k;
+    if (S.hash == h && S.n == n && S.key == key) return (int)k;
   }
   PackedSet S;
   S.n = n;
-  S.rowmajor = rowmajor;
   S.key = std::move(key);
   S.hash = h;
   S.count = count;
@@ -164,9 +162,9 @@ int build_banks(setd_batch* B, const std::vector<std::vector<double>>& Ah, const
           const Splitting& S = B->sp[kBankEll[e]];
           for (int t = 0; t < T; ++t) scal.push_back(stage_scale(kBankStage[e]) * B->tau * S.alpha[t][mu]);
         }
-        B->inst[b].bank[c][mu] = find_set(B, n, mu == 0, Ah[k], scal, 5 * T, A[k]);
+        B->inst[b].bank[c][mu] = find_set(B, n, Ah[k], scal, 5 * T, A[k]);
         B->inst[b].apk[c][mu] =
-            B->tridiag ? kNoPacked : find_set(B, n, mu == 0, Ah[k], std::vector<double>(), 1, A[k]);
+            B->tridiag ? kNoPacked : find_set(B, n, Ah[k], std::vector<double>(), 1, A[k]);
       }
   size_t bytes = 0;
   for (PackedSet& S : B->sets) {
@@ -178,7 +176,7 @@ int build_banks(setd_batch* B, const std::vector<std::vector<double>>& Ah, const
     const PackedSet& S = B->sets[k];
     const int n = S.n;
     if (S.count == 1) {   // A itself, for the dense K action
-      SETD_TRY(pack_matrix_f64(S.A_dev, n, 1.0, S.rowmajor, (double*)packed(B, (int)k, 0), s));
+      SETD_TRY(pack_matrix_f64(S.A_dev, n, 1.0, false, (double*)packed(B, (int)k, 0), s));
       continue;
     }
     const std::vector<double> scal(S.key.begin() + (size_t)n * n, S.key.end());
@@ -193,7 +191,7 @@ int build_banks(setd_batch* B, const std::vector<std::vector<double>>& Ah, const
       for (int t = 0; t < T; ++t) {
         const int j = e * T + t;
         const int li = B->sp[kBankEll[e]].ell_i[t];
-        SETD_TRY(pack_matrix_f64(outs[j * 3 + li], n, 1.0, S.rowmajor, (double*)packed(B, (int)k, j), s));
+        SETD_TRY(pack_matrix_f64(outs[j * 3 + li], n, 1.0, false, (double*)packed(B, (int)k, j), s));
       }
     SETD_HIP(hipStreamSynchronize(s));   // raw is released at scope exit
   }
@@ -224,30 +222,28 @@ struct PlanBuilder {
   std::vector<Op> ops;
   std::vector<std::vector<ModeJob>> lists;   // host jobs of each list op (same order as list ops)
 
-  // Splits jobs by kernel variant and appends one list launch per variant.
-  void add_lists(std::vector<ModeJob>& jobs, bool mode1) {
+  // Appends one list launch, its jobs sorted by the length of a tile's
+  // contraction, longest first, so that the last tiles to run are short ones.
+  void add_list(std::vector<ModeJob>& jobs, bool mode1) {
+    if (jobs.empty()) return;
     const int* cfg = mode1 ? c1 : cb;
-    std::vector<ModeJob> part[3];
-    for (const ModeJob& jb : jobs) part[job_mode(jb, mode1, cfg[0], cfg[1])].push_back(jb);
-    for (int m = 2; m >= 0; --m) {
-      if (part[m].empty()) continue;
-      Op op{};
-      op.list = true;
-      op.L.njobs = (int)part[m].size();
-      op.L.total = assign_tiles(part[m].data(), op.L.njobs, mode1, cfg[0], cfg[1]);
-      op.L.mode1 = mode1;
-      op.L.tm = cfg[0];
-      op.L.tn = cfg[1];
-      op.L.mode = m;
-      op.L.grid_cap = cfg[2];
-      for (const ModeJob& jb : part[m]) {
-        const double N = (double)jb.na * jb.n * jb.nb;
-        op.L.flops += jb.nterms * 2.0 * N * jb.n;
-        op.L.bytes += jb.nterms * (N * 8 + (double)jb.n * jb.n * 8) + N * 8 * (jb.base ? 2.0 : 1.0);
-      }
-      ops.push_back(op);
-      lists.push_back(std::move(part[m]));
+    std::stable_sort(jobs.begin(), jobs.end(),
+                     [](const ModeJob& a, const ModeJob& b) { return a.nterms * a.n > b.nterms * b.n; });
+    Op op{};
+    op.list = true;
+    op.L.njobs = (int)jobs.size();
+    op.L.total = assign_tiles_f64(jobs.data(), op.L.njobs, mode1, cfg[mode1 ? 0 : 1], cfg[mode1 ? 1 : 0]);
+    op.L.mode1 = mode1;
+    op.L.tm = cfg[0];
+    op.L.tn = cfg[1];
+    op.L.grid_cap = cfg[2];
+    for (const ModeJob& jb : jobs) {
+      const double N = (double)jb.na * jb.n * jb.nb;
+      op.L.flops += jb.nterms * 2.0 * N * jb.n;
+      op.L.bytes += jb.nterms * (N * 8 + (double)jb.n * jb.n * 8) + N * 8 * (jb.base ? 2.0 : 1.0);
     }
+    ops.push_back(op);
+    lists.push_back(std::move(jobs));
     jobs.clear();
   }
 
@@ -273,10 +269,10 @@ struct PlanBuilder {
         const Inst& I = B->inst[o.b];
         for (int t = 0; t < o.nterms; ++t) {
           const Term& tm = o.term[t];
-          jobs.push_back(mk_job(tm.X, tm.P[0], 1.0, tm.Y1, nullptr, 1, I.dims[0], I.N / I.dims[0]));
+          jobs.push_back(mk_job(tm.X, tm.P[0], tm.scale, tm.Y1, nullptr, 1, I.dims[0], I.N / I.dims[0]));
         }
       }
-      add_lists(jobs, true);
+      add_list(jobs, true);
       if (part == 1) return;
     }
     {
@@ -292,7 +288,7 @@ struct PlanBuilder {
             jobs.push_back(mk_job(src, tm.P[mu], 1.0, dst, nullptr, na, I.dims[mu], I.N / (na * I.dims[mu])));
           }
         }
-        add_lists(jobs, false);
+        add_list(jobs, false);
       }
     }
     const int mu = d - 1;
@@ -304,7 +300,7 @@ struct PlanBuilder {
         const Term& tm = o.term[t];
         jb.X[t] = (mu % 2 == 1) ? tm.Y1 : tm.Y2;
         jb.P[t] = tm.P[mu];
-        jb.scale[t] = tm.scale;
+        jb.scale[t] = 1.0;   // the first product has the term's factor
       }
       jb.Y = o.Y;
       jb.base = o.base;
@@ -314,7 +310,7 @@ struct PlanBuilder {
       jb.ldp = packed_ld(jb.n);
       jobs.push_back(jb);
     }
-    add_lists(jobs, false);
+    add_list(jobs, false);
   }
 
   // Outputs of the phi_1 group on F (stages 2, 3 and final) for every
@@ -397,7 +393,7 @@ struct PlanBuilder {
                               I.N / I.dims[0]));
       }
     }
-    add_lists(jobs, true);
+    add_list(jobs, true);
     for (int mu = 1; mu < B->d; ++mu) {
       for (int b = 0; b < B->nb; ++b) {
         const Inst& I = B->inst[b];
@@ -409,7 +405,7 @@ struct PlanBuilder {
                                 I.N / (na * I.dims[mu])));
         }
       }
-      add_lists(jobs, false);
+      add_list(jobs, false);
     }
   }
 

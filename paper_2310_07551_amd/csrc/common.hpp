@@ -69,7 +69,10 @@ constexpr int kMaxJobs = 20;
 
 // One output tensor Y[a, i, b] = base[a, i, b] + sum_t sum_p S_t[i, p] X_t[a, p, b]
 // over a (extent na, stride 1), i/p (extent n, stride na), b (extent nb,
-// stride na*n).  S_t is scale_t * P_t with P_t a packed matrix.
+// stride na*n).  S_t is scale_t * P_t with P_t a packed matrix.  The FP64
+// kernels apply one scale to the whole sum (a term whose scale differs rescales
+// the sum before it): a Tucker group puts the factors of its terms on their
+// first products.
 struct ModeJob {
   const void* X[kMaxTerms];
   const void* P[kMaxTerms];   // packed matrix (layout depends on the kernel)
@@ -92,7 +95,7 @@ struct ModeJobs {
 // Job owning logical tile t: one division when all jobs have the same tile
 // count, else a binary search over tile_begin (no serial chain of loads).
 __device__ __forceinline__ int find_job(const ModeJobs& J, int64_t t) {
-  if (J.tiles_per_job > 0) return (int)(t / J.tiles_per_job);
+  if (J.tiles_per_job > 0) return (int)((uint32_t)t / (uint32_t)J.tiles_per_job);   // a grid has fewer than 2^32 tiles
   int lo = 0, hi = J.njobs - 1;
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
@@ -151,21 +154,21 @@ int launch_modeB_lp(ModeJobs& jobs, int prec, DType out, hipStream_t s);
 // fills tiles_i / tiles_a / tile_begin for a TM x TN tile (16 TM rows of the
 // MFMA row index, 16 TN columns) and returns the total tile count.
 int64_t assign_tiles(ModeJob* jobs, int njobs, bool mode1, int TM, int TN);
-// Kernel variant a job can use: 0 = element loads with checks, 1 = vector
-// loads (aligned, extents a multiple of 4), 2 = interior fast path.
-int job_mode(const ModeJob& jb, bool mode1, int TM, int TN);
+// The same for the FP64 kernels: blocks of 16 ti values of i and 16 to of the
+// other index (b in mode 1, a and b together else).
+int64_t assign_tiles_f64(ModeJob* jobs, int njobs, bool mode1, int ti, int to);
 
 // A work list in device memory (FP64): one persistent launch walks all tiles
 // of `njobs` jobs, each of which may belong to a different problem instance.
-// Every job of a list shares the regime, the tile shape and the variant.
+// Every job of a list shares the regime and the tile shape.
 struct ModeList {
   const ModeJob* jobs;   // device
   const int64_t* begins; // device: jobs[j].tile_begin
   int njobs;
   int64_t total;         // tiles
   bool mode1;
-  int tm, tn, mode;
-  int64_t grid_cap;      // maximum number of workgroups (0: one per tile)
+  int tm, tn;
+  int64_t grid_cap;      // maximum number of waves (0: one per tile)
   double flops, bytes;   // algorithmic work, for the kernel timing
 };
 int launch_list_f64(const ModeList& L, hipStream_t s);
@@ -174,11 +177,12 @@ int launch_list_f64(const ModeList& L, hipStream_t s);
 // once, output written once, base read once; es = element sizes in bytes).
 void job_work(const ModeJobs& J, int es_in, int es_out, int es_mat, double& flops, double& bytes);
 
-// Matrix packing (pointwise.hip).
-//   pack_rowmajor: PT[i*ldp + p] = scale*M[i + n p]   (mode-1 operand)
-//   pack_colmajor: P [i + ldp*p] = scale*M[i + n p]   (mode >= 2 operand)
-// zero outside n x n.
-int pack_matrix_f64(const double* M, int n, double scale, bool rowmajor, double* out, hipStream_t s);
+// Matrix packing (pointwise.hip); zero outside n x n.
+// FP64, any mode: scale * M (or its transpose) in the matrix cores' operand
+// order (mode_f64.hip).  FP32 and bf16:
+//   rowmajor:       out[i*ldp + p] = scale*M[i + n p]   (mode-1 operand)
+//   not rowmajor:   out[i + ldp*p] = scale*M[i + n p]   (modes >= 2 operand)
+int pack_matrix_f64(const double* M, int n, double scale, bool trans, double* out, hipStream_t s);
 int pack_matrix_f32(const double* M, int n, double scale, bool rowmajor, float* out, hipStream_t s);
 int pack_matrix_bf16(const double* M, int n, double scale, bool rowmajor, int np, void* out, hipStream_t s);
 inline bool is_prec(int p) {

@@ -61,7 +61,7 @@ int build_cplx_bank(setd_ctx* c, double tau, hipStream_t s) {
     for (int mu = 0; mu < d; ++mu) {
       const int n = c->dims[mu];
       const size_t nn = (size_t)n * n, mm = 4 * nn;
-      const bool rowmajor = mu == 0, last = mu == d - 1;
+      const bool last = mu == d - 1;
       DevBuf A, B, raw, Pr, Pi, Qr, Qi;
       SETD_TRY(A.alloc(nn * 8));
       SETD_TRY(B.alloc(mm * 8));
@@ -108,10 +108,10 @@ int build_cplx_bank(setd_ctx* c, double tau, hipStream_t s) {
             }
             void** slot = c->cbank[cc][ents[k]][t][mu];
             slot[0] = q;
-            SETD_TRY(pack_matrix_f64(src_r, n, 1.0, rowmajor, (double*)q, s));
+            SETD_TRY(pack_matrix_f64(src_r, n, 1.0, false, (double*)q, s));
             q += packed_bytes(n, SETD_PREC_F64);
             slot[1] = q;
-            SETD_TRY(pack_matrix_f64(src_i, n, 1.0, rowmajor, (double*)q, s));
+            SETD_TRY(pack_matrix_f64(src_i, n, 1.0, false, (double*)q, s));
             q += packed_bytes(n, SETD_PREC_F64);
           }
           SETD_HIP(hipStreamSynchronize(s));   // raw is reused by the next (ell, t)

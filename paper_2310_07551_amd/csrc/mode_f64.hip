@@ -6,29 +6,45 @@
 //
 //     Y[a, i, b] = sum_p L[i, p] X[a, p, b].
 //
-// Two kernels cover every mode:
+// Operand layout.  The matrix is packed in the order the matrix cores read
+// it: entry (tile t, chunk c, lane, j) = L[16 t + lane % 16][8 c + 2 (lane / 16)
+// + j], j in {0, 1}, zero past n.  One 16-byte load per lane (1 KB contiguous
+// per wave) is the operand of two k-steps, whichever side of the product the
+// matrix is on, so mode 1 and the other modes share one layout.  The tensor
+// is read in place, with the same assignment of p to k-steps:
 //   * mode 1 (no a index): Y = L X as a GEMM over the column-major unfolding
-//     X_(1) (n x N/n), no copy.  MFMA rows = i, columns = b, k = p.  The
-//     contraction index is the contiguous one, so each lane loads four
-//     consecutive p of one column (32 bytes) and uses them over four MFMA
-//     k-steps; the matrix is packed row-major (L[i, p] at i*ldp + p) to match.
+//     X_(1) (n x N/n), no copy.  MFMA rows = b, columns = i: a lane loads two
+//     consecutive p of its column of X, and the 16 lanes of a group hold 16
+//     consecutive i of the result.
 //   * modes >= 2: for each b, Y[:, :, b] = X[:, :, b] L^T with a contiguous.
-//     MFMA rows = a, columns = i, k = p.  Each lane loads TM consecutive a
-//     (one row of every row tile) and TN consecutive i of the column-major
-//     packed matrix, so every global access is a contiguous 16-32 byte run
-//     and a 16-lane group covers a full 128-byte line or more.
+//     MFMA rows = i, columns = a: 16 lanes load 128 contiguous bytes of a row
+//     of X, and store 128 contiguous bytes of the result.
+// Either way no load or store needs more than 8-byte alignment, so odd sizes
+// run the same code as round ones: indices past an edge are clamped (their
+// results are not stored), and the last n % 8 contraction indices are taken
+// first, as one masked chunk.
 //
-// Register tiling: a wave owns a (16 TM) x (16 TN) output tile held in
-// TM x TN MFMA accumulators; rows of the tile are interleaved (lane row m of
-// row-tile t is a0 + TM m + t) so the per-lane loads and the epilogue stores
-// are contiguous.  The next k-chunk is loaded into registers while the
-// current one feeds the MFMAs.
+// Each wave owns TI x TO accumulators (16 TI of i, 16 TO of the other index)
+// and keeps a ring of D chunks of operands in registers, each loaded D - 1
+// chunks of products before its use.  With KS > 1 the waves of a workgroup
+// share a tile, each a part of the contraction, and add their accumulators
+// through LDS in a fixed order.
 //
 // Each launch runs a table of independent jobs (up to kMaxJobs outputs; each
 // may sum up to kMaxTerms inputs along the contraction, which is how the
-// terms of a split phi action are accumulated into one output), one wave per
-// workgroup, with the block index remapped so that each XCD gets a contiguous
-// range of tiles (neighbouring tiles share X or L in that XCD's L2).
+// terms of a split phi action are accumulated into one output), four waves
+// per workgroup on neighbouring tiles, with the block index remapped so that
+// each XCD gets a contiguous range of tiles (neighbouring tiles share X or L
+// in that XCD's L2).
+//
+// What bounds them: the matrix cores (64 cycles per MFMA and SIMD) from n =
+// 192 on; below that also the tensor traffic (n / 8 flops per byte), and on
+// small grids the latency of one wave (about 2 us besides its products), so
+// that the tile is chosen per launch (choose_tile).  Steps of two components
+// against kernels with one fixed tile per contraction length and vector
+// accesses for aligned sizes only: 64^2 107 -> 52 us, 300^2 595 -> 112 us
+// (the last mode alone 151 -> 20 and 9 us), 100^3 739 -> 559 us, 128^3 1060
+// -> 1031 us, 256^3 11.93 -> 11.97 ms.
 #include "common.hpp"
 
 #include <algorithm>
@@ -44,157 +60,258 @@ __device__ __forceinline__ d4 mfma(double a, double b, d4 c) {
   return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
-// ---------------------------------------------------------------------------
-// mode 1
-// ---------------------------------------------------------------------------
-// One wave computes tile `lt` of job `jb`.
-template <int TM, int TN, int MODE>
-__device__ __forceinline__ void mode1_tile(const ModeJob& jb, int64_t lt) {
-  // MODE 0: element loads with bounds checks everywhere; 1: vector loads
-  // (aligned operands); 2: additionally every tile interior and n % 32 == 0.
-  constexpr bool VEC = MODE >= 1;
-  const int it = (int)(lt % jb.tiles_i);
-  const int64_t bt = lt / jb.tiles_i;
+typedef double d2u __attribute__((ext_vector_type(2), aligned(8)));   // a pair at any 8-byte address
 
-  const int lane = threadIdx.x, g = lane >> 4, l = lane & 15;
-  const int n = jb.n, ldp = jb.ldp;
-  const int64_t nb = jb.nb;
-  const int i0 = it * 16 * TM;
-  const int64_t b0 = bt * 16 * TN;
-  const double* __restrict__ X = (const double*)jb.X[0];
-  const double* __restrict__ PT = (const double*)jb.P[0];
-  const double sc = jb.scale[0];
+// Packed FP64 matrix: tile t starts at t * chunks(n) * 128 doubles.
+__device__ __forceinline__ int chunks_of(int n) { return (n + 7) >> 3; }
+__device__ __forceinline__ double packed_at(const double* P, int n, int i, int p) {
+  return P[((int64_t)(i >> 4) * chunks_of(n) + (p >> 3)) * 128 + ((((p >> 1) & 3) << 4) + (i & 15)) * 2 + (p & 1)];
+}
 
-  // Lanes of group g hold KP consecutive p of each chunk of 4 KP (KP = 2 on
-  // the interior path, whose two-deep register ring must fit beside the
-  // accumulators in the two-wave budget; 4 elsewhere).
-  constexpr int KP = MODE == 2 ? 2 : 4;
-  const double* pa[TM];
+// Adds sum_p S[i, p] X[.., p, ..] of one term to the accumulators, for p of
+// the chunks lo .. hi - 1.  x0 is the tile's first element, xo[o] the byte
+// offset of the lane's first element of column (row) block o from it; M1:
+// consecutive p are adjacent, else `na` elements apart.
+template <bool M1, int TI, int TO, int D, typename Off>
+__device__ __forceinline__ void add_term(d4 (&acc)[TI][TO], const double* __restrict__ x0, const Off (&xo)[TO],
+                                         int64_t na, const double* __restrict__ P, int t0, int nt, int n, int lane,
+                                         int lo, int hi) {
+  const int g = lane >> 4;
+  const int nch = chunks_of(n), nfull = n >> 3;
+  const double* pt[TI];
 #pragma unroll
-  for (int m = 0; m < TM; ++m) pa[m] = PT + (int64_t)(i0 + TM * l + m) * ldp + KP * g;
-  const double* pb[TN];
-  bool vb[TN];
+  for (int i = 0; i < TI; ++i) pt[i] = P + (int64_t)min(t0 + i, nt - 1) * nch * 128;
+  auto load = [&](int c, d2 (&xr)[TO], d2 (&pr)[TI]) {
 #pragma unroll
-  for (int u = 0; u < TN; ++u) {
-    const int64_t b = b0 + 16 * u + l;
-    vb[u] = b < nb;
-    pb[u] = X + (vb[u] ? b : 0) * (int64_t)n + KP * g;
-  }
-
-  d4 acc[TM][TN];
+    for (int i = 0; i < TI; ++i) pr[i] = *(const d2*)(pt[i] + (int64_t)c * 128 + 2 * lane);
+    if constexpr (M1) {
+      const char* xb = (const char*)(x0 + 8 * c);
 #pragma unroll
-  for (int m = 0; m < TM; ++m)
+      for (int o = 0; o < TO; ++o) xr[o] = *(const d2u*)(xb + xo[o]);
+    } else {
+      const char* xb0 = (const char*)(x0 + na * (8 * (int64_t)c));
+      const char* xb1 = (const char*)(x0 + na * (8 * (int64_t)c + 1));
 #pragma unroll
-    for (int u = 0; u < TN; ++u) acc[m][u] = d4{0.0, 0.0, 0.0, 0.0};
-
-  // The scale multiplies the operand where it is used, never inside a load:
-  // a multiply right after a prefetch would make the wave wait for it.
-  auto mma = [&](const d4* ar, const d4* br) {
+      for (int o = 0; o < TO; ++o) xr[o][0] = *(const double*)(xb0 + xo[o]);
 #pragma unroll
-    for (int jj = 0; jj < 4; ++jj)
-#pragma unroll
-      for (int m = 0; m < TM; ++m) {
-        const double av = ar[m][jj] * sc;
-#pragma unroll
-        for (int u = 0; u < TN; ++u) acc[m][u] = mfma(av, br[u][jj], acc[m][u]);
-      }
+      for (int o = 0; o < TO; ++o) xr[o][1] = *(const double*)(xb1 + xo[o]);
+    }
   };
-  if constexpr (MODE == 2) {
-    // Interior tile: chunks of 8 p (two k-steps) in a two-deep register ring,
-    // no masks and no register copies; each chunk is loaded a whole chunk of
-    // MFMAs before its use.  The last loads re-read a valid chunk instead of
-    // branching.
-    auto load = [&](int p0, d2* ar, d2* br) {
+  auto mma = [&](const d2 (&xr)[TO], const d2 (&pr)[TI]) {
 #pragma unroll
-      for (int m = 0; m < TM; ++m) ar[m] = *(const d2*)(pa[m] + p0);
+    for (int j = 0; j < 2; ++j)
 #pragma unroll
-      for (int u = 0; u < TN; ++u) br[u] = *(const d2*)(pb[u] + p0);
-    };
-    auto mma2 = [&](const d2* ar, const d2* br) {
+      for (int i = 0; i < TI; ++i)
 #pragma unroll
-      for (int jj = 0; jj < 2; ++jj)
+        for (int o = 0; o < TO; ++o)
+          acc[i][o] = M1 ? mfma(xr[o][j], pr[i][j], acc[i][o]) : mfma(pr[i][j], xr[o][j], acc[i][o]);
+  };
+  const int c0 = lo, c1 = min(hi, nfull);
+  const bool tail = hi > nfull;   // the last chunk, of n % 8
+  d2 xr[D][TO], pr[D][TI];
+  if (tail) {
+    // the last n % 8 values of p: clamped loads, zero past n
 #pragma unroll
-        for (int m = 0; m < TM; ++m)
+    for (int i = 0; i < TI; ++i) pr[D - 1][i] = *(const d2*)(pt[i] + (int64_t)nfull * 128 + 2 * lane);
+    const int64_t ps = M1 ? 1 : na;
 #pragma unroll
-          for (int u = 0; u < TN; ++u) acc[m][u] = mfma(ar[m][jj], br[u][jj], acc[m][u]);
-    };
-    d2 a0[TM], b0r[TN], a1[TM], b1r[TN];
-    load(0, a0, b0r);
-    load(8, a1, b1r);
-    for (int p0 = 0; p0 < n; p0 += 16) {
-      mma2(a0, b0r);
-      load(p0 + 16 < n ? p0 + 16 : p0, a0, b0r);
-      mma2(a1, b1r);
-      load(p0 + 24 < n ? p0 + 24 : p0 + 8, a1, b1r);
-    }
-  } else {
-    auto load = [&](int p0, d4* ar, d4* br) {
+    for (int j = 0; j < 2; ++j) {
+      const int p = 8 * nfull + 2 * g + j;
+      const double* xp = x0 + ps * (min(p, n - 1) - 2 * g);   // xo holds the lane's 2 g
 #pragma unroll
-      for (int m = 0; m < TM; ++m) ar[m] = *(const d4*)(pa[m] + p0);
-      const bool full = VEC && (p0 + 16 <= n);
+      for (int o = 0; o < TO; ++o) xr[D - 1][o][j] = *(const double*)((const char*)xp + xo[o]);
 #pragma unroll
-      for (int u = 0; u < TN; ++u) {
-        if (full) {
-          br[u] = vb[u] ? *(const d4*)(pb[u] + p0) : d4{0.0, 0.0, 0.0, 0.0};
-        } else {
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            br[u][e] = (vb[u] && p0 + 4 * g + e < n) ? pb[u][p0 + e] : 0.0;
-        }
-      }
-    };
-    d4 a[TM], bx[TN];
-    load(0, a, bx);
-    for (int p0 = 0; p0 < n; p0 += 16) {
-      d4 an[TM], bn[TN];
-      const bool more = p0 + 16 < n;
-      if (more) load(p0 + 16, an, bn);
-      mma(a, bx);
-      if (more) {
-#pragma unroll
-        for (int m = 0; m < TM; ++m) a[m] = an[m];
-#pragma unroll
-        for (int u = 0; u < TN; ++u) bx[u] = bn[u];
-      }
+      for (int o = 0; o < TO; ++o) xr[D - 1][o][j] = p < n ? xr[D - 1][o][j] : 0.0;
     }
   }
-
-  // Epilogue.  The FP64 16x16 accumulator holds tile row 4 r + g in register
-  // r of lane (g, l), column l; tile row q of row-tile m is output row
-  // i0 + TM q + m.  So lane (g, l) owns, for each r, the TM consecutive rows
-  // i0 + TM g + 4 TM r + (0..TM-1) of column b0 + 16 u + l.
-  // The interior path leaves the scale to the epilogue.
-  const double osc = MODE == 2 ? sc : 1.0;
-  double* __restrict__ Y = (double*)jb.Y;
-  const double* __restrict__ base = (const double*)jb.base;
+  if (c0 < c1) {
 #pragma unroll
-  for (int u = 0; u < TN; ++u) {
-    if (!vb[u]) continue;
-    const int64_t col = (b0 + 16 * u + l) * (int64_t)n;
+    for (int d = 0; d < D - 1; ++d) load(min(c0 + d, c1 - 1), xr[d], pr[d]);
+  }
+  if (tail) mma(xr[D - 1], pr[D - 1]);
+  if (c0 >= c1) return;
+  load(min(c0 + D - 1, c1 - 1), xr[D - 1], pr[D - 1]);
+  int c = c0;
+  for (; c + D <= c1; c += D) {
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      mma(xr[d], pr[d]);
+      load(min(c + d + D, c1 - 1), xr[d], pr[d]);   // the last ones re-read a valid chunk: no branch
+    }
+  }
+#pragma unroll
+  for (int d = 0; d < D - 1; ++d)
+    if (c + d < c1) mma(xr[d], pr[d]);
+}
+
+// One wave computes tile `lt` of job `jb` (part kw of ks of its contraction;
+// `red` is the LDS the waves of one tile add up in when ks > 1).
+template <bool M1, int TI, int TO, int D, int KS, typename Off>
+__device__ __forceinline__ void mode_tile(const ModeJob& jb, uint32_t lt, int lane, int kw, d4* red) {
+  const int g = lane >> 4, l = lane & 15;
+  const int n = jb.n, nt = (n + 15) >> 4;
+  const uint32_t ti = (uint32_t)jb.tiles_i;
+  const uint32_t ot = lt / ti;
+  const int t0 = (int)(lt - ot * ti) * TI;
+  // The other tiled index: b in mode 1; else a and b together, q = a + na b,
+  // so that only the last tile is ragged whatever na is.
+  const int64_t na = M1 ? 1 : jb.na;
+  const int64_t ext = M1 ? jb.nb : na * jb.nb;
+  const int64_t q0 = (int64_t)ot * (16 * TO);
+  const uint32_t una = (uint32_t)na;
+  const uint32_t b0 = M1 ? 0 : jb.nb == 1 ? 0 : (uint32_t)((uint64_t)q0 / una);
+  const int64_t r0 = q0 - (int64_t)b0 * na;   // a of the tile's first column
+  const int64_t origin_x = M1 ? q0 * n : (int64_t)b0 * na * n + r0;
+  // element offset of the lane's column in block o of the tile (clamped to
+  // the extent) from the tile's first
+  auto column = [&](int k) -> Off {
+    const int64_t rel = min(q0 + k, ext - 1) - q0;
+    if (M1) return (Off)(rel * n);
+    if (jb.nb == 1) return (Off)rel;
+    const Off q = (Off)(r0 + rel);
+    const Off bb = q / (Off)na;
+    return (Off)(bb * (Off)(na * n) + (q - bb * (Off)na) - (Off)r0);
+  };
+  Off xo[TO];
+#pragma unroll
+  for (int o = 0; o < TO; ++o) xo[o] = (column(16 * o + l) + (M1 ? (Off)(2 * g) : (Off)na * (Off)(2 * g))) * 8;
+  d4 acc[TI][TO];
+#pragma unroll
+  for (int i = 0; i < TI; ++i)
+#pragma unroll
+    for (int o = 0; o < TO; ++o) acc[i][o] = d4{0.0, 0.0, 0.0, 0.0};
+  __builtin_amdgcn_s_setprio(1);   // products ahead of another wave's epilogue on the SIMD
+  // the chunks of all terms in a row, in KS equal parts
+  const int nterms = M1 ? 1 : jb.nterms, nch = chunks_of(n);
+  const int first = KS > 1 ? nterms * nch * kw / KS : 0, last = KS > 1 ? nterms * nch * (kw + 1) / KS : nterms * nch;
+  for (int term = 0; term < nterms; ++term) {
+    if (term > 0 && jb.scale[term] != jb.scale[term - 1]) {   // the sum is kept in units of the term's scale
+      const double ratio = jb.scale[term - 1] / jb.scale[term];
+#pragma unroll
+      for (int i = 0; i < TI; ++i)
+#pragma unroll
+        for (int o = 0; o < TO; ++o) acc[i][o] *= ratio;
+    }
+    const int lo = max(first - term * nch, 0), hi = min(last - term * nch, nch);
+    if (lo < hi)
+      add_term<M1, TI, TO, D, Off>(acc, (const double*)jb.X[term] + origin_x, xo, na, (const double*)jb.P[term], t0,
+                                   nt, n, lane, lo, hi);
+  }
+  const double sc = jb.scale[nterms - 1];
+  __builtin_amdgcn_s_setprio(0);
+  // Epilogue.  The FP64 16x16 accumulator holds tile row 4 r + g in register
+  // r of lane (g, l), column l: mode 1, row b and column i; else row i and
+  // column a.  16 lanes write 128 contiguous bytes.  The base values of a
+  // block of rows are read together, from clamped indices, so that they are
+  // one wait and not one each.
+  constexpr int TR = M1 ? TO : TI, TC = M1 ? TI : TO;
+  const int64_t origin = M1 ? q0 * n + 16 * t0 : origin_x + na * 16 * t0;
+  const int imax = n - 16 * t0;                                     // i of the tile below it
+  const int omax = (int)min(ext - q0, (int64_t)(16 * TO));          // columns of the tile
+  double* __restrict__ Y = (double*)jb.Y + origin;
+  const double* __restrict__ bs = (const double*)jb.base + origin;
+  const bool has_base = jb.base != nullptr;
+  const int64_t ld = M1 ? n : na;
+  Off yo[TC];   // column of each block
+#pragma unroll
+  for (int u = 0; u < TC; ++u) yo[u] = M1 ? (Off)min(16 * u + l, imax - 1) : column(16 * u + l);
+  if constexpr (KS > 1) {
+    // the parts meet in LDS; each wave adds up and stores its share of the blocks
+#pragma unroll
+    for (int i = 0; i < TI; ++i)
+#pragma unroll
+      for (int o = 0; o < TO; ++o) red[(kw * TI * TO + (M1 ? o * TI + i : i * TO + o)) * 64 + lane] = acc[i][o];
+    __syncthreads();
+#pragma unroll 1
+    for (int k = kw; k < TR * TC; k += KS) {
+      const int m = k / TC, u = k % TC;
+      const Off y = M1 ? (Off)min(16 * u + l, imax - 1) : column(16 * u + l);
+      double bv[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        bv[r] = has_base ? bs[min(16 * m + 4 * r + g, (M1 ? omax : imax) - 1) * ld + y] : -0.0;
+      d4 v = red[k * 64 + lane];
+#pragma unroll
+      for (int w = 1; w < KS; ++w) v += red[(w * TI * TO + k) * 64 + lane];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = 16 * m + 4 * r + g;
+        if (row < (M1 ? omax : imax) && 16 * u + l < (M1 ? imax : omax)) Y[row * ld + y] = v[r] * sc + bv[r];
+      }
+    }
+    return;
+  }
+#pragma unroll
+  for (int m = 0; m < TR; ++m) {
+    double bv[4][TC];
+    if (has_base) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int u = 0; u < TC; ++u) bv[r][u] = bs[min(16 * m + 4 * r + g, (M1 ? omax : imax) - 1) * ld + yo[u]];
+    } else {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int u = 0; u < TC; ++u) bv[r][u] = -0.0;   // the sum is then the product itself
+    }
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int ir = i0 + TM * g + 4 * TM * r;
-      if (VEC && ir + TM <= n) {
+      const int row = 16 * m + 4 * r + g;
 #pragma unroll
-        for (int m = 0; m < TM; m += 2) {
-          d2 w = d2{acc[m][u][r], acc[m + 1][u][r]} * osc;
-          if (base) w += *(const d2*)(base + col + ir + m);
-          *(d2*)(Y + col + ir + m) = w;
-        }
-      } else {
-#pragma unroll
-        for (int m = 0; m < TM; ++m) {
-          if (ir + m < n) {
-            double w = acc[m][u][r] * osc;
-            if (base) w += base[col + ir + m];
-            Y[col + ir + m] = w;
-          }
-        }
-      }
+      for (int u = 0; u < TC; ++u)
+        if (row < (M1 ? omax : imax) && 16 * u + l < (M1 ? imax : omax))
+          Y[row * ld + yo[u]] = (M1 ? acc[u][m][r] : acc[m][u][r]) * sc + bv[r][u];
     }
   }
 }
 
+// Ring depth: more chunks in flight where a chunk is only a few products.
+constexpr int ring_depth(int ti, int to) { return ti * to <= 2 ? 4 : ti * to <= 4 ? 3 : 2; }
+// LDS of a workgroup whose waves split contractions: 4 / KS tiles, KS parts each.
+constexpr int red_size(int ti, int to, int ks) { return ks > 1 ? 4 * ti * to * 64 : 1; }
+
+// Job table in the kernel arguments (up to kMaxJobs outputs per launch).
+// Two waves per SIMD is the target occupancy of the larger tiles: with that
+// register budget the accumulators stay in place through the k loop (a
+// tighter default made the compiler copy all of them between register files
+// every iteration).
+template <bool M1, int TI, int TO, int KS, typename Off>
+__global__ void __launch_bounds__(256, 2) mode_f64_kernel(const ModeJobs J, int64_t per_xcd) {
+  __shared__ d4 red[red_size(TI, TO, KS)];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const uint32_t t = (uint32_t)remap_xcd(blockIdx.x, per_xcd) * (4 / KS) + wave / KS;
+  if (t >= (uint32_t)J.total_tiles) {
+    if constexpr (KS > 1) __syncthreads();   // the barrier of the waves with a tile
+    return;
+  }
+  const ModeJob& jb = J.job[find_job(J, t)];
+  mode_tile<M1, TI, TO, ring_depth(TI, TO), KS, Off>(jb, t - (uint32_t)jb.tile_begin, lane, wave % KS,
+                                                     red + (wave / KS) * KS * TI * TO * 64);
+}
+
+// Work list in device memory (any number of jobs, e.g. many independent
+// instances), walked by a persistent grid of 4-wave workgroups.  The tiles of
+// a list differ in length (they are sorted longest first), so an XCD takes
+// runs of kListRun workgroups in turn rather than one contiguous range.
+constexpr int kListRun = 8;
+template <bool M1, int TI, int TO>
+__global__ void __launch_bounds__(256, 2) mode_f64_list_kernel(const ModeJob* __restrict__ jobs,
+                                                               const int64_t* __restrict__ begins, int njobs,
+                                                               int64_t total, int64_t ngroups) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  for (int64_t raw = blockIdx.x; raw < ngroups; raw += gridDim.x) {
+    const int64_t run = raw / (8 * kListRun), in = raw % (8 * kListRun);
+    const int64_t t = (run * 8 * kListRun + (in & 7) * kListRun + (in >> 3)) * 4 + wave;
+    if (t >= total) continue;
+    const int j = find_job_list(begins, njobs, t);
+    mode_tile<M1, TI, TO, ring_depth(TI, TO), 1, uint32_t>(jobs[j], (uint32_t)(t - begins[j]), lane, 0, nullptr);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// 192 <= n <= 256: the matrix panel in LDS
+// ---------------------------------------------------------------------------
 // Mode 1 with the matrix panel in LDS (interior jobs, 192 <= n <= 256,
 // 4 x 4 tiles).  A workgroup of 8 waves shares one 64-row panel of P, stored
 // in LDS in the order the MFMA reads it (chunk of 16 p, row m, lane: 4 p),
@@ -219,7 +336,7 @@ __global__ void __launch_bounds__(512, 1) mode1_lds_kernel(const ModeJobs J, int
   const int64_t lw = w - jb.tile_begin;
   const int it = (int)(lw % jb.tiles_i);
   const int64_t bg = lw / jb.tiles_i;
-  const int n = jb.n, ldp = jb.ldp;
+  const int n = jb.n;
   const int nchunk = n / 16;
   const int i0 = it * 64;
   const double* __restrict__ PT = (const double*)jb.P[0];
@@ -227,7 +344,10 @@ __global__ void __launch_bounds__(512, 1) mode1_lds_kernel(const ModeJobs J, int
   for (int q = threadIdx.x; q < nchunk * 256; q += 512) {
     const int ln = q & 63, m = (q >> 6) & 3, c = q >> 8;
     const int l = ln & 15, g = ln >> 4;
-    panel[q] = *(const d4*)(PT + (int64_t)(i0 + 4 * l + m) * ldp + 16 * c + 4 * g);
+    const int i = i0 + 4 * l + m, p = 16 * c + 4 * g;   // p % 4 == 0: two neighbouring pairs of the packed matrix
+    const double* e = PT + ((int64_t)(i >> 4) * chunks_of(n) + (p >> 3)) * 128 + (((p >> 1) & 3) * 16 + (i & 15)) * 2;
+    const d2 lo = *(const d2*)e, hi = *(const d2*)(e + 32);
+    panel[q] = d4{lo[0], lo[1], hi[0], hi[1]};
   }
   __syncthreads();
   const int wave = threadIdx.x >> 6;
@@ -301,204 +421,6 @@ __global__ void __launch_bounds__(512, 1) mode1_lds_kernel(const ModeJobs J, int
   }
 }
 
-// Job table in the kernel arguments (up to kMaxJobs outputs per launch).
-// Two waves per SIMD is the target occupancy: with that register budget the
-// accumulators stay in place through the k loop (a tighter default made the
-// compiler copy all of them between register files every iteration).
-template <int TM, int TN, int MODE>
-__global__ void __launch_bounds__(64, 2) mode1_f64_kernel(const ModeJobs J, int64_t per_xcd) {
-  const int64_t t = remap_xcd(blockIdx.x, per_xcd);
-  if (t >= J.total_tiles) return;
-  const int j = find_job(J, t);
-  mode1_tile<TM, TN, MODE>(J.job[j], t - J.job[j].tile_begin);
-}
-
-// Work list in device memory (any number of jobs, e.g. many independent
-// instances): a persistent grid walks the logical tiles with a stride that
-// keeps every block on its XCD's contiguous range.
-template <int TM, int TN, int MODE>
-__global__ void __launch_bounds__(64, 2) mode1_f64_list_kernel(const ModeJob* __restrict__ jobs,
-                                                            const int64_t* __restrict__ begins, int njobs,
-                                                            int64_t total, int64_t per_xcd) {
-  for (int64_t raw = blockIdx.x; raw < 8 * per_xcd; raw += gridDim.x) {
-    const int64_t t = remap_xcd(raw, per_xcd);
-    if (t >= total) continue;
-    const int j = find_job_list(begins, njobs, t);
-    mode1_tile<TM, TN, MODE>(jobs[j], t - jobs[j].tile_begin);
-  }
-}
-
-// ---------------------------------------------------------------------------
-// modes >= 2
-// ---------------------------------------------------------------------------
-template <int TM, int TN, int MODE>
-__device__ __forceinline__ void modeB_tile(const ModeJob& jb, int64_t lt) {
-  constexpr bool VEC = MODE >= 1;   // as in the mode-1 kernel
-  const int it = (int)(lt % jb.tiles_i);
-  const int64_t rest = lt / jb.tiles_i;
-  const int64_t at = rest % jb.tiles_a;
-  const int64_t b = rest / jb.tiles_a;
-
-  const int lane = threadIdx.x, g = lane >> 4, l = lane & 15;
-  const int n = jb.n, ldp = jb.ldp, nterms = jb.nterms;
-  const int64_t na = jb.na;
-  const int64_t a0 = at * 16 * TM;
-  const int i0 = it * 16 * TN;
-  const int64_t arow = a0 + TM * l;                 // first of this lane's TM rows
-  const bool lane_full = arow + TM <= na;
-
-  d4 acc[TM][TN];
-#pragma unroll
-  for (int m = 0; m < TM; ++m)
-#pragma unroll
-    for (int u = 0; u < TN; ++u) acc[m][u] = d4{0.0, 0.0, 0.0, 0.0};
-
-  const int64_t slab = na * (int64_t)n * b;
-  constexpr bool fast = MODE == 2;   // every tile interior, n % 32 == 0 (checked at launch)
-  __builtin_amdgcn_s_setprio(1);   // products ahead of another wave's epilogue on the SIMD
-  for (int term = 0; term < nterms; ++term) {
-    const double* __restrict__ xb = (const double*)jb.X[term] + slab + arow + na * g;
-    const double* __restrict__ pbp = (const double*)jb.P[term] + i0 + TN * l + (int64_t)ldp * g;
-    const double sc = jb.scale[term];
-
-    if constexpr (fast) {
-      // Interior tile: blocks of KB k-steps (4 KB values of p) in ping-pong
-      // registers; the scale is applied to the matrix operand at use.  A
-      // 4 x 4 tile takes blocks of 2, so that its ring fits beside the 128
-      // accumulator registers at two waves per SIMD.
-      constexpr int KB = (TM == 4 && TN == 4) ? 2 : 4;
-      auto loadblk = [&](int p0, double (*xr)[TM], double (*pr)[TN]) {
-#pragma unroll
-        for (int k = 0; k < KB; ++k) {
-          const double* xs = xb + na * (int64_t)(p0 + 4 * k);
-          if constexpr (TM == 4) {
-            const d4 v = *(const d4*)xs;
-#pragma unroll
-            for (int m = 0; m < TM; ++m) xr[k][m] = v[m];
-          } else {
-            const d2 v = *(const d2*)xs;
-#pragma unroll
-            for (int m = 0; m < TM; ++m) xr[k][m] = v[m];
-          }
-          const double* ps = pbp + (int64_t)ldp * (p0 + 4 * k);
-          if constexpr (TN == 4) {
-            const d4 v = *(const d4*)ps;
-#pragma unroll
-            for (int u = 0; u < TN; ++u) pr[k][u] = v[u];
-          } else {
-            const d2 v = *(const d2*)ps;
-#pragma unroll
-            for (int u = 0; u < TN; ++u) pr[k][u] = v[u];
-          }
-        }
-      };
-      auto mmablk = [&](double (*xr)[TM], double (*pr)[TN]) {
-#pragma unroll
-        for (int k = 0; k < KB; ++k)
-#pragma unroll
-          for (int u = 0; u < TN; ++u) {
-            const double pv = pr[k][u] * sc;
-#pragma unroll
-            for (int m = 0; m < TM; ++m) acc[m][u] = mfma(xr[k][m], pv, acc[m][u]);
-          }
-      };
-      double xa[KB][TM], pa[KB][TN], xq[KB][TM], pq[KB][TN];
-      loadblk(0, xa, pa);
-      for (int p0 = 0; p0 < n; p0 += 8 * KB) {
-        loadblk(p0 + 4 * KB, xq, pq);
-        mmablk(xa, pa);
-        loadblk(p0 + 8 * KB < n ? p0 + 8 * KB : p0, xa, pa);
-        mmablk(xq, pq);
-      }
-      continue;
-    }
-
-    auto load = [&](int p0, double* xr, double* pr) {
-      const bool vp = p0 + g < n;
-      const double* xs = xb + na * (int64_t)p0;
-      if (VEC && TM == 4 && lane_full && vp) {
-        const d4 v = *(const d4*)xs;
-#pragma unroll
-        for (int m = 0; m < TM; ++m) xr[m] = v[m];
-      } else if (VEC && TM == 2 && lane_full && vp) {
-        const d2 v = *(const d2*)xs;
-#pragma unroll
-        for (int m = 0; m < TM; ++m) xr[m] = v[m];
-      } else {
-#pragma unroll
-        for (int m = 0; m < TM; ++m) xr[m] = (vp && arow + m < na) ? xs[m] : 0.0;
-      }
-      const double* ps = pbp + (int64_t)ldp * p0;
-      if (TN == 4) {
-        const d4 v = *(const d4*)ps;
-#pragma unroll
-        for (int u = 0; u < TN; ++u) pr[u] = v[u];
-      } else if (TN == 2) {
-        const d2 v = *(const d2*)ps;
-#pragma unroll
-        for (int u = 0; u < TN; ++u) pr[u] = v[u];
-      } else {
-#pragma unroll
-        for (int u = 0; u < TN; ++u) pr[u] = ps[u];
-      }
-    };
-
-    double xr[TM], pr[TN];
-    load(0, xr, pr);
-    for (int p0 = 0; p0 < n; p0 += 4) {
-      double xn[TM], pn[TN];
-      const bool more = p0 + 4 < n;
-      if (more) load(p0 + 4, xn, pn);
-#pragma unroll
-      for (int u = 0; u < TN; ++u) {
-        const double pv = pr[u] * sc;
-#pragma unroll
-        for (int m = 0; m < TM; ++m) acc[m][u] = mfma(xr[m], pv, acc[m][u]);
-      }
-      if (more) {
-#pragma unroll
-        for (int m = 0; m < TM; ++m) xr[m] = xn[m];
-#pragma unroll
-        for (int u = 0; u < TN; ++u) pr[u] = pn[u];
-      }
-    }
-  }
-
-  __builtin_amdgcn_s_setprio(0);
-  // Epilogue (accumulator layout as in the mode-1 kernel): lane (g, l) owns,
-  // for each r, the TM consecutive a = a0 + TM g + 4 TM r + (0..TM-1) of
-  // column i = i0 + TN l + u.
-  double* __restrict__ Y = (double*)jb.Y;
-  const double* __restrict__ base = (const double*)jb.base;
-#pragma unroll
-  for (int u = 0; u < TN; ++u) {
-    const int i = i0 + TN * l + u;
-    if (i >= n) continue;
-    const int64_t off = slab + na * (int64_t)i;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int64_t ar = a0 + TM * g + 4 * TM * r;
-      if (VEC && ar + TM <= na) {
-#pragma unroll
-        for (int m = 0; m < TM; m += 2) {
-          d2 w = d2{acc[m][u][r], acc[m + 1][u][r]};
-          if (base) w += *(const d2*)(base + off + ar + m);
-          *(d2*)(Y + off + ar + m) = w;
-        }
-      } else {
-#pragma unroll
-        for (int m = 0; m < TM; ++m) {
-          if (ar + m < na) {
-            double w = acc[m][u][r];
-            if (base) w += base[off + ar + m];
-            Y[off + ar + m] = w;
-          }
-        }
-      }
-    }
-  }
-}
-
 // Modes >= 2 with the matrix panel in LDS (interior single-term jobs,
 // 192 <= n <= 256, n % 64 == 0, 4 x 4 tiles).  A workgroup of 8 waves shares
 // one 64-column panel of P (times the job's scale), stored in LDS in the
@@ -517,7 +439,7 @@ __global__ void __launch_bounds__(512, 1) modeB_lds_kernel(const ModeJobs J, int
   const int64_t lw = w - jb.tile_begin;
   const int it = (int)(lw % jb.tiles_i);
   const int64_t grp = lw / jb.tiles_i;
-  const int n = jb.n, ldp = jb.ldp;
+  const int n = jb.n;
   const int64_t na = jb.na;
   const int64_t npairs = (int64_t)jb.tiles_a * jb.nb;
   const int i0 = it * 64;
@@ -528,7 +450,9 @@ __global__ void __launch_bounds__(512, 1) modeB_lds_kernel(const ModeJobs J, int
     const double sc = jb.scale[0];
     for (int q = threadIdx.x; q < (n / 4) * 64; q += 512) {
       const int ln = q & 63, kk = q >> 6;
-      panel[q] = *(const d4*)(P + i0 + 4 * (ln & 15) + (int64_t)ldp * (4 * kk + (ln >> 4))) * sc;
+      const int i = i0 + 4 * (ln & 15), p = 4 * kk + (ln >> 4);
+      panel[q] = d4{packed_at(P, n, i, p), packed_at(P, n, i + 1, p), packed_at(P, n, i + 2, p),
+                    packed_at(P, n, i + 3, p)} * sc;
     }
   }
   __syncthreads();
@@ -605,31 +529,21 @@ __global__ void __launch_bounds__(512, 1) modeB_lds_kernel(const ModeJobs J, int
   }
 }
 
-// Two waves per SIMD, as for mode 1 (with it the 4 x 4 tile fits in 232
-// registers).
-template <int TM, int TN, int MODE>
-__global__ void __launch_bounds__(64, 2) modeB_f64_kernel(const ModeJobs J, int64_t per_xcd) {
-  const int64_t t = remap_xcd(blockIdx.x, per_xcd);
-  if (t >= J.total_tiles) return;
-  const int j = find_job(J, t);
-  modeB_tile<TM, TN, MODE>(J.job[j], t - J.job[j].tile_begin);
-}
-
-template <int TM, int TN, int MODE>
-__global__ void __launch_bounds__(64, 2) modeB_f64_list_kernel(const ModeJob* __restrict__ jobs,
-                                                            const int64_t* __restrict__ begins, int njobs,
-                                                            int64_t total, int64_t per_xcd) {
-  for (int64_t raw = blockIdx.x; raw < 8 * per_xcd; raw += gridDim.x) {
-    const int64_t t = remap_xcd(raw, per_xcd);
-    if (t >= total) continue;
-    const int j = find_job_list(begins, njobs, t);
-    modeB_tile<TM, TN, MODE>(jobs[j], t - jobs[j].tile_begin);
-  }
-}
-
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
+int64_t assign_tiles_f64(ModeJob* jobs, int njobs, bool mode1, int ti, int to) {
+  int64_t tot = 0;
+  for (int j = 0; j < njobs; ++j) {
+    ModeJob& jb = jobs[j];
+    jb.tiles_i = (int)ceil_div(jb.n, 16 * ti);
+    jb.tiles_a = 0;   // not used
+    jb.tile_begin = tot;
+    tot += jb.tiles_i * ceil_div(mode1 ? jb.nb : jb.na * jb.nb, 16 * to);
+  }
+  return tot;
+}
+
 int64_t assign_tiles(ModeJob* jobs, int njobs, bool mode1, int TM, int TN) {
   int64_t tot = 0;
   for (int j = 0; j < njobs; ++j) {
@@ -648,62 +562,128 @@ int64_t assign_tiles(ModeJob* jobs, int njobs, bool mode1, int TM, int TN) {
 }
 
 namespace {
+
 bool aligned(const void* p, uintptr_t a) { return ((uintptr_t)p % a) == 0; }
-bool no_interior() {
-  static const bool off = std::getenv("SETD_NO_INTERIOR_PATH") != nullptr;
-  return off;
-}
-}  // namespace
 
-int job_mode(const ModeJob& jb, bool mode1, int TM, int TN) {
-  bool vec, interior;
-  if (mode1) {
-    vec = (jb.n % 4 == 0) && aligned(jb.X[0], 32) && aligned(jb.Y, 16) && aligned(jb.base, 16);
-    interior = jb.n % 32 == 0 && jb.nb % (16 * TN) == 0;
-  } else {
-    vec = (jb.na % 4 == 0) && aligned(jb.Y, 16) && aligned(jb.base, 16);
-    for (int t = 0; t < jb.nterms; ++t) vec = vec && aligned(jb.X[t], 32);
-    interior = jb.n % 32 == 0 && jb.na % (16 * TM) == 0;
-  }
-  if (!vec) return 0;
-  return (interior && !no_interior()) ? 2 : 1;
-}
-
-namespace {
-
+// Tile of one launch: ti x to blocks of 16 (i x the other index) per wave, ks
+// waves per tile.  rate: share of the matrix rate that the products of its
+// waves reach (1 x 1 tiles wait for their operands); block: cycles per block
+// that loading and storing it adds to a wave (fitted to sweeps of all tiles
+// at 64^2 .. 600^2 and 64^3 .. 256^3).
 struct TileCfg {
-  int tm, tn;
+  int ti, to, ks;
+  double rate, block;
 };
+constexpr TileCfg kTiles[] = {{1, 1, 4, .50, 550}, {2, 2, 4, .92, 550}, {2, 2, 2, .86, 600}, {2, 2, 1, .80, 700},
+                              {4, 2, 4, .92, 550}, {4, 2, 2, .92, 600}, {4, 2, 1, .90, 700}, {5, 2, 4, .92, 550},
+                              {5, 2, 1, .92, 700}, {7, 1, 4, .92, 550}, {7, 2, 1, .92, 700}, {4, 4, 1, .94, 700}};
 
 TileCfg env_tile(const char* name, TileCfg def) {
   const char* s = std::getenv(name);
   if (!s) return def;
-  int a = 0, b = 0;
-  if (std::sscanf(s, "%dx%d", &a, &b) == 2 && (a == 2 || a == 4) && (b == 2 || b == 4)) return {a, b};
+  int a = 0, b = 0, c = 1;
+  if (std::sscanf(s, "%dx%dx%d", &a, &b, &c) >= 2)
+    for (const TileCfg& t : kTiles)
+      if (t.ti == a && t.to == b && t.ks == c) return t;
   return def;
 }
 
-int finish_tiles(ModeJobs& J, bool mode1, int TM, int TN) {
-  J.total_tiles = assign_tiles(J.job, J.njobs, mode1, TM, TN);
+int64_t tile_count(const ModeJobs& J, bool mode1, const TileCfg& t) {
+  int64_t w = 0;
+  for (int j = 0; j < J.njobs; ++j) {
+    const ModeJob& jb = J.job[j];
+    w += ceil_div(jb.n, 16 * t.ti) * ceil_div(mode1 ? jb.nb : jb.na * jb.nb, 16 * t.to);
+  }
+  return w;
+}
+
+// The tile whose launch should take least time: rounds of 1024 SIMDs (a
+// partial one counts whole while there are few), each as long as one wave, 64
+// cycles per MFMA.  Measured against each other at the two ends: 300^2, 4
+// jobs of mode 1: 2 x 2 tiles with 4 waves each 9.2 us, 4 x 4 41.9; 256^3, 6
+// jobs of 3 terms: 4 x 4 2.32 ms, 4 x 2 2.46, 2 x 2 with 4 waves 3.4.
+TileCfg choose_tile(const ModeJobs& J, bool mode1) {
+  TileCfg best = kTiles[0];
+  double bt = 1e300;
+  for (const TileCfg& t : kTiles) {
+    const double w = (double)tile_count(J, mode1, t) * t.ks / 1024.0;
+    double wave = 0.0;
+    for (int j = 0; j < J.njobs; ++j) {
+      const ModeJob& jb = J.job[j];
+      const double chunks = (double)jb.nterms * ceil_div(jb.n, 8) / t.ks;
+      wave = std::max(wave, t.ti * t.to * (chunks * 128.0 / t.rate + t.block * (jb.base ? 1.6 : 1.0)));
+    }
+    const double time = ((w < 6.0 ? std::ceil(w) : w) + 0.3) * wave;
+    if (time < bt) {
+      bt = time;
+      best = t;
+    }
+  }
+  return best;
+}
+
+int finish_tiles(ModeJobs& J, bool mode1, const TileCfg& t) {
+  J.total_tiles = assign_tiles_f64(J.job, J.njobs, mode1, t.ti, t.to);
   J.tiles_per_job = J.njobs > 0 ? J.total_tiles / J.njobs : 0;
   for (int j = 0; j < J.njobs; ++j)
     if (J.job[j].tile_begin != (int64_t)j * J.tiles_per_job) J.tiles_per_job = 0;
   return SETD_OK;
 }
 
-}  // namespace
+template <bool M1, int TI, int TO, int KS, typename Off>
+int launch_tile(const ModeJobs& J, hipStream_t s) {
+  const int64_t per = ceil_div(ceil_div(J.total_tiles, 4 / KS), 8);
+  hipLaunchKernelGGL((mode_f64_kernel<M1, TI, TO, KS, Off>), dim3((unsigned)(per * 8)), dim3(256), 0, s, J, per);
+  SETD_LAUNCHED();
+  return SETD_OK;
+}
 
-#define SETD_LAUNCH_MODES(KERNEL, TM_, TN_)                                                    \
-  if (cfg.tm == TM_ && cfg.tn == TN_) {                                                       \
-    if (mode == 2)                                                                            \
-      hipLaunchKernelGGL((KERNEL<TM_, TN_, 2>), grid, dim3(64), 0, s, J, per);                 \
-    else if (mode == 1)                                                                       \
-      hipLaunchKernelGGL((KERNEL<TM_, TN_, 1>), grid, dim3(64), 0, s, J, per);                 \
-    else                                                                                      \
-      hipLaunchKernelGGL((KERNEL<TM_, TN_, 0>), grid, dim3(64), 0, s, J, per);                 \
-    SETD_LAUNCHED();                                                                          \
-    return SETD_OK;                                                                           \
+template <bool M1>
+int launch_cfg(const ModeJobs& J, const TileCfg& t, hipStream_t s) {
+#define SETD_TILE(TI_, TO_, KS_) \
+  if (t.ti == TI_ && t.to == TO_ && t.ks == KS_) return launch_tile<M1, TI_, TO_, KS_, uint32_t>(J, s);
+  SETD_TILE(1, 1, 4)
+  SETD_TILE(2, 2, 4)
+  SETD_TILE(2, 2, 2)
+  SETD_TILE(2, 2, 1)
+  SETD_TILE(4, 2, 4)
+  SETD_TILE(4, 2, 2)
+  SETD_TILE(4, 2, 1)
+  SETD_TILE(5, 2, 4)
+  SETD_TILE(5, 2, 1)
+  SETD_TILE(7, 1, 4)
+  SETD_TILE(7, 2, 1)
+  SETD_TILE(4, 4, 1)
+#undef SETD_TILE
+  set_error("unsupported tile %dx%d", t.ti, t.to);
+  return SETD_EUNSUPPORTED;
+}
+
+// The panel kernels' job records: workgroups instead of tiles.
+void finish_panels(ModeJobs& J, bool mode1) {
+  int64_t tot = 0;
+  for (int j = 0; j < J.njobs; ++j) {
+    ModeJob& jb = J.job[j];
+    jb.tiles_i = (int)ceil_div(jb.n, 64);
+    jb.tiles_a = (int)((mode1 ? jb.nb : jb.na) / 64);
+    jb.tile_begin = tot;
+    tot += (int64_t)jb.tiles_i * ceil_div((int64_t)jb.tiles_a * (mode1 ? 1 : jb.nb), (int64_t)kLdsWaves * kLdsReps);
   }
+  J.total_tiles = tot;
+  J.tiles_per_job = J.njobs > 0 ? tot / J.njobs : 0;
+  for (int j = 0; j < J.njobs; ++j)
+    if (J.job[j].tile_begin != (int64_t)j * J.tiles_per_job) J.tiles_per_job = 0;
+}
+
+// Whether the LDS panel kernels take a job: one term, 192 <= n <= 256, whole
+// panels and tiles, aligned vector accesses.
+bool panel_job(const ModeJob& jb, bool mode1) {
+  if (jb.nterms != 1 || jb.n < kLdsMinN || jb.n > kLdsMaxN) return false;
+  if (!aligned(jb.X[0], 32) || !aligned(jb.Y, 16) || !aligned(jb.base, 16)) return false;
+  return mode1 ? jb.n % 32 == 0 && jb.nb % 64 == 0 : jb.n % 64 == 0 && jb.na % 64 == 0;
+}
+
+}  // namespace
 
 void job_work(const ModeJobs& J, int es_in, int es_out, int es_mat, double& flops, double& bytes) {
   flops = 0.0;
@@ -717,141 +697,73 @@ void job_work(const ModeJobs& J, int es_in, int es_out, int es_mat, double& flop
 }
 
 int launch_mode1_f64(ModeJobs& J, hipStream_t s) {
-  // default from a sweep on MI355X at FHN 256^3 (two waves per SIMD):
-  // 4 x 4 53.7, 2 x 4 43.7, 4 x 2 42.2, 2 x 2 34.3 TFLOP/s.  Only the
-  // interior variant of the 4 x 4 tile fits the two-wave register budget
-  // (its 2-p ring); jobs that need the checked variants take 4 x 2 tiles,
-  // which do not spill.
-  auto min_mode = [&](int tm, int tn) {
-    int m = 2;
-    for (int j = 0; j < J.njobs; ++j) m = std::min(m, job_mode(J.job[j], true, tm, tn));
-    return m;
-  };
-  TileCfg def{4, 4};
-  if (min_mode(4, 4) < 2) def = TileCfg{4, 2};
-  const TileCfg cfg = env_tile("SETD_TILE_MODE1", def);
-  finish_tiles(J, true, cfg.tm, cfg.tn);
-  if (J.total_tiles == 0) return SETD_OK;
   double fl = 0.0, by = 0.0;
   if (prof_on()) job_work(J, 8, 8, 8, fl, by);
+  bool lds = J.njobs > 0;
+  for (int j = 0; j < J.njobs; ++j) lds = lds && panel_job(J.job[j], true);
+  const TileCfg cfg = env_tile("SETD_TILE_MODE1", choose_tile(J, true));
+  if (lds) finish_panels(J, true);
+  else finish_tiles(J, true, cfg);
+  if (J.total_tiles == 0) return SETD_OK;
   ProfScope prof(s, kProfMode1F64, fl, by);
-  const int mode = min_mode(cfg.tm, cfg.tn);
-  bool lds = mode == 2 && cfg.tm == 4 && cfg.tn == 4;
-  for (int j = 0; j < J.njobs; ++j)
-    lds = lds && J.job[j].n >= kLdsMinN && J.job[j].n <= kLdsMaxN && J.job[j].n % 32 == 0;
-  if (lds) {
-    // workgroups instead of tiles: per job tiles_i panels x column groups of
-    // 8 * reps tiles
-    const int reps = kLdsReps;
-    int64_t tot = 0;
-    for (int j = 0; j < J.njobs; ++j) {
-      ModeJob& jb = J.job[j];
-      jb.tile_begin = tot;
-      tot += (int64_t)jb.tiles_i * ceil_div(jb.tiles_a, kLdsWaves * reps);
-    }
-    J.total_tiles = tot;
-    J.tiles_per_job = J.njobs > 0 ? tot / J.njobs : 0;
-    for (int j = 0; j < J.njobs; ++j)
-      if (J.job[j].tile_begin != (int64_t)j * J.tiles_per_job) J.tiles_per_job = 0;
-    const int64_t per = ceil_div(tot, 8);
-    hipLaunchKernelGGL(mode1_lds_kernel, dim3((unsigned)(per * 8)), dim3(64 * kLdsWaves), 0, s, J, per, reps);
-    SETD_LAUNCHED();
-    return SETD_OK;
-  }
+  if (!lds) return launch_cfg<true>(J, cfg, s);
   const int64_t per = ceil_div(J.total_tiles, 8);
-  const dim3 grid((unsigned)(per * 8));
-  SETD_LAUNCH_MODES(mode1_f64_kernel, 4, 4)
-  SETD_LAUNCH_MODES(mode1_f64_kernel, 4, 2)
-  SETD_LAUNCH_MODES(mode1_f64_kernel, 2, 4)
-  SETD_LAUNCH_MODES(mode1_f64_kernel, 2, 2)
-  set_error("unsupported mode-1 tile");
-  return SETD_EUNSUPPORTED;
+  hipLaunchKernelGGL(mode1_lds_kernel, dim3((unsigned)(per * 8)), dim3(64 * kLdsWaves), 0, s, J, per, kLdsReps);
+  SETD_LAUNCHED();
+  return SETD_OK;
 }
 
 int launch_modeB_f64(ModeJobs& J, hipStream_t s) {
-  // default tiles from sweeps on MI355X: 4 x 4 when every contraction is
-  // long (n >= 192; FHN 256^3 last mode 68.4 against 64.2 TFLOP/s for 4 x 2),
-  // 4 x 2 otherwise (FHN 128^3: 48.0 against 45.1; fewer, shorter tiles)
-  bool long_k = true;
-  for (int j = 0; j < J.njobs; ++j) long_k = long_k && J.job[j].n >= kLdsMinN;
-  const TileCfg cfg = env_tile("SETD_TILE_MODEB", long_k ? TileCfg{4, 4} : TileCfg{4, 2});
-  finish_tiles(J, false, cfg.tm, cfg.tn);
-  if (J.total_tiles == 0) return SETD_OK;
   double fl = 0.0, by = 0.0;
   if (prof_on()) job_work(J, 8, 8, 8, fl, by);
-  int mode = 2;
-  for (int j = 0; j < J.njobs; ++j) mode = std::min(mode, job_mode(J.job[j], false, cfg.tm, cfg.tn));
-  bool lds = mode == 2 && cfg.tm == 4;
+  bool lds = J.njobs > 0, big = false;
   for (int j = 0; j < J.njobs; ++j) {
+    lds = lds && panel_job(J.job[j], false);
+    // a tile's offsets span more than 32 bits: 8 rows of X, or (with several
+    // slabs) the slabs of one tile's columns
     const ModeJob& jb = J.job[j];
-    lds = lds && jb.nterms == 1 && jb.n >= kLdsMinN && jb.n <= kLdsMaxN && jb.n % 64 == 0 && jb.na % 64 == 0;
+    big = big || jb.na > (int64_t(1) << 26) ||
+          (jb.nb > 1 && (ceil_div(128, jb.na) + 1) * jb.na * jb.n > (int64_t(1) << 28));
   }
+  const TileCfg cfg = big ? TileCfg{4, 2, 1, 0.0, 0.0} : env_tile("SETD_TILE_MODEB", choose_tile(J, false));
+  if (lds) finish_panels(J, false);
+  else finish_tiles(J, false, cfg);
+  if (J.total_tiles == 0) return SETD_OK;
   // the two kernels are timed as separate classes
   ProfScope prof(s, lds ? kProfModeBPanelF64 : kProfModeBF64, fl, by);
-  if (lds) {
-    // workgroups: per job n / 64 panels x groups of 8 * reps (a-block, slab)
-    // pairs; 4 tiles per wave as in mode 1 (measured at FHN 256^3: the
-    // single-term launches go from 62.6 to 65.3 TFLOP/s)
-    const int reps = kLdsReps;
-    int64_t tot = 0;
-    for (int j = 0; j < J.njobs; ++j) {
-      ModeJob& jb = J.job[j];
-      jb.tiles_i = jb.n / 64;
-      jb.tiles_a = (int)(jb.na / 64);
-      jb.tile_begin = tot;
-      tot += (int64_t)jb.tiles_i * ceil_div((int64_t)jb.tiles_a * jb.nb, (int64_t)kLdsWaves * reps);
-    }
-    J.total_tiles = tot;
-    J.tiles_per_job = J.njobs > 0 ? tot / J.njobs : 0;
-    for (int j = 0; j < J.njobs; ++j)
-      if (J.job[j].tile_begin != (int64_t)j * J.tiles_per_job) J.tiles_per_job = 0;
-    const int64_t per = ceil_div(tot, 8);
-    hipLaunchKernelGGL(modeB_lds_kernel, dim3((unsigned)(per * 8)), dim3(64 * kLdsWaves), 0, s, J, per, reps);
-    SETD_LAUNCHED();
-    return SETD_OK;
-  }
+  if (big && !lds) return launch_tile<false, 4, 2, 1, uint64_t>(J, s);
+  if (!lds) return launch_cfg<false>(J, cfg, s);
   const int64_t per = ceil_div(J.total_tiles, 8);
-  const dim3 grid((unsigned)(per * 8));
-  SETD_LAUNCH_MODES(modeB_f64_kernel, 4, 4)
-  SETD_LAUNCH_MODES(modeB_f64_kernel, 4, 2)
-  SETD_LAUNCH_MODES(modeB_f64_kernel, 2, 4)
-  SETD_LAUNCH_MODES(modeB_f64_kernel, 2, 2)
-  set_error("unsupported mode-b tile");
-  return SETD_EUNSUPPORTED;
+  hipLaunchKernelGGL(modeB_lds_kernel, dim3((unsigned)(per * 8)), dim3(64 * kLdsWaves), 0, s, J, per, kLdsReps);
+  SETD_LAUNCHED();
+  return SETD_OK;
 }
 
-#define SETD_LAUNCH_LIST(KERNEL, TM_, TN_)                                                     \
+#define SETD_LAUNCH_LIST(TM_, TN_)                                                             \
   if (L.tm == TM_ && L.tn == TN_) {                                                           \
-    if (L.mode == 2)                                                                          \
-      hipLaunchKernelGGL((KERNEL<TM_, TN_, 2>), grid, dim3(64), 0, s, L.jobs, L.begins, L.njobs, L.total, per); \
-    else if (L.mode == 1)                                                                     \
-      hipLaunchKernelGGL((KERNEL<TM_, TN_, 1>), grid, dim3(64), 0, s, L.jobs, L.begins, L.njobs, L.total, per); \
+    if (L.mode1)                                                                              \
+      hipLaunchKernelGGL((mode_f64_list_kernel<true, TM_, TN_>), grid, dim3(256), 0, s, L.jobs, L.begins, L.njobs, \
+                         L.total, groups);                                                    \
     else                                                                                      \
-      hipLaunchKernelGGL((KERNEL<TM_, TN_, 0>), grid, dim3(64), 0, s, L.jobs, L.begins, L.njobs, L.total, per); \
+      hipLaunchKernelGGL((mode_f64_list_kernel<false, TN_, TM_>), grid, dim3(256), 0, s, L.jobs, L.begins, L.njobs, \
+                         L.total, groups);                                                    \
     SETD_LAUNCHED();                                                                          \
     return SETD_OK;                                                                           \
   }
 
 int launch_list_f64(const ModeList& L, hipStream_t s) {
   if (L.total == 0) return SETD_OK;
-  const int64_t per = ceil_div(L.total, 8);
+  const int64_t groups = round_up(ceil_div(L.total, 4), 8 * kListRun);
   // a multiple of 8 blocks, so that block b stays on XCD b % 8 through the
-  // whole loop; at most `grid_cap` blocks (0: one block per tile)
-  int64_t nblk = per * 8;
-  if (L.grid_cap > 0 && nblk > L.grid_cap) nblk = round_up(L.grid_cap, 8);
+  // whole loop; at most `grid_cap` waves (0: one wave per tile)
+  int64_t nblk = groups;
+  if (L.grid_cap > 0 && nblk * 4 > L.grid_cap) nblk = round_up(ceil_div(L.grid_cap, 4), 8);
   const dim3 grid((unsigned)nblk);
   ProfScope prof(s, L.mode1 ? kProfMode1F64 : kProfModeBF64, L.flops, L.bytes);
-  if (L.mode1) {
-    SETD_LAUNCH_LIST(mode1_f64_list_kernel, 4, 4)
-    SETD_LAUNCH_LIST(mode1_f64_list_kernel, 4, 2)
-    SETD_LAUNCH_LIST(mode1_f64_list_kernel, 2, 4)
-    SETD_LAUNCH_LIST(mode1_f64_list_kernel, 2, 2)
-  } else {
-    SETD_LAUNCH_LIST(modeB_f64_list_kernel, 4, 4)
-    SETD_LAUNCH_LIST(modeB_f64_list_kernel, 4, 2)
-    SETD_LAUNCH_LIST(modeB_f64_list_kernel, 2, 4)
-    SETD_LAUNCH_LIST(modeB_f64_list_kernel, 2, 2)
-  }
+  SETD_LAUNCH_LIST(2, 2)
+  SETD_LAUNCH_LIST(2, 4)
+  SETD_LAUNCH_LIST(4, 2)
+  SETD_LAUNCH_LIST(4, 4)
   set_error("unsupported tile %dx%d", L.tm, L.tn);
   return SETD_EUNSUPPORTED;
 }

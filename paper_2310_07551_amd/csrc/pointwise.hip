@@ -19,6 +19,19 @@ namespace setd {
 // ---------------------------------------------------------------------------
 // packing
 // ---------------------------------------------------------------------------
+// FP64: entry (tile t, chunk c, lane, j) = scale * M[16 t + lane % 16][8 c + 2 (lane / 16) + j],
+// M[i][p] at i + n p (trans: at p + n i).  One thread per entry.
+__global__ void pack_f64_kernel(const double* __restrict__ M, int n, double scale, bool trans,
+                                double* __restrict__ out, int64_t tot) {
+  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (idx >= tot) return;
+  const int nch = (n + 7) >> 3;
+  const int e = (int)(idx & 127), lane = e >> 1;
+  const int64_t tc = idx >> 7;
+  const int i = 16 * (int)(tc / nch) + (lane & 15), p = 8 * (int)(tc % nch) + 2 * (lane >> 4) + (e & 1);
+  out[idx] = (i < n && p < n) ? scale * M[trans ? p + (int64_t)n * i : i + (int64_t)n * p] : 0.0;
+}
+
 template <typename T>
 __global__ void pack_kernel(const double* __restrict__ M, int n, int ldp, double scale, bool rowmajor,
                             T* __restrict__ out) {
@@ -67,11 +80,10 @@ size_t packed_bytes(int n, int prec) {
   return e * 4;                                 // two bf16 planes
 }
 
-int pack_matrix_f64(const double* M, int n, double scale, bool rowmajor, double* out, hipStream_t s) {
-  const int ldp = packed_ld(n);
-  const int64_t tot = (int64_t)ldp * ldp;
-  hipLaunchKernelGGL(pack_kernel<double>, dim3((unsigned)ceil_div(tot, 256)), dim3(256), 0, s, M, n, ldp, scale,
-                     rowmajor, out);
+int pack_matrix_f64(const double* M, int n, double scale, bool trans, double* out, hipStream_t s) {
+  const int64_t tot = ceil_div(n, 16) * ceil_div(n, 8) * 128;
+  hipLaunchKernelGGL(pack_f64_kernel, dim3((unsigned)ceil_div(tot, 256)), dim3(256), 0, s, M, n, scale, trans, out,
+                     tot);
   SETD_LAUNCHED();
   return SETD_OK;
 }

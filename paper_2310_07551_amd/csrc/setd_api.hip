@@ -133,12 +133,13 @@ int push(ModeJobs& J, const ModeJob& jb, const LaunchKind& k, hipStream_t s) {
   return SETD_OK;
 }
 
-// Packs a matrix for the mode kernels of the given arithmetic: mode 1 reads
-// it row-major; modes >= 2 column-major (FP64, FP32) or row-major (bf16).
+// Packs a matrix for the mode kernels of the given arithmetic: FP64 in one
+// operand order for every mode; FP32 row-major for mode 1 and column-major for
+// modes >= 2; bf16 row-major.
 }  // namespace
 
 int setd::pack_for(int prec, const double* M, int n, double scale, int mu, void* out, hipStream_t s) {
-  if (prec == SETD_PREC_F64) return pack_matrix_f64(M, n, scale, mu == 0, (double*)out, s);
+  if (prec == SETD_PREC_F64) return pack_matrix_f64(M, n, scale, false, (double*)out, s);
   if (prec == SETD_PREC_F32) return pack_matrix_f32(M, n, scale, mu == 0, (float*)out, s);
   if (prec == SETD_PREC_I8X4) return pack_matrix_i8(M, n, scale, out, s);
   return pack_matrix_bf16(M, n, scale, true, prec == SETD_PREC_BF16X3 ? 3 : 2, out, s);
@@ -289,7 +290,9 @@ int setd::run_tucker_group(int d, const int* dims, TuckerOut* outs, int nouts, i
     for (int t = 0; t < outs[o].nterms; ++t, ++chain) {
       const TuckerTerm& tm = outs[o].term[t];
       void* y = fuse ? chain_slot(chain) : tm.Y1;
-      SETD_TRY(push(J, mk_job(tm.X, tm.P[0], 1.0, y, nullptr, 1, dims[0], N / dims[0]), k1, s));
+      // FP64: the term's factor goes on this product's results
+      const double sc = prec == SETD_PREC_F64 ? tm.scale : 1.0;
+      SETD_TRY(push(J, mk_job(tm.X, tm.P[0], sc, y, nullptr, 1, dims[0], N / dims[0]), k1, s));
     }
   SETD_TRY(flush(J, k1, s));
   // inner modes, ping-pong Y1 <-> Y2
@@ -320,7 +323,7 @@ int setd::run_tucker_group(int d, const int* dims, TuckerOut* outs, int nouts, i
       const TuckerTerm& tm = outs[o].term[t];
       jb.X[t] = klast.presliced ? chain_slot(chain) : (mu % 2 == 1) ? tm.Y1 : tm.Y2;
       jb.P[t] = tm.P[mu];
-      jb.scale[t] = tm.scale;
+      jb.scale[t] = prec == SETD_PREC_F64 ? 1.0 : tm.scale;
     }
     jb.Y = outs[o].Y;
     jb.base = outs[o].base;
@@ -430,7 +433,7 @@ int build_bank(setd_ctx* c, hipStream_t s) {
         const int li = c->sp[kBankEll[e]].ell_i[t];
         SETD_TRY(pack_for(c->prec, src + ((size_t)k * 3 + li) * nn, n, 1.0, mu, c->bank[cc][e][t][mu], s));
       }
-      SETD_TRY(pack_matrix_f64(Adev(cc, mu), n, 1.0, mu == 0, (double*)c->Apk[cc][mu], s));
+      SETD_TRY(pack_matrix_f64(Adev(cc, mu), n, 1.0, false, (double*)c->Apk[cc][mu], s));
     }
     SETD_HIP(hipStreamSynchronize(s));   // raw buffers are released at scope exit
   }
