@@ -140,11 +140,36 @@ struct ProfScope {
 };
 
 
+// The mode-1 and mode-2 products of Tucker operators in one pass over slabs of
+// n1 x n2 (slab_f64_kernel): Y_b = base_b + sum_t scale_t P1_t X_t,b P2_t^T for
+// b < nb.  Every job of a launch has the same n1 <= kSlabMaxN1, n2 and nb.
+// Jobs of two terms (the Tucker sums of a small 2D grid) have n1 <= kSlabSumN.
+// raw: the matrices are column-major n x n instead of packed (one term).
+constexpr int kSlabMaxN1 = 256, kSlabSumN = 64;
+struct SlabJob {
+  const void* X[kMaxTerms];
+  const void* P1[kMaxTerms];
+  const void* P2[kMaxTerms];
+  double scale[kMaxTerms];
+  void* Y;
+  const void* base;   // nullable
+  int64_t nb;
+  int n1, n2, nterms;
+};
+struct SlabJobs {
+  SlabJob job[kMaxJobs];
+  int njobs;
+  int nblk;               // column blocks per slab
+  int64_t tiles_per_job, total;
+};
+int launch_slab_f64(SlabJobs& jobs, hipStream_t s, bool raw = false);
+
 // Mode-product launchers (implemented in mode_f64.hip / mode_lp.hip).
 // `jobs` is filled by the caller except for the tile fields, which the
 // launcher computes.  All jobs of one launch share regime (mode 1 or not).
-int launch_mode1_f64(ModeJobs& jobs, hipStream_t s);
-int launch_modeB_f64(ModeJobs& jobs, hipStream_t s);
+// raw: the jobs' matrices are column-major n x n instead of packed.
+int launch_mode1_f64(ModeJobs& jobs, hipStream_t s, bool raw = false);
+int launch_modeB_f64(ModeJobs& jobs, hipStream_t s, bool raw = false);
 // Reduced precision (mode_lp.hip): FP32 tensor inputs, output FP32 or FP64
 // (FP64 output adds the optional FP64 base).
 int launch_mode1_lp(ModeJobs& jobs, int prec, DType out, hipStream_t s);

@@ -68,22 +68,67 @@ __device__ __forceinline__ double packed_at(const double* P, int n, int i, int p
   return P[((int64_t)(i >> 4) * chunks_of(n) + (p >> 3)) * 128 + ((((p >> 1) & 3) << 4) + (i & 15)) * 2 + (p & 1)];
 }
 
+// The matrix operand of TI tiles from tile t0: packed, or (RAW) read as it is
+// given, column-major n x n, for a matrix that is used once: 16 lanes read 128
+// contiguous bytes of a column.  Tiles and rows past the last are clamped.
+template <bool RAW, int TI>
+struct MatrixTiles {
+  const double* at[TI];   // packed: the lane's pair of the tile's first chunk
+  uint32_t off[TI];       // RAW: byte offset of the lane's entry in columns 0, 8, ..
+  const double* M;
+  int n, g;
+
+  __device__ __forceinline__ MatrixTiles(const void* P, int n_, int t0, int lane) : M((const double*)P), n(n_), g(lane >> 4) {
+    const int nt = (n + 15) >> 4, nch = chunks_of(n);
+#pragma unroll
+    for (int i = 0; i < TI; ++i) {
+      if constexpr (RAW) off[i] = (uint32_t)((min(16 * (t0 + i) + (lane & 15), n - 1) + (int64_t)n * (2 * g)) * 8);
+      else at[i] = M + (int64_t)min(t0 + i, nt - 1) * nch * 128 + 2 * lane;
+    }
+  }
+  // chunk c: entries of p = 8 c + 2 g + j; RAW: c < n / 8
+  __device__ __forceinline__ void load(int c, d2 (&p)[TI]) const {
+    if constexpr (RAW) {
+      const char* c0 = (const char*)(M + (int64_t)n * (8 * c));
+      const char* c1 = (const char*)(M + (int64_t)n * (8 * c + 1));
+#pragma unroll
+      for (int i = 0; i < TI; ++i) p[i] = d2{*(const double*)(c0 + off[i]), *(const double*)(c1 + off[i])};
+    } else {
+#pragma unroll
+      for (int i = 0; i < TI; ++i) p[i] = *(const d2*)(at[i] + (int64_t)c * 128);
+    }
+  }
+  // the last chunk, of n % 8: zero past n
+  __device__ __forceinline__ void load_tail(d2 (&p)[TI]) const {
+    if constexpr (RAW) {
+      const int c = n >> 3;
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int q = 8 * c + 2 * g + j;
+        const char* cq = (const char*)(M + (int64_t)n * (min(q, n - 1) - 2 * g));
+#pragma unroll
+        for (int i = 0; i < TI; ++i) p[i][j] = *(const double*)(cq + off[i]);
+#pragma unroll
+        for (int i = 0; i < TI; ++i) p[i][j] = q < n ? p[i][j] : 0.0;
+      }
+    } else {
+      load(n >> 3, p);
+    }
+  }
+};
+
 // Adds sum_p S[i, p] X[.., p, ..] of one term to the accumulators, for p of
 // the chunks lo .. hi - 1.  x0 is the tile's first element, xo[o] the byte
 // offset of the lane's first element of column (row) block o from it; M1:
 // consecutive p are adjacent, else `na` elements apart.
-template <bool M1, int TI, int TO, int D, typename Off>
+template <bool M1, bool RAW, int TI, int TO, int D, typename Off>
 __device__ __forceinline__ void add_term(d4 (&acc)[TI][TO], const double* __restrict__ x0, const Off (&xo)[TO],
-                                         int64_t na, const double* __restrict__ P, int t0, int nt, int n, int lane,
-                                         int lo, int hi) {
+                                         int64_t na, const MatrixTiles<RAW, TI>& mat, int n, int lane, int lo,
+                                         int hi) {
   const int g = lane >> 4;
-  const int nch = chunks_of(n), nfull = n >> 3;
-  const double* pt[TI];
-#pragma unroll
-  for (int i = 0; i < TI; ++i) pt[i] = P + (int64_t)min(t0 + i, nt - 1) * nch * 128;
+  const int nfull = n >> 3;
   auto load = [&](int c, d2 (&xr)[TO], d2 (&pr)[TI]) {
-#pragma unroll
-    for (int i = 0; i < TI; ++i) pr[i] = *(const d2*)(pt[i] + (int64_t)c * 128 + 2 * lane);
+    mat.load(c, pr);
     if constexpr (M1) {
       const char* xb = (const char*)(x0 + 8 * c);
 #pragma unroll
@@ -111,8 +156,7 @@ __device__ __forceinline__ void add_term(d4 (&acc)[TI][TO], const double* __rest
   d2 xr[D][TO], pr[D][TI];
   if (tail) {
     // the last n % 8 values of p: clamped loads, zero past n
-#pragma unroll
-    for (int i = 0; i < TI; ++i) pr[D - 1][i] = *(const d2*)(pt[i] + (int64_t)nfull * 128 + 2 * lane);
+    mat.load_tail(pr[D - 1]);
     const int64_t ps = M1 ? 1 : na;
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
@@ -146,10 +190,10 @@ __device__ __forceinline__ void add_term(d4 (&acc)[TI][TO], const double* __rest
 
 // One wave computes tile `lt` of job `jb` (part kw of ks of its contraction;
 // `red` is the LDS the waves of one tile add up in when ks > 1).
-template <bool M1, int TI, int TO, int D, int KS, typename Off>
+template <bool M1, bool RAW, int TI, int TO, int D, int KS, typename Off>
 __device__ __forceinline__ void mode_tile(const ModeJob& jb, uint32_t lt, int lane, int kw, d4* red) {
   const int g = lane >> 4, l = lane & 15;
-  const int n = jb.n, nt = (n + 15) >> 4;
+  const int n = jb.n;
   const uint32_t ti = (uint32_t)jb.tiles_i;
   const uint32_t ot = lt / ti;
   const int t0 = (int)(lt - ot * ti) * TI;
@@ -194,8 +238,8 @@ __device__ __forceinline__ void mode_tile(const ModeJob& jb, uint32_t lt, int la
     }
     const int lo = max(first - term * nch, 0), hi = min(last - term * nch, nch);
     if (lo < hi)
-      add_term<M1, TI, TO, D, Off>(acc, (const double*)jb.X[term] + origin_x, xo, na, (const double*)jb.P[term], t0,
-                                   nt, n, lane, lo, hi);
+      add_term<M1, RAW, TI, TO, D, Off>(acc, (const double*)jb.X[term] + origin_x, xo, na,
+                                        MatrixTiles<RAW, TI>(jb.P[term], n, t0, lane), n, lane, lo, hi);
   }
   const double sc = jb.scale[nterms - 1];
   __builtin_amdgcn_s_setprio(0);
@@ -276,7 +320,7 @@ constexpr int red_size(int ti, int to, int ks) { return ks > 1 ? 4 * ti * to * 6
 // register budget the accumulators stay in place through the k loop (a
 // tighter default made the compiler copy all of them between register files
 // every iteration).
-template <bool M1, int TI, int TO, int KS, typename Off>
+template <bool M1, bool RAW, int TI, int TO, int KS, typename Off>
 __global__ void __launch_bounds__(256, 2) mode_f64_kernel(const ModeJobs J, int64_t per_xcd) {
   __shared__ d4 red[red_size(TI, TO, KS)];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -286,8 +330,8 @@ __global__ void __launch_bounds__(256, 2) mode_f64_kernel(const ModeJobs J, int6
     return;
   }
   const ModeJob& jb = J.job[find_job(J, t)];
-  mode_tile<M1, TI, TO, ring_depth(TI, TO), KS, Off>(jb, t - (uint32_t)jb.tile_begin, lane, wave % KS,
-                                                     red + (wave / KS) * KS * TI * TO * 64);
+  mode_tile<M1, RAW, TI, TO, ring_depth(TI, TO), KS, Off>(jb, t - (uint32_t)jb.tile_begin, lane, wave % KS,
+                                                          red + (wave / KS) * KS * TI * TO * 64);
 }
 
 // Work list in device memory (any number of jobs, e.g. many independent
@@ -305,7 +349,194 @@ __global__ void __launch_bounds__(256, 2) mode_f64_list_kernel(const ModeJob* __
     const int64_t t = (run * 8 * kListRun + (in & 7) * kListRun + (in >> 3)) * 4 + wave;
     if (t >= total) continue;
     const int j = find_job_list(begins, njobs, t);
-    mode_tile<M1, TI, TO, ring_depth(TI, TO), 1, uint32_t>(jobs[j], (uint32_t)(t - begins[j]), lane, 0, nullptr);
+    mode_tile<M1, false, TI, TO, ring_depth(TI, TO), 1, uint32_t>(jobs[j], (uint32_t)(t - begins[j]), lane, 0, nullptr);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// modes 1 and 2 in one pass
+// ---------------------------------------------------------------------------
+// Y_b = base_b + sum_t s_t P1_t X_t,b P2_t^T for every slab b (n1 x n2, i_1
+// fastest): the mode-1 and the mode-2 product of a Tucker operator without
+// the intermediate tensor.  A workgroup of 4 waves owns one slab and up to
+// 16 TJ columns j of its result.  Phase 1 forms Z = X_b P2^T for those
+// columns (a modes >= 2 product over the whole mode-2 fibres), each wave the
+// blocks of 16 i_1 w, w + 4, ..; Z goes to LDS (with the term's scale), where
+// phase 2 reads it as the tensor operand of the mode-1 product.  Both
+// contractions run over all of Z, so nothing is computed twice; X_b is
+// re-read once per column block, from L2.
+// Bound by the matrix cores once two or more workgroups share a CU (128^3:
+// busy 79%).  It saves
+// the traffic of the intermediate, which is what the two products were bound
+// by for n < 200 (n / 8 flops per byte), and one launch.
+// Waves whose share of i_1 blocks or columns is one smaller run their own
+// instance of the body (NI - 1, TJ - 1), and the smaller share moves round
+// the SIMDs from one workgroup to the next.
+constexpr int slab_ring(int tj, int ni) { return tj * ni >= 6 ? 2 : 3; }
+
+template <bool RAW, bool SUM, int TJ, int NI, int LD>
+__device__ __forceinline__ void slab_body(const SlabJob& jb, uint32_t b, int tj0, int w, int term, int lane,
+                                          double* Zall) {
+  const int g = lane >> 4, l = lane & 15;
+  const int n1 = jb.n1, n2 = jb.n2, nch1 = chunks_of(n1);
+  const int64_t slab = (int64_t)n1 * n2 * b;
+  double* Z = Zall + term * (16 * TJ * LD);
+  {
+    uint32_t xo[NI];
+#pragma unroll
+    for (int o = 0; o < NI; ++o) xo[o] = (uint32_t)((min(16 * (w + 4 * o) + l, n1 - 1) + n1 * (2 * g)) * 8);
+    d4 z[TJ][NI];
+#pragma unroll
+    for (int m = 0; m < TJ; ++m)
+#pragma unroll
+      for (int o = 0; o < NI; ++o) z[m][o] = d4{0.0, 0.0, 0.0, 0.0};
+    add_term<false, RAW, TJ, NI, slab_ring(TJ, NI), uint32_t>(
+        z, (const double*)jb.X[term] + slab, xo, n1, MatrixTiles<RAW, TJ>(jb.P2[term], n2, tj0, lane), n2, lane, 0,
+        chunks_of(n2));
+    const double sc = jb.scale[term];
+#pragma unroll
+    for (int m = 0; m < TJ; ++m)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int o = 0; o < NI; ++o) {
+          const int a = 16 * (w + 4 * o) + l;
+          Z[(16 * m + 4 * r + g) * LD + a] = a < n1 ? z[m][o][r] * sc : 0.0;
+        }
+  }
+  // phase 2: the wave's tiles w, w + 4, .. of P1, one MatrixTiles each
+  const MatrixTiles<RAW, 1> mat0(jb.P1[term], n1, w, lane);
+  const uint32_t step = 4u * nch1 * 128 * 8;   // packed: bytes from one of them to the next
+  auto load = [&](int c, d2 (&p)[NI]) {
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      if constexpr (RAW) {
+        d2 q[1];
+        const MatrixTiles<true, 1> mi(jb.P1[term], n1, w + 4 * i, lane);
+        if (c < (n1 >> 3)) mi.load(c, q);
+        else mi.load_tail(q);
+        p[i] = q[0];
+      } else {
+        p[i] = *(const d2*)((const char*)(mat0.at[0] + (int64_t)c * 128) + (uint32_t)i * step);
+      }
+    }
+  };
+  d4 acc[NI][TJ];
+#pragma unroll
+  for (int i = 0; i < NI; ++i)
+#pragma unroll
+    for (int m = 0; m < TJ; ++m) acc[i][m] = d4{0.0, 0.0, 0.0, 0.0};
+  constexpr int D2 = 2;
+  d2 p[D2][NI];
+#pragma unroll
+  for (int d = 0; d < D2; ++d) load(min(d, nch1 - 1), p[d]);   // in flight over the barrier
+  __syncthreads();
+  const double* zr = Z + l * LD + 2 * g;
+  auto mma = [&](int c, const d2 (&pr)[NI]) {
+    d2 zz[TJ];
+#pragma unroll
+    for (int m = 0; m < TJ; ++m) zz[m] = *(const d2*)(zr + 16 * m * LD + 8 * c);
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int m = 0; m < TJ; ++m) acc[i][m] = mfma(zz[m][j], pr[i][j], acc[i][m]);
+  };
+  int c = 0;
+  for (; c + D2 <= nch1; c += D2) {
+#pragma unroll
+    for (int d = 0; d < D2; ++d) {
+      mma(c + d, p[d]);
+      load(min(c + d + D2, nch1 - 1), p[d]);
+    }
+  }
+#pragma unroll
+  for (int d = 0; d < D2 - 1; ++d)
+    if (c + d < nch1) mma(c + d, p[d]);
+  if constexpr (SUM) {
+    // the waves of the first term add up the others', handed over in their Z
+    constexpr int share = (LD - 2) / 64 * TJ;   // accumulators of the wave with the most blocks
+    __syncthreads();
+    d4* red = (d4*)Z + w * share * 64 + lane;
+    if (term > 0) {
+#pragma unroll
+      for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int m = 0; m < TJ; ++m) red[(i * TJ + m) * 64] = acc[i][m];
+    }
+    __syncthreads();
+    if (term > 0) return;
+    for (int t = 1; t < jb.nterms; ++t) {
+      red = (d4*)(Zall + t * (16 * TJ * LD)) + w * share * 64 + lane;
+#pragma unroll
+      for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int m = 0; m < TJ; ++m) acc[i][m] += red[(i * TJ + m) * 64];
+    }
+  }
+  double* __restrict__ Y = (double*)jb.Y + slab;
+  const bool has_base = jb.base != nullptr;
+  const double* __restrict__ bs = (const double*)jb.base + slab;
+#pragma unroll
+  for (int m = 0; m < TJ; ++m) {
+    double bv[4][NI];
+    if (has_base) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+          bv[r][i] = bs[min(16 * (tj0 + m) + 4 * r + g, n2 - 1) * n1 + min(16 * (w + 4 * i) + l, n1 - 1)];
+    } else {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int i = 0; i < NI; ++i) bv[r][i] = -0.0;
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int j = 16 * (tj0 + m) + 4 * r + g;
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+        const int a = 16 * (w + 4 * i) + l;
+        if (j < n2 && a < n1) Y[j * n1 + a] = acc[i][m][r] + bv[r][i];
+      }
+    }
+  }
+}
+
+// SUM: jobs of kSlabTerms terms, each term on four waves of its own; else one.
+constexpr int kSlabTerms = 2;
+template <bool RAW, bool SUM, int TJ, int NI>
+__global__ void __launch_bounds__(SUM ? 256 * kSlabTerms : 256, 2) slab_f64_kernel(const SlabJobs J, int64_t per_xcd) {
+  // rows of Z two doubles apart from a multiple of 64: the 16 lanes of a
+  // phase-2 read start 16 bytes apart in the banks
+  constexpr int LD = 64 * NI + 2;
+  __shared__ double Z[(SUM ? kSlabTerms : 1) * 16 * TJ * LD];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t t = (uint32_t)remap_xcd(blockIdx.x, per_xcd);
+  if (t >= (uint32_t)J.total) return;   // uniform over the workgroup
+  const uint32_t jj = t / (uint32_t)J.tiles_per_job;
+  const SlabJob& jb = J.job[jj];
+  const uint32_t lt = t - jj * (uint32_t)J.tiles_per_job;
+  const uint32_t b = lt / (uint32_t)J.nblk;
+  const int blk = (int)(lt - b * (uint32_t)J.nblk);
+  const int nt1 = (jb.n1 + 15) >> 4, nt2 = (jb.n2 + 15) >> 4;
+  // column blocks: nt2 / nblk tiles each, the first nt2 % nblk one more
+  const int q = nt2 / J.nblk, rem = nt2 % J.nblk;
+  const int tj0 = blk * q + min(blk, rem), tj = q + (blk < rem);
+  const int w = ((wave & 3) + (int)(lt & 3)) & 3, term = SUM ? wave >> 2 : 0;
+  const int ni = (nt1 - w + 3) >> 2;   // tiles w, w + 4, .. below nt1
+  if (ni == 0) {   // a wave without i_1 blocks only keeps the barriers
+    for (int k = 0; k < (SUM ? 3 : 1); ++k) __syncthreads();
+    return;
+  }
+  if (tj == TJ) {
+    if (ni == NI) slab_body<RAW, SUM, TJ, NI, LD>(jb, b, tj0, w, term, lane, Z);
+    else if constexpr (NI > 1) slab_body<RAW, SUM, TJ, NI - 1, LD>(jb, b, tj0, w, term, lane, Z);
+  } else if constexpr (TJ > 1) {
+    if (ni == NI) slab_body<RAW, SUM, TJ - 1, NI, LD>(jb, b, tj0, w, term, lane, Z);
+    else if constexpr (NI > 1) slab_body<RAW, SUM, TJ - 1, NI - 1, LD>(jb, b, tj0, w, term, lane, Z);
   }
 }
 
@@ -630,18 +861,18 @@ int finish_tiles(ModeJobs& J, bool mode1, const TileCfg& t) {
   return SETD_OK;
 }
 
-template <bool M1, int TI, int TO, int KS, typename Off>
+template <bool M1, bool RAW, int TI, int TO, int KS, typename Off>
 int launch_tile(const ModeJobs& J, hipStream_t s) {
   const int64_t per = ceil_div(ceil_div(J.total_tiles, 4 / KS), 8);
-  hipLaunchKernelGGL((mode_f64_kernel<M1, TI, TO, KS, Off>), dim3((unsigned)(per * 8)), dim3(256), 0, s, J, per);
+  hipLaunchKernelGGL((mode_f64_kernel<M1, RAW, TI, TO, KS, Off>), dim3((unsigned)(per * 8)), dim3(256), 0, s, J, per);
   SETD_LAUNCHED();
   return SETD_OK;
 }
 
-template <bool M1>
+template <bool M1, bool RAW>
 int launch_cfg(const ModeJobs& J, const TileCfg& t, hipStream_t s) {
 #define SETD_TILE(TI_, TO_, KS_) \
-  if (t.ti == TI_ && t.to == TO_ && t.ks == KS_) return launch_tile<M1, TI_, TO_, KS_, uint32_t>(J, s);
+  if (t.ti == TI_ && t.to == TO_ && t.ks == KS_) return launch_tile<M1, RAW, TI_, TO_, KS_, uint32_t>(J, s);
   SETD_TILE(1, 1, 4)
   SETD_TILE(2, 2, 4)
   SETD_TILE(2, 2, 2)
@@ -696,27 +927,27 @@ void job_work(const ModeJobs& J, int es_in, int es_out, int es_mat, double& flop
   }
 }
 
-int launch_mode1_f64(ModeJobs& J, hipStream_t s) {
+int launch_mode1_f64(ModeJobs& J, hipStream_t s, bool raw) {
   double fl = 0.0, by = 0.0;
   if (prof_on()) job_work(J, 8, 8, 8, fl, by);
-  bool lds = J.njobs > 0;
+  bool lds = J.njobs > 0 && !raw;
   for (int j = 0; j < J.njobs; ++j) lds = lds && panel_job(J.job[j], true);
   const TileCfg cfg = env_tile("SETD_TILE_MODE1", choose_tile(J, true));
   if (lds) finish_panels(J, true);
   else finish_tiles(J, true, cfg);
   if (J.total_tiles == 0) return SETD_OK;
   ProfScope prof(s, kProfMode1F64, fl, by);
-  if (!lds) return launch_cfg<true>(J, cfg, s);
+  if (!lds) return raw ? launch_cfg<true, true>(J, cfg, s) : launch_cfg<true, false>(J, cfg, s);
   const int64_t per = ceil_div(J.total_tiles, 8);
   hipLaunchKernelGGL(mode1_lds_kernel, dim3((unsigned)(per * 8)), dim3(64 * kLdsWaves), 0, s, J, per, kLdsReps);
   SETD_LAUNCHED();
   return SETD_OK;
 }
 
-int launch_modeB_f64(ModeJobs& J, hipStream_t s) {
+int launch_modeB_f64(ModeJobs& J, hipStream_t s, bool raw) {
   double fl = 0.0, by = 0.0;
   if (prof_on()) job_work(J, 8, 8, 8, fl, by);
-  bool lds = J.njobs > 0, big = false;
+  bool lds = J.njobs > 0 && !raw, big = false;
   for (int j = 0; j < J.njobs; ++j) {
     lds = lds && panel_job(J.job[j], false);
     // a tile's offsets span more than 32 bits: 8 rows of X, or (with several
@@ -731,12 +962,62 @@ int launch_modeB_f64(ModeJobs& J, hipStream_t s) {
   if (J.total_tiles == 0) return SETD_OK;
   // the two kernels are timed as separate classes
   ProfScope prof(s, lds ? kProfModeBPanelF64 : kProfModeBF64, fl, by);
-  if (big && !lds) return launch_tile<false, 4, 2, 1, uint64_t>(J, s);
-  if (!lds) return launch_cfg<false>(J, cfg, s);
+  if (big && !lds)
+    return raw ? launch_tile<false, true, 4, 2, 1, uint64_t>(J, s) : launch_tile<false, false, 4, 2, 1, uint64_t>(J, s);
+  if (!lds) return raw ? launch_cfg<false, true>(J, cfg, s) : launch_cfg<false, false>(J, cfg, s);
   const int64_t per = ceil_div(J.total_tiles, 8);
   hipLaunchKernelGGL(modeB_lds_kernel, dim3((unsigned)(per * 8)), dim3(64 * kLdsWaves), 0, s, J, per, kLdsReps);
   SETD_LAUNCHED();
   return SETD_OK;
+}
+
+namespace {
+template <bool RAW, bool SUM, int TJ, int NI>
+int launch_slab_tile(SlabJobs& J, hipStream_t s) {
+  J.nblk = (int)ceil_div(ceil_div(J.job[0].n2, 16), TJ);
+  J.tiles_per_job = J.nblk * J.job[0].nb;
+  J.total = J.tiles_per_job * J.njobs;
+  const int64_t per = ceil_div(J.total, 8);
+  hipLaunchKernelGGL((slab_f64_kernel<RAW, SUM, TJ, NI>), dim3((unsigned)(per * 8)),
+                     dim3(SUM ? 256 * kSlabTerms : 256), 0, s, J, per);
+  SETD_LAUNCHED();
+  return SETD_OK;
+}
+
+template <bool RAW, bool SUM>
+int launch_slab_ni(SlabJobs& J, hipStream_t s) {
+  // one column tile per workgroup while that leaves a workgroup per CU or less
+  const bool wide = ceil_div(J.job[0].n2, 16) * J.job[0].nb * J.njobs > 256;
+  if constexpr (SUM) return launch_slab_tile<RAW, SUM, 1, 1>(J, s);   // n1 <= kSlabSumN
+  switch (ceil_div(J.job[0].n1, 64)) {
+    case 1: return wide ? launch_slab_tile<RAW, SUM, 2, 1>(J, s) : launch_slab_tile<RAW, SUM, 1, 1>(J, s);
+    case 2: return wide ? launch_slab_tile<RAW, SUM, 2, 2>(J, s) : launch_slab_tile<RAW, SUM, 1, 2>(J, s);
+    case 3: return wide ? launch_slab_tile<RAW, SUM, 2, 3>(J, s) : launch_slab_tile<RAW, SUM, 1, 3>(J, s);
+    case 4: return wide ? launch_slab_tile<RAW, SUM, 2, 4>(J, s) : launch_slab_tile<RAW, SUM, 1, 4>(J, s);
+  }
+  set_error("slab product: n1 = %d", J.job[0].n1);
+  return SETD_EUNSUPPORTED;
+}
+}  // namespace
+
+int launch_slab_f64(SlabJobs& J, hipStream_t s, bool raw) {
+  if (J.njobs == 0) return SETD_OK;
+  double fl = 0.0, by = 0.0;
+  bool sum = false;
+  for (int j = 0; j < J.njobs; ++j) {
+    const SlabJob& q = J.job[j];
+    const double N = (double)q.n1 * q.n2 * q.nb;
+    fl += q.nterms * 2.0 * N * (q.n1 + q.n2);
+    by += q.nterms * (8.0 * N + 8.0 * q.n1 * q.n1 + 8.0 * q.n2 * q.n2) + N * (q.base ? 16.0 : 8.0);
+    sum = sum || q.nterms > 1;
+  }
+  ProfScope prof(s, kProfMode1F64, fl, by);
+  if (raw && !sum) return launch_slab_ni<true, false>(J, s);
+  if (sum && (raw || J.job[0].n1 > kSlabSumN)) {
+    set_error("slab product: sums need packed matrices and n1 <= %d", kSlabSumN);
+    return SETD_EUNSUPPORTED;
+  }
+  return sum ? launch_slab_ni<false, true>(J, s) : launch_slab_ni<false, false>(J, s);
 }
 
 #define SETD_LAUNCH_LIST(TM_, TN_)                                                             \

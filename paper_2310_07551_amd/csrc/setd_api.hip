@@ -192,6 +192,25 @@ bool setd::i8_order312(int d, const int* dims, int nchains, size_t i8bytes) {
 
 bool setd::i8_emit() { return i8_emit_on(); }
 
+namespace {
+// Whether an FP64 group runs modes 1 and 2 as one pass over slabs.  d = 3: n1
+// up to 256 (phi_1 group of a step, the two products apart against the pass:
+// 64^3 51 -> 30 us, 128^3 414 -> 320, 200^3 2.18 -> 2.03 ms), but not where
+// both products have LDS panel kernels (256^3: 4.59 ms for the two, 4.82 for
+// the pass).  d = 2: up to 64 x 64, where the kernels are as long as their
+// latencies and the pass saves a launch (64^2: 9.2 -> 6.9 us; 100^2: 11 us
+// apart, 12.5 together, the products' contractions being split no further).
+bool use_slab(int d, const int* dims, const TuckerOut* outs, int nouts) {
+  if (d == 2) {
+    for (int o = 0; o < nouts; ++o)
+      if (outs[o].nterms != 2) return false;
+    return dims[0] <= kSlabSumN && dims[1] <= kSlabSumN;
+  }
+  const bool panels = dims[0] >= 192 && dims[0] % 64 == 0 && dims[1] >= 192 && dims[1] <= 256 && dims[1] % 64 == 0;
+  return d == 3 && dims[0] <= kSlabMaxN1 && !panels;
+}
+}  // namespace
+
 int setd::run_tucker_group(int d, const int* dims, TuckerOut* outs, int nouts, int prec, hipStream_t s,
                            void* i8ws, size_t i8bytes) {
   int64_t N = 1;
@@ -281,6 +300,49 @@ int setd::run_tucker_group(int d, const int* dims, TuckerOut* outs, int nouts, i
     k1.i8ws = chain_digits + (size_t)nchains * slot;
     k1.i8bytes = i8bytes - (size_t)nchains * slot;
     k1.fuse_next = dims[1];
+  }
+  // FP64: modes 1 and 2 in one pass; d = 3: the last mode sums the terms
+  if (prec == SETD_PREC_F64 && use_slab(d, dims, outs, nouts)) {
+    SlabJobs S;
+    S.njobs = 0;
+    for (int o = 0; o < nouts; ++o) {
+      SlabJob jb{};
+      jb.n1 = dims[0];
+      jb.n2 = dims[1];
+      jb.nb = N / ((int64_t)dims[0] * dims[1]);
+      jb.nterms = d == 2 ? outs[o].nterms : 1;
+      for (int t = 0; t < outs[o].nterms; ++t) {
+        const TuckerTerm& tm = outs[o].term[t];
+        const int k = d == 2 ? t : 0;
+        jb.X[k] = tm.X;
+        jb.P1[k] = tm.P[0];
+        jb.P2[k] = tm.P[1];
+        jb.scale[k] = tm.scale;
+        if (d == 2 && t + 1 < outs[o].nterms) continue;
+        jb.Y = d == 2 ? outs[o].Y : (double*)tm.Y2;
+        jb.base = d == 2 ? outs[o].base : nullptr;
+        S.job[S.njobs++] = jb;
+        if (S.njobs == kMaxJobs) {
+          SETD_TRY(launch_slab_f64(S, s));
+          S.njobs = 0;
+        }
+      }
+    }
+    SETD_TRY(launch_slab_f64(S, s));
+    if (d == 2) return SETD_OK;
+    ModeJobs J;
+    J.njobs = 0;
+    for (int o = 0; o < nouts; ++o) {
+      ModeJob jb = mk_job(nullptr, nullptr, 1.0, outs[o].Y, outs[o].base, (int64_t)dims[0] * dims[1], dims[2], 1);
+      jb.nterms = outs[o].nterms;
+      for (int t = 0; t < outs[o].nterms; ++t) {
+        jb.X[t] = outs[o].term[t].Y2;
+        jb.P[t] = outs[o].term[t].P[2];
+        jb.scale[t] = 1.0;
+      }
+      SETD_TRY(push(J, jb, klast, s));
+    }
+    return flush(J, klast, s);
   }
   ModeJobs J;
   J.njobs = 0;
