@@ -362,15 +362,24 @@ int launch_batch_pointwise(int kind, const BatchInstDev* inst, const int64_t* bl
 int launch_gf_stencil(const double* u, int ncomp, int64_t N, int d, const int* dims, const StencilSet& S,
                       const GParams& gp, double* G, void* F, DType ftype, hipStream_t s) {
   const int n3 = d == 3 ? dims[2] : 1;
-  constexpr int RB = 8;   // i2 rows per thread
   const int bx = (int)std::min<int64_t>(256, round_up(dims[0], 64));
-  const dim3 grid((unsigned)ceil_div(dims[0], bx), (unsigned)ceil_div(dims[1], RB), (unsigned)n3);
+  // i2 rows per thread: 8 where the grid fills the chip anyway (each row is
+  // read once; 256^3 0.222 ms, 0.290 with 1), fewer on small grids, where a
+  // thread's rows would run one after the other (64^2 7.1 us with 8, 3.6 with
+  // 1; 300^2 10.1 and 5.4; 64^3 9.4 with 8, 7.1 with 2)
+  const int rows = N <= (1 << 17) ? 1 : N <= (1 << 19) ? 2 : 8;
+  const dim3 grid((unsigned)ceil_div(dims[0], bx), (unsigned)ceil_div(dims[1], rows), (unsigned)n3);
   // reads u once, writes G (FP64) and F
   ProfScope prof(s, kProfPointwise, 0.0, (double)N * ncomp * (8 + 8 + (ftype == DType::F64 ? 8 : 4)));
-  auto launch = [&](auto tf, auto nc) {
+  auto launch_rows = [&](auto tf, auto nc, auto rb) {
     using TF = decltype(tf);
-    hipLaunchKernelGGL((gf_stencil_kernel<TF, RB, decltype(nc)::value>), grid, dim3(bx), 0, s, u, N, d, dims[0],
-                       dims[1], n3, S, gp, G, (TF*)F);
+    hipLaunchKernelGGL((gf_stencil_kernel<TF, decltype(rb)::value, decltype(nc)::value>), grid, dim3(bx), 0, s, u, N, d,
+                       dims[0], dims[1], n3, S, gp, G, (TF*)F);
+  };
+  auto launch = [&](auto tf, auto nc) {
+    if (rows == 1) launch_rows(tf, nc, std::integral_constant<int, 1>{});
+    else if (rows == 2) launch_rows(tf, nc, std::integral_constant<int, 2>{});
+    else launch_rows(tf, nc, std::integral_constant<int, 8>{});
   };
   if (ftype == DType::F64) {
     if (ncomp == 1) launch(0.0, std::integral_constant<int, 1>{});
