@@ -193,6 +193,11 @@ bool setd::i8_order312(int d, const int* dims, int nchains, size_t i8bytes) {
 bool setd::i8_emit() { return i8_emit_on(); }
 
 namespace {
+// Slabs of 32 rows or fewer leave two of a workgroup's four waves without
+// work; on a small tensor that costs less than a launch (phi_1 group of a
+// step: 32^3 9 us against 14 for two products, 20 x 100 x 100 53 against 49).
+bool slab_rows(int64_t n1, int64_t N) { return n1 > 32 || N <= (1 << 17); }
+
 // Whether an FP64 group runs modes 1 and 2 as one pass over slabs.  d = 3: n1
 // up to 256 (phi_1 group of a step, the two products apart against the pass:
 // 64^3 51 -> 30 us, 128^3 414 -> 320, 200^3 2.18 -> 2.03 ms), but not where
@@ -207,7 +212,7 @@ bool use_slab(int d, const int* dims, const TuckerOut* outs, int nouts) {
     return dims[0] <= kSlabSumN && dims[1] <= kSlabSumN;
   }
   const bool panels = dims[0] >= 192 && dims[0] % 64 == 0 && dims[1] >= 192 && dims[1] <= 256 && dims[1] % 64 == 0;
-  return d == 3 && dims[0] <= kSlabMaxN1 && !panels;
+  return d == 3 && dims[0] <= kSlabMaxN1 && !panels && slab_rows(dims[0], (int64_t)dims[0] * dims[1] * dims[2]);
 }
 }  // namespace
 
@@ -793,6 +798,84 @@ int noalloc_scratch(void** out) {
 }
 }  // namespace
 
+namespace {
+
+// FP64 Tucker operator with the matrices read as they are given: packing pays
+// when a matrix is used again, or by many tiles (256^3; the LDS panel kernels
+// need it).  At 150^3 the three packing launches took 13 of 118 us, at 64^2
+// half of the four launches.
+constexpr int64_t kRawElems = int64_t(1) << 23;
+
+// Modes 1 and 2 as one pass over slabs, which needs no intermediate.  A few
+// slabs run on a few workgroups (about 4.5 + 0.13 c us, c = chunks of both
+// contractions x blocks of 64 rows), against two launches (10 us) and, without
+// a workspace from the caller, an allocation (18 us): 64^2 9 us a call (40
+// with packing and two products), 128^2 10 (40), 200^2 29 by two products.
+bool raw_slab(const int64_t* dims, int64_t nb, bool own_ws) {
+  if (dims[0] > kSlabMaxN1) return false;
+  const int64_t c = (ceil_div(dims[0], 8) + ceil_div(dims[1], 8)) * ceil_div(dims[0], 64);
+  if (nb * ceil_div(dims[1], 16) <= 64) return c <= (own_ws ? 180 : 50);
+  return dims[1] >= 8 && slab_rows(dims[0], nb * dims[0] * dims[1]);
+}
+
+int tucker_raw(const double* V, double* W, int d, const int64_t* dims, int64_t N, const double* const* M,
+               const int* modes, int nm, double alpha, double beta, void* ws, hipStream_t s) {
+  const bool slab = nm >= 2 && modes[0] == 0 && modes[1] == 1 &&
+                    raw_slab(dims, N / (dims[0] * dims[1]), ws == nullptr);
+  const int nops = slab ? nm - 1 : nm;
+  const int64_t fb = round_up(N * 8, 256);
+  void* own = nullptr;
+  if (nops > 1 && ws == nullptr) SETD_HIP(hipMallocAsync(&own, std::min(nops - 1, 2) * fb, s));
+  char* q = (char*)round_up((int64_t)(uintptr_t)(own ? own : ws), 256);
+  double* buf[2] = {(double*)q, (double*)(q + fb)};
+  // beta: the last product adds W, scaled first unless beta is 1
+  int rc = beta != 0.0 && beta != 1.0 ? launch_scale(W, N, beta, s) : SETD_OK;
+  const double* src = V;
+  for (int op = 0, k = 0; op < nops && rc == SETD_OK; ++op) {
+    const bool last = op == nops - 1;
+    double* dst = last ? W : buf[op & 1];
+    const double* base = last && beta != 0.0 ? W : nullptr;
+    const double scale = last ? alpha : 1.0;
+    if (slab && op == 0) {
+      SlabJobs S;
+      S.njobs = 1;
+      SlabJob jb{};
+      jb.X[0] = src;
+      jb.P1[0] = M[0];
+      jb.P2[0] = M[1];
+      jb.scale[0] = scale;
+      jb.nterms = 1;
+      jb.Y = dst;
+      jb.base = base;
+      jb.n1 = (int)dims[0];
+      jb.n2 = (int)dims[1];
+      jb.nb = N / (dims[0] * dims[1]);
+      S.job[0] = jb;
+      rc = launch_slab_f64(S, s, true);
+      k = 2;
+    } else {
+      const int mu = modes[k++];
+      int64_t na = 1;
+      for (int nu = 0; nu < mu; ++nu) na *= dims[nu];
+      ModeJobs J;
+      J.njobs = 1;
+      J.job[0] = mk_job(src, M[mu], scale, dst, base, na, (int)dims[mu], N / (na * dims[mu]));
+      rc = mu == 0 ? launch_mode1_f64(J, s, true) : launch_modeB_f64(J, s, true);
+    }
+    src = dst;
+  }
+  if (own) {
+    const hipError_t e = hipFreeAsync(own, s);
+    if (rc == SETD_OK && e != hipSuccess) {
+      set_error("hipFreeAsync failed: %s", hipGetErrorString(e));
+      rc = SETD_EHIP;
+    }
+  }
+  return rc;
+}
+
+}  // namespace
+
 extern "C" {
 
 const char* setd_last_error(void) { return g_err; }
@@ -923,6 +1006,12 @@ int setd_tucker_apply(const double* V, double* W, int d, const int64_t* dims, co
   int modes[8], nm = 0;
   for (int mu = 0; mu < d; ++mu)
     if (M[mu] != nullptr) modes[nm++] = mu;
+  // a matrix inside W has to be packed before W is written
+  bool in_w = false;
+  for (int k = 0; k < nm; ++k)
+    in_w = in_w || overlap(M[modes[k]], (size_t)dims[modes[k]] * dims[modes[k]] * 8, W, N * 8);
+  if (prec == SETD_PREC_F64 && nm > 0 && N <= kRawElems && !in_w)
+    return tucker_raw(V, W, d, dims, N, M, modes, nm, alpha, beta, ws, s);
   // the workspace first, so that a failed allocation leaves W untouched
   void* wsp = ws;
   bool own = false;

@@ -38,3 +38,39 @@ def test_modes_1_and_2_in_one_pass(dims):
         assert rel_err(host(W, dims), 0.3 * ref + W0) < TOL, (dims, ell)
         ctx.split_phi_apply(1, ell, stage, dev(V), W)
         assert rel_err(host(W, dims), ref) < TOL, (dims, ell)
+
+
+@pytest.mark.parametrize("dims", [(2, 2), (16, 8), (33, 17), (64, 64), (65, 100), (130, 7), (200, 40), (256, 31), (300, 9),
+                                  (20, 9, 30), (40, 50, 3), (100, 37, 20), (17, 33, 5, 4), (3, 64, 90)])
+@pytest.mark.parametrize("own", [True, False])
+def test_matrices_as_given(dims, own):
+    """Tucker operators that read their matrices unpacked: one pass or single
+    products, every subset of modes, with and without the caller's workspace.
+    n <= 300 products of uniform entries: 1e-13 of the largest result."""
+    T, W0 = wl.random_tensor(dims, 1), wl.random_tensor(dims, 2)
+    Ls = [wl.random_matrix(n, 3 + k, scale=0.3) for k, n in enumerate(dims)]
+    ws = None if own else torch().empty(setd.tucker_workspace_bytes(dims) // 8 + 1, dtype=torch().float64, device="cuda")
+    d = len(dims)
+    for mask in range(1, 2 ** d):
+        mats = [Ls[mu] if mask >> mu & 1 else None for mu in range(d)]
+        ref = T
+        for mu in range(d):
+            if mats[mu] is not None:
+                ref = oracle.mode_product(ref, mats[mu], mu + 1)
+        for alpha, beta in ((1.0, 0.0), (-0.7, 1.0), (0.5, 0.25)):
+            W = dev(W0)
+            say("as given", dims, mask, alpha, beta)
+            setd.tucker_apply(dev(T), W, dims, [None if L is None else dev(L) for L in mats], alpha=alpha, beta=beta,
+                              workspace=ws)
+            assert rel_err(host(W, dims), alpha * ref + beta * W0) < 1e-13, (dims, mask, alpha, beta)
+
+
+def test_matrix_inside_the_result():
+    """A matrix that lies in W's memory is used as it was before the call."""
+    dims = (40, 30)
+    T = wl.random_tensor(dims, 1)
+    L = [wl.random_matrix(40, 2), wl.random_matrix(30, 3)]
+    W = dev(wl.random_tensor(dims, 4))
+    W[:900].copy_(dev(L[1]))
+    setd.tucker_apply(dev(T), W, dims, [dev(L[0]), W[:900]])
+    assert rel_err(host(W, dims), oracle.tucker(T, L)) < 1e-13
