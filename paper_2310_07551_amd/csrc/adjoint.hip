@@ -203,7 +203,8 @@ int build_adjoint_bank(setd_ctx* c, hipStream_t s) {
     for (int mu = 0; mu < d; ++mu) bytes += (2 * 5 * T + 1) * packed_bytes(c->dims[mu], SETD_PREC_F64);
   SETD_TRY(c->adj_bank_mem.alloc(bytes));
   char* q = (char*)c->adj_bank_mem.p;
-  for (int cc = 0; cc < c->ncomp; ++cc)
+  for (int cc = 0; cc < c->ncomp; ++cc) {
+    std::vector<double> scals[3];
     for (int mu = 0; mu < d; ++mu) {
       const int n = c->dims[mu];
       const size_t pb = packed_bytes(n, SETD_PREC_F64);
@@ -213,33 +214,45 @@ int build_adjoint_bank(setd_ctx* c, hipStream_t s) {
         for (int t = 0; t < T; ++t)
           scal.push_back(stage_scale(kBankStage[e]) * c->tau * c->sp[kBankEll[e]].alpha[t][mu]);
       const int E = (int)scal.size();
-      DevBuf A, raw, tmp;
+      // a direction with an earlier one's matrix and scalars shares its packed matrices
+      int same = -1;
+      for (int nu = 0; nu < mu && same < 0; ++nu)
+        if (c->dims[nu] == n && c->Ah[cc][nu] == c->Ah[cc][mu] && scals[nu] == scal) same = nu;
+      scals[mu] = scal;
+      if (same >= 0) {
+        for (int e = 0; e < 5; ++e)
+          for (int t = 0; t < T; ++t) {
+            c->bankT[cc][e][t][mu] = c->bankT[cc][e][t][same];
+            c->dbank[cc][e][t][mu] = c->dbank[cc][e][t][same];
+          }
+        c->ApkT[cc][mu] = c->ApkT[cc][same];
+        continue;
+      }
+      DevBuf A, raw;
       SETD_TRY(A.alloc(nn * sizeof(double)));
       SETD_HIP(hipMemcpyAsync(A.p, c->Ah[cc][mu].data(), nn * sizeof(double), hipMemcpyHostToDevice, s));
       SETD_TRY(raw.alloc((size_t)E * 3 * nn * sizeof(double)));
-      SETD_TRY(tmp.alloc(nn * sizeof(double)));
-      std::vector<double*> outs(E * 3);
-      for (int k = 0; k < E * 3; ++k) outs[k] = (double*)raw.p + (size_t)k * nn;
-      SETD_TRY(phi_batch((const double*)A.p, n, scal.data(), E, 2, outs.data(), s));
+      SETD_TRY(phi_batch((const double*)A.p, n, scal.data(), E, 2, (double*)raw.p, s));
+      std::vector<PackJob> jobs;
+      auto phi = [&](int k, int l) { return (const double*)raw.p + (size_t)(k * 3 + l) * nn; };
       for (int e = 0; e < 5; ++e)
         for (int t = 0; t < T; ++t) {
           const int k = e * T + t;
           const int li = c->sp[kBankEll[e]].ell_i[t];
           c->bankT[cc][e][t][mu] = q;
-          SETD_TRY(pack_matrix_f64(outs[k * 3 + li], n, 1.0, true, (double*)q, s));
+          jobs.push_back({phi(k, li), nullptr, 0.0, true, (double*)q});
           q += pb;
-          // phi_{l-1} - l phi_l
-          SETD_HIP(hipMemcpyAsync(tmp.p, outs[k * 3 + li - 1], nn * sizeof(double), hipMemcpyDeviceToDevice, s));
-          SETD_TRY(launch_axpby(outs[k * 3 + li], (double*)tmp.p, (int64_t)nn, -(double)li, 1.0, s));
-          c->dbank[cc][e][t][mu] = q;
-          SETD_TRY(pack_matrix_f64((const double*)tmp.p, n, 1.0, false, (double*)q, s));
+          c->dbank[cc][e][t][mu] = q;   // phi_{l-1} - l phi_l
+          jobs.push_back({phi(k, li - 1), phi(k, li), -(double)li, false, (double*)q});
           q += pb;
         }
       c->ApkT[cc][mu] = q;
-      SETD_TRY(pack_matrix_f64((const double*)A.p, n, 1.0, true, (double*)q, s));
+      jobs.push_back({(const double*)A.p, nullptr, 0.0, true, (double*)q});
       q += pb;
-      SETD_HIP(hipStreamSynchronize(s));   // A, raw and tmp are released at scope exit
+      SETD_TRY(pack_matrices_f64(jobs.data(), (int)jobs.size(), n, s));
+      SETD_HIP(hipStreamSynchronize(s));   // A and raw are released at scope exit
     }
+  }
   c->adj_tau = c->tau;
   return SETD_OK;
 }

@@ -184,15 +184,16 @@ int build_banks(setd_batch* B, const std::vector<std::vector<double>>& Ah, const
     const size_t nn = (size_t)n * n;
     DevBuf raw;
     SETD_TRY(raw.alloc((size_t)E * 3 * nn * sizeof(double)));
-    std::vector<double*> outs(E * 3);
-    for (int j = 0; j < E * 3; ++j) outs[j] = (double*)raw.p + (size_t)j * nn;
-    SETD_TRY(phi_batch(S.A_dev, n, scal.data(), E, 2, outs.data(), s));
+    SETD_TRY(phi_batch(S.A_dev, n, scal.data(), E, 2, (double*)raw.p, s));
+    std::vector<PackJob> jobs;
     for (int e = 0; e < 5; ++e)
       for (int t = 0; t < T; ++t) {
         const int j = e * T + t;
         const int li = B->sp[kBankEll[e]].ell_i[t];
-        SETD_TRY(pack_matrix_f64(outs[j * 3 + li], n, 1.0, false, (double*)packed(B, (int)k, j), s));
+        jobs.push_back({(const double*)raw.p + (size_t)(j * 3 + li) * nn, nullptr, 0.0, false,
+                        (double*)packed(B, (int)k, j)});
       }
+    SETD_TRY(pack_matrices_f64(jobs.data(), (int)jobs.size(), n, s));
     SETD_HIP(hipStreamSynchronize(s));   // raw is released at scope exit
   }
   SETD_HIP(hipStreamSynchronize(s));

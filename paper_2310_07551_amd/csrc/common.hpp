@@ -208,6 +208,15 @@ void job_work(const ModeJobs& J, int es_in, int es_out, int es_mat, double& flop
 //   rowmajor:       out[i*ldp + p] = scale*M[i + n p]   (mode-1 operand)
 //   not rowmajor:   out[i + ldp*p] = scale*M[i + n p]   (modes >= 2 operand)
 int pack_matrix_f64(const double* M, int n, double scale, bool trans, double* out, hipStream_t s);
+// Several FP64 matrices of one size: src + coef * src2 (src2 nullable).
+struct PackJob {
+  const double* src;
+  const double* src2;
+  double coef;
+  bool trans;
+  double* out;
+};
+int pack_matrices_f64(const PackJob* jobs, int count, int n, hipStream_t s);
 int pack_matrix_f32(const double* M, int n, double scale, bool rowmajor, float* out, hipStream_t s);
 int pack_matrix_bf16(const double* M, int n, double scale, bool rowmajor, int np, void* out, hipStream_t s);
 inline bool is_prec(int p) {

@@ -87,11 +87,9 @@ int build_cplx_bank(setd_ctx* c, double tau, hipStream_t s) {
             }
           const int E = (int)scal.size();
           SETD_TRY(raw.alloc((size_t)E * 3 * mm * 8));
-          std::vector<double*> outs(E * 3);
-          for (int k = 0; k < E * 3; ++k) outs[k] = (double*)raw.p + (size_t)k * mm;
-          SETD_TRY(phi_batch((const double*)B.p, 2 * n, scal.data(), E, 2, outs.data(), s));
+          SETD_TRY(phi_batch((const double*)B.p, 2 * n, scal.data(), E, 2, (double*)raw.p, s));
           for (int k = 0; k < E; ++k) {
-            const double* P = outs[k * 3 + li];
+            const double* P = (const double*)raw.p + (size_t)(k * 3 + li) * mm;
             SETD_TRY(extract_block(P, n, 0, (double*)Pr.p, s));   // Re: upper-left block
             SETD_TRY(extract_block(P, n, n, (double*)Pi.p, s));   // Im: lower-left block
             const double* src_r = (const double*)Pr.p;

@@ -19,17 +19,28 @@ namespace setd {
 // ---------------------------------------------------------------------------
 // packing
 // ---------------------------------------------------------------------------
-// FP64: entry (tile t, chunk c, lane, j) = scale * M[16 t + lane % 16][8 c + 2 (lane / 16) + j],
-// M[i][p] at i + n p (trans: at p + n i).  One thread per entry.
-__global__ void pack_f64_kernel(const double* __restrict__ M, int n, double scale, bool trans,
-                                double* __restrict__ out, int64_t tot) {
+// FP64: entry (tile t, chunk c, lane, j) = M[16 t + lane % 16][8 c + 2 (lane / 16) + j],
+// M[i][p] at i + n p (trans: at p + n i).  One thread per entry, one blockIdx.y
+// per matrix: the 45 matrices of a 3D component in 3 launches.
+constexpr int kPackJobs = 48;
+struct PackTable {
+  PackJob job[kPackJobs];
+};
+__global__ void pack_f64_kernel(const PackTable T, int n, double scale, int64_t tot) {
   const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= tot) return;
+  const PackJob& J = T.job[blockIdx.y];
   const int nch = (n + 7) >> 3;
   const int e = (int)(idx & 127), lane = e >> 1;
   const int64_t tc = idx >> 7;
   const int i = 16 * (int)(tc / nch) + (lane & 15), p = 8 * (int)(tc % nch) + 2 * (lane >> 4) + (e & 1);
-  out[idx] = (i < n && p < n) ? scale * M[trans ? p + (int64_t)n * i : i + (int64_t)n * p] : 0.0;
+  double v = 0.0;
+  if (i < n && p < n) {
+    const int64_t at = J.trans ? p + (int64_t)n * i : i + (int64_t)n * p;
+    v = scale * J.src[at];
+    if (J.src2) v += J.coef * J.src2[at];
+  }
+  J.out[idx] = v;
 }
 
 template <typename T>
@@ -82,9 +93,22 @@ size_t packed_bytes(int n, int prec) {
 
 int pack_matrix_f64(const double* M, int n, double scale, bool trans, double* out, hipStream_t s) {
   const int64_t tot = ceil_div(n, 16) * ceil_div(n, 8) * 128;
-  hipLaunchKernelGGL(pack_f64_kernel, dim3((unsigned)ceil_div(tot, 256)), dim3(256), 0, s, M, n, scale, trans, out,
-                     tot);
+  PackTable T{};
+  T.job[0] = {M, nullptr, 0.0, trans, out};
+  hipLaunchKernelGGL(pack_f64_kernel, dim3((unsigned)ceil_div(tot, 256)), dim3(256), 0, s, T, n, scale, tot);
   SETD_LAUNCHED();
+  return SETD_OK;
+}
+
+int pack_matrices_f64(const PackJob* jobs, int count, int n, hipStream_t s) {
+  const int64_t tot = ceil_div(n, 16) * ceil_div(n, 8) * 128;
+  for (int k = 0; k < count; k += kPackJobs) {
+    const int m = std::min(kPackJobs, count - k);
+    PackTable T{};
+    std::copy(jobs + k, jobs + k + m, T.job);
+    hipLaunchKernelGGL(pack_f64_kernel, dim3((unsigned)ceil_div(tot, 256), (unsigned)m), dim3(256), 0, s, T, n, 1.0, tot);
+    SETD_LAUNCHED();
+  }
   return SETD_OK;
 }
 

@@ -78,8 +78,10 @@ size_t norm_workspace_bytes();
 int launch_norms(const double* x, const double* y, int64_t n, double* ws, hipStream_t s);
 
 // phi-functions of c_j * A for a batch of scalars (phi.hip).  For entry j the
-// blocks phi_0..phi_p(c_j A) are written to out[j*(p+1) + k] (device n x n
-// column-major).  Synchronises s.
-int phi_batch(const double* A, int n, const double* c, int nentries, int p, double* const* out, hipStream_t s);
+// blocks phi_0..phi_p(c_j A) are written to out + (j (p+1) + k) n^2 (device
+// n x n column-major).  Synchronises s.
+int phi_batch(const double* A, int n, const double* c, int nentries, int p, double* out, hipStream_t s);
+// Frees the workspace that the builds keep on a device.
+int phi_release_workspace(int dev);
 
 }  // namespace setd

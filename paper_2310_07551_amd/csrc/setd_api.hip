@@ -485,22 +485,28 @@ int build_bank(setd_ctx* c, hipStream_t s) {
       const size_t nn = (size_t)n * n;
       if (rep[mu] == mu) {
         SETD_TRY(raw[mu].alloc((size_t)E * 3 * nn * sizeof(double)));
-        std::vector<double*> outs(E * 3);
-        for (int k = 0; k < E * 3; ++k) outs[k] = (double*)raw[mu].p + (size_t)k * nn;
-        SETD_TRY(phi_batch(Adev(cc, mu), n, scal[mu].data(), E, 2, outs.data(), s));
+        SETD_TRY(phi_batch(Adev(cc, mu), n, scal[mu].data(), E, 2, (double*)raw[mu].p, s));
       }
       const double* src = (const double*)raw[rep[mu]].p;
+      const bool f64 = c->prec == SETD_PREC_F64;
+      std::vector<PackJob> jobs;   // FP64: one launch for the direction
+      auto pack = [&](const double* M, void** slot) -> int {
+        if (!f64) return pack_for(c->prec, M, n, 1.0, mu, slot[mu], s);
+        if (rep[mu] != mu) slot[mu] = slot[rep[mu]];   // the same matrices, one packing for every mode
+        else jobs.push_back({M, nullptr, 0.0, false, (double*)slot[mu]});
+        return SETD_OK;
+      };
       for (int k = 0; k < E; ++k) {
         if (which[mu][k] < 0) {
-          for (int l = 1; l <= 2; ++l)
-            SETD_TRY(pack_for(c->prec, src + ((size_t)k * 3 + l) * nn, n, 1.0, mu, c->bank2[cc][l - 1][mu], s));
+          for (int l = 1; l <= 2; ++l) SETD_TRY(pack(src + ((size_t)k * 3 + l) * nn, c->bank2[cc][l - 1]));
           continue;
         }
         const int e = which[mu][k] / 3, t = which[mu][k] % 3;
         const int li = c->sp[kBankEll[e]].ell_i[t];
-        SETD_TRY(pack_for(c->prec, src + ((size_t)k * 3 + li) * nn, n, 1.0, mu, c->bank[cc][e][t][mu], s));
+        SETD_TRY(pack(src + ((size_t)k * 3 + li) * nn, c->bank[cc][e][t]));
       }
-      SETD_TRY(pack_matrix_f64(Adev(cc, mu), n, 1.0, false, (double*)c->Apk[cc][mu], s));
+      jobs.push_back({Adev(cc, mu), nullptr, 0.0, false, (double*)c->Apk[cc][mu]});
+      SETD_TRY(pack_matrices_f64(jobs.data(), (int)jobs.size(), n, s));
     }
     SETD_HIP(hipStreamSynchronize(s));   // raw buffers are released at scope exit
   }
@@ -928,7 +934,7 @@ int setd_release_workspace(void) {
   hipMemPool_t pool;
   SETD_HIP(hipDeviceGetDefaultMemPool(&pool, dev));
   SETD_HIP(hipMemPoolTrimTo(pool, 0));
-  return SETD_OK;
+  return phi_release_workspace(dev);
 }
 
 int setd_phi_matrices(const double* A, int64_t n, double tau, int ell, double* out, void* stream) {
@@ -941,10 +947,7 @@ int setd_phi_matrices(const double* A, int64_t n, double tau, int ell, double* o
     set_error("tau is not finite");
     return SETD_ENONFINITE;
   }
-  hipStream_t s = (hipStream_t)stream;
-  std::vector<double*> outs(ell + 1);
-  for (int k = 0; k <= ell; ++k) outs[k] = out + (size_t)k * n * n;
-  return phi_batch(A, (int)n, &tau, 1, ell, outs.data(), s);
+  return phi_batch(A, (int)n, &tau, 1, ell, out, (hipStream_t)stream);
 }
 
 int setd_tucker_apply_noalloc(const double* V, double* W, int d, const int64_t* dims, const double* const* M,
