@@ -329,14 +329,15 @@ int setd_etd_adjoint_step_recorded(setd_ctx* ctx, const double* u, const double*
  * The work lists refer to u itself: a call with another u rebuilds them
  * (synchronising); calls that overlap on the same u race.
  *
- * setd_batch_tune times every candidate tile shape (2 or 4 tiles of 16 on
- * each side) and grid cap on the phi_1 group of the step, separately for
- * mode 1 and for modes >= 2, and keeps the fastest.  Synchronises `stream`.
+ * setd_batch_tune times every candidate tile (2 or 4 tiles of 16 on each
+ * side, its contraction on 1, 2 or 4 waves) on the phi_1 and the phi_2 groups
+ * of the step, separately for mode 1 and for modes >= 2, and keeps the
+ * fastest.  Synchronises `stream`.
  * setd_batch_set_tiles fixes them instead: cfg (host) = {tm, tn, cap} for
  * mode 1 followed by {tm, tn, cap} for modes >= 2 (cap = largest number of
  * workgroups of a launch, 0 = one per tile).
- * setd_batch_info (host, SETD_BATCH_INFO entries): the six tile values as
- * for setd_batch_set_tiles, whether they were tuned or set, launches per
+ * setd_batch_info (host, SETD_BATCH_INFO entries): the six tile values of the
+ * phi_1 group as for setd_batch_set_tiles, whether they were tuned or set, launches per
  * step (0 before the first step), the length of u, and the number of
  * distinct packed matrix sets.
  */

@@ -16,6 +16,7 @@
 // by timing candidate shapes on the batch's own work lists.
 #include <algorithm>
 #include <cmath>
+#include <cstdio>
 #include <cstdlib>
 #include <cstring>
 #include <new>
@@ -51,6 +52,11 @@ struct PackedSet {
   size_t offset = 0;         // bytes into bank_mem
   int count = 0;             // matrices in the set
   const double* A_dev = nullptr;
+};
+
+// {tm, tn, grid cap, waves per tile} for mode 1 and for modes >= 2.
+struct TileChoice {
+  int mode1[4], modeB[4];
 };
 
 struct Op {
@@ -94,8 +100,9 @@ struct setd_batch {
   // reaction parameters: inst_host holds the latest, inst_dev gets them
   // before the next launch
   bool params_dirty = true;
-  // tile choice: {tm, tn, grid cap} for mode 1 and for modes >= 2
-  int cfg1[3] = {4, 4, 0}, cfgB[3] = {4, 2, 0};
+  // tile choice of the phi_1 group and of the phi_2 groups (a third of its
+  // products): mode 1 (tm blocks of i) and modes >= 2 (tn blocks of i)
+  TileChoice tiles[2] = {{{4, 4, 0, 1}, {4, 2, 0, 1}}, {{2, 2, 0, 1}, {2, 2, 0, 1}}};
   bool tuned = false;
   // plan of one step for state buffer plan_u
   std::vector<Op> plan;
@@ -218,25 +225,25 @@ struct Out {
 
 struct PlanBuilder {
   setd_batch* B;
-  const int* c1;
-  const int* cb;
+  const TileChoice* tiles;   // of the two kinds of group
   std::vector<Op> ops;
   std::vector<std::vector<ModeJob>> lists;   // host jobs of each list op (same order as list ops)
 
   // Appends one list launch, its jobs sorted by the length of a tile's
   // contraction, longest first, so that the last tiles to run are short ones.
-  void add_list(std::vector<ModeJob>& jobs, bool mode1) {
+  void add_list(std::vector<ModeJob>& jobs, bool mode1, int kind) {
     if (jobs.empty()) return;
-    const int* cfg = mode1 ? c1 : cb;
+    const int* cfg = mode1 ? tiles[kind].mode1 : tiles[kind].modeB;
     std::stable_sort(jobs.begin(), jobs.end(),
                      [](const ModeJob& a, const ModeJob& b) { return a.nterms * a.n > b.nterms * b.n; });
     Op op{};
     op.list = true;
     op.L.njobs = (int)jobs.size();
-    op.L.total = assign_tiles_f64(jobs.data(), op.L.njobs, mode1, cfg[mode1 ? 0 : 1], cfg[mode1 ? 1 : 0]);
     op.L.mode1 = mode1;
-    op.L.tm = cfg[0];
-    op.L.tn = cfg[1];
+    op.L.ti = cfg[mode1 ? 0 : 1];
+    op.L.to = cfg[mode1 ? 1 : 0];
+    op.L.ks = cfg[3];
+    op.L.total = assign_tiles_f64(jobs.data(), op.L.njobs, mode1, op.L.ti, op.L.to);
     op.L.grid_cap = cfg[2];
     for (const ModeJob& jb : jobs) {
       const double N = (double)jb.na * jb.n * jb.nb;
@@ -261,8 +268,9 @@ struct PlanBuilder {
   // All outputs of one Tucker group over every instance (cf. the grouped
   // launches of the single-instance step): mode 1 into Y1, inner modes
   // ping-pong, last mode summing the terms and adding the base.
-  // part: 0 all modes, 1 mode 1 only, 2 modes >= 2 only (for the tuner).
-  void group(const std::vector<Out>& outs, int part = 0) {
+  // kind: 0 the phi_1 group, 1 a phi_2 group (whose tiles it takes); part: 0
+  // all modes, 1 mode 1 only, 2 modes >= 2 only (for the tuner).
+  void group(const std::vector<Out>& outs, int kind, int part = 0) {
     const int d = B->d;
     std::vector<ModeJob> jobs;
     if (part != 2) {
@@ -273,7 +281,7 @@ struct PlanBuilder {
           jobs.push_back(mk_job(tm.X, tm.P[0], tm.scale, tm.Y1, nullptr, 1, I.dims[0], I.N / I.dims[0]));
         }
       }
-      add_list(jobs, true);
+      add_list(jobs, true, kind);
       if (part == 1) return;
     }
     {
@@ -289,7 +297,7 @@ struct PlanBuilder {
             jobs.push_back(mk_job(src, tm.P[mu], 1.0, dst, nullptr, na, I.dims[mu], I.N / (na * I.dims[mu])));
           }
         }
-        add_list(jobs, false);
+        add_list(jobs, false, kind);
       }
     }
     const int mu = d - 1;
@@ -311,7 +319,7 @@ struct PlanBuilder {
       jb.ldp = packed_ld(jb.n);
       jobs.push_back(jb);
     }
-    add_list(jobs, false);
+    add_list(jobs, false, kind);
   }
 
   // Outputs of the phi_1 group on F (stages 2, 3 and final) for every
@@ -394,7 +402,7 @@ struct PlanBuilder {
                               I.N / I.dims[0]));
       }
     }
-    add_list(jobs, true);
+    add_list(jobs, true, 1);
     for (int mu = 1; mu < B->d; ++mu) {
       for (int b = 0; b < B->nb; ++b) {
         const Inst& I = B->inst[b];
@@ -406,7 +414,7 @@ struct PlanBuilder {
                                 I.N / (na * I.dims[mu])));
         }
       }
-      add_list(jobs, false);
+      add_list(jobs, false, 1);
     }
   }
 
@@ -414,11 +422,11 @@ struct PlanBuilder {
   void step(double* u) {
     const double tau = B->tau;
     gf(u);
-    group(f_group(u, nullptr));
+    group(f_group(u, nullptr), 0);
     pointwise(2, B->U2, B->G, B->D);
-    group(d_group(bank_index(SETD_STAGE_3, 2), 4.0 * tau / 3.0, B->U3, B->U3));
+    group(d_group(bank_index(SETD_STAGE_3, 2), 4.0 * tau / 3.0, B->U3, B->U3), 1);
     pointwise(2, B->U3, B->G, B->D);
-    group(d_group(bank_index(SETD_STAGE_F, 2), 1.5 * tau, u, B->W));
+    group(d_group(bank_index(SETD_STAGE_F, 2), 1.5 * tau, u, B->W), 1);
   }
 
   // Uploads every list (job records, then the array of first tiles) into
@@ -474,7 +482,7 @@ void drop_graph(setd_batch* B) {
 
 // Work lists of one step for state buffer u with the current tile choice.
 int build_plan(setd_batch* B, double* u) {
-  PlanBuilder pb{B, B->cfg1, B->cfgB, {}, {}};
+  PlanBuilder pb{B, B->tiles, {}, {}};
   pb.step(u);
   drop_graph(B);
   SETD_TRY(pb.upload(B->list_mem, B->plan));
@@ -516,12 +524,16 @@ bool batch_use_graph() {
 }
 
 // ---- autotuner ----
-// Times the mode-product lists of the phi_1 group on F (the largest group of
-// the step; its outputs and intermediates are internal buffers, G stands in
-// for the added field) for each candidate tile shape and grid cap, per
-// regime, and keeps the fastest.
-const int kCand[4][2] = {{2, 2}, {2, 4}, {4, 2}, {4, 4}};
-const int kCaps[3] = {0, 2048, 8192};
+// Times the mode-product lists of the phi_1 group on F and of the phi_2 group
+// (outputs and intermediates are internal buffers, G stands in for the added
+// field) for each candidate tile {blocks of i, of the other index, waves}, per
+// regime, and keeps the fastest.  The two groups differ: with 16 instances the
+// phi_1 group is fastest with 2 x 4 tiles (82 us for mode 1), and a phi_2 group,
+// a third of its products, takes 36 us with 2 x 2 tiles of two waves where the
+// 2 x 4 tiles took 60.  Tiles whose waves split the contraction are what fills
+// the card for few instances: 3 of up to 96 x 96 take 13 us instead of 23 for
+// modes >= 2.  SETD_TILE_MODE1 / SETD_TILE_MODEB keep one candidate only.
+const int kCand[][3] = {{2, 2, 4}, {2, 2, 2}, {2, 2, 1}, {2, 4, 1}, {4, 2, 4}, {4, 2, 2}, {4, 2, 1}, {4, 4, 1}};
 
 int time_ops(setd_batch* B, const std::vector<Op>& ops, hipStream_t s, int reps, float& ms) {
   hipEvent_t e0, e1;
@@ -540,34 +552,35 @@ int time_ops(setd_batch* B, const std::vector<Op>& ops, hipStream_t s, int reps,
 }
 
 int tune(setd_batch* B, hipStream_t s) {
-  const bool was_prof = prof_on();
-  for (int regime = 0; regime < 2; ++regime) {
-    float best = 1e30f;
-    int bestc[3] = {0, 0, 0};
-    for (const auto& cand : kCand)
-      for (int cap : kCaps) {
-        int c1[3] = {B->cfg1[0], B->cfg1[1], B->cfg1[2]}, cb[3] = {B->cfgB[0], B->cfgB[1], B->cfgB[2]};
-        int* c = regime == 0 ? c1 : cb;
-        c[0] = cand[0];
-        c[1] = cand[1];
-        c[2] = cap;
-        PlanBuilder pb{B, c1, cb, {}, {}};
-        pb.group(pb.f_group(nullptr, B->G), regime == 0 ? 1 : 2);
+  for (int kind = 0; kind < 2; ++kind)
+    for (int regime = 0; regime < 2; ++regime) {
+      float best = 1e30f;
+      TileChoice bestt = B->tiles[kind];
+      int f[3];
+      const char* e = std::getenv(regime == 0 ? "SETD_TILE_MODE1" : "SETD_TILE_MODEB");
+      const bool forced = e && std::sscanf(e, "%dx%dx%d", f, f + 1, f + 2) == 3;
+      for (const auto& cand : kCand) {
+        if (forced && !std::equal(f, f + 3, cand)) continue;
+        TileChoice t[2] = {B->tiles[0], B->tiles[1]};
+        int* cc = regime == 0 ? t[kind].mode1 : t[kind].modeB;
+        cc[0] = cand[regime == 0 ? 0 : 1];
+        cc[1] = cand[regime == 0 ? 1 : 0];
+        cc[2] = 0;
+        cc[3] = cand[2];
+        PlanBuilder pb{B, t, {}, {}};
+        if (kind == 0) pb.group(pb.f_group(nullptr, B->G), kind, regime + 1);
+        else pb.group(pb.d_group(bank_index(SETD_STAGE_F, 2), 1.5 * B->tau, B->U2, B->G), kind, regime + 1);
         std::vector<Op> ops;
         SETD_TRY(pb.upload(B->tune_mem, ops));
         float ms = 0.0f;
         SETD_TRY(time_ops(B, ops, s, 3, ms));
         if (ms < best) {
           best = ms;
-          bestc[0] = c[0];
-          bestc[1] = c[1];
-          bestc[2] = c[2];
+          bestt = t[kind];
         }
       }
-    int* dst = regime == 0 ? B->cfg1 : B->cfgB;
-    for (int k = 0; k < 3; ++k) dst[k] = bestc[k];
-  }
-  (void)was_prof;
+      B->tiles[kind] = bestt;
+    }
   B->tuned = true;
   B->plan_u = nullptr;   // rebuild the plan with the new shapes
   drop_graph(B);
@@ -775,10 +788,8 @@ int setd_batch_set_tiles(setd_batch* B, const int* cfg) {
   SETD_CHECK_ARG(B != nullptr && cfg != nullptr, "batch and cfg must be non-NULL");
   SETD_CHECK_ARG(valid_tile(cfg[0], cfg[1]) && valid_tile(cfg[3], cfg[4]), "tiles must be 2 or 4 on each side");
   SETD_CHECK_ARG(cfg[2] >= 0 && cfg[5] >= 0, "grid caps must be >= 0");
-  for (int k = 0; k < 3; ++k) {
-    B->cfg1[k] = cfg[k];
-    B->cfgB[k] = cfg[3 + k];
-  }
+  for (TileChoice& t : B->tiles)
+    t = {{cfg[0], cfg[1], cfg[2], 1}, {cfg[3], cfg[4], cfg[5], 1}};
   B->tuned = true;
   B->plan_u = nullptr;
   drop_graph(B);
@@ -789,8 +800,8 @@ int setd_batch_info(const setd_batch* B, int64_t* info) {
   clear_error();
   SETD_CHECK_ARG(B != nullptr && info != nullptr, "batch and info must be non-NULL");
   for (int k = 0; k < 3; ++k) {
-    info[k] = B->cfg1[k];
-    info[3 + k] = B->cfgB[k];
+    info[k] = B->tiles[0].mode1[k];
+    info[3 + k] = B->tiles[0].modeB[k];
   }
   info[6] = B->tuned ? 1 : 0;
   info[7] = (int64_t)B->plan.size();

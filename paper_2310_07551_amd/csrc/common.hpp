@@ -192,7 +192,7 @@ struct ModeList {
   int njobs;
   int64_t total;         // tiles
   bool mode1;
-  int tm, tn;
+  int ti, to, ks;        // tile: 16 ti of i, 16 to of the other index, ks waves
   int64_t grid_cap;      // maximum number of waves (0: one per tile)
   double flops, bytes;   // algorithmic work, for the kernel timing
 };

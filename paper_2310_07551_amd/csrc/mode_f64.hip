@@ -339,17 +339,23 @@ __global__ void __launch_bounds__(256, 2) mode_f64_kernel(const ModeJobs J, int6
 // a list differ in length (they are sorted longest first), so an XCD takes
 // runs of kListRun workgroups in turn rather than one contiguous range.
 constexpr int kListRun = 8;
-template <bool M1, int TI, int TO>
+template <bool M1, int TI, int TO, int KS>
 __global__ void __launch_bounds__(256, 2) mode_f64_list_kernel(const ModeJob* __restrict__ jobs,
                                                                const int64_t* __restrict__ begins, int njobs,
                                                                int64_t total, int64_t ngroups) {
+  __shared__ d4 red[red_size(TI, TO, KS)];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   for (int64_t raw = blockIdx.x; raw < ngroups; raw += gridDim.x) {
     const int64_t run = raw / (8 * kListRun), in = raw % (8 * kListRun);
-    const int64_t t = (run * 8 * kListRun + (in & 7) * kListRun + (in >> 3)) * 4 + wave;
-    if (t >= total) continue;
-    const int j = find_job_list(begins, njobs, t);
-    mode_tile<M1, false, TI, TO, ring_depth(TI, TO), 1, uint32_t>(jobs[j], (uint32_t)(t - begins[j]), lane, 0, nullptr);
+    const int64_t t = (run * 8 * kListRun + (in & 7) * kListRun + (in >> 3)) * (4 / KS) + wave / KS;
+    if (t < total) {
+      const int j = find_job_list(begins, njobs, t);
+      mode_tile<M1, false, TI, TO, ring_depth(TI, TO), KS, uint32_t>(jobs[j], (uint32_t)(t - begins[j]), lane, wave % KS,
+                                                                     red + (wave / KS) * KS * TI * TO * 64);
+    } else if (KS > 1) {
+      __syncthreads();   // the barrier of the waves with a tile
+    }
+    if constexpr (KS > 1) __syncthreads();   // the parts have been read
   }
 }
 
@@ -1020,33 +1026,43 @@ int launch_slab_f64(SlabJobs& J, hipStream_t s, bool raw) {
   return sum ? launch_slab_ni<false, true>(J, s) : launch_slab_ni<false, false>(J, s);
 }
 
-#define SETD_LAUNCH_LIST(TM_, TN_)                                                             \
-  if (L.tm == TM_ && L.tn == TN_) {                                                           \
-    if (L.mode1)                                                                              \
-      hipLaunchKernelGGL((mode_f64_list_kernel<true, TM_, TN_>), grid, dim3(256), 0, s, L.jobs, L.begins, L.njobs, \
-                         L.total, groups);                                                    \
-    else                                                                                      \
-      hipLaunchKernelGGL((mode_f64_list_kernel<false, TN_, TM_>), grid, dim3(256), 0, s, L.jobs, L.begins, L.njobs, \
-                         L.total, groups);                                                    \
-    SETD_LAUNCHED();                                                                          \
-    return SETD_OK;                                                                           \
-  }
+namespace {
+template <int TI, int TO, int KS>
+void launch_list_tile(const ModeList& L, dim3 grid, int64_t groups, hipStream_t s) {
+  if (L.mode1)
+    hipLaunchKernelGGL((mode_f64_list_kernel<true, TI, TO, KS>), grid, dim3(256), 0, s, L.jobs, L.begins, L.njobs,
+                       L.total, groups);
+  else
+    hipLaunchKernelGGL((mode_f64_list_kernel<false, TI, TO, KS>), grid, dim3(256), 0, s, L.jobs, L.begins, L.njobs,
+                       L.total, groups);
+}
+}  // namespace
 
 int launch_list_f64(const ModeList& L, hipStream_t s) {
   if (L.total == 0) return SETD_OK;
-  const int64_t groups = round_up(ceil_div(L.total, 4), 8 * kListRun);
+  const int64_t groups = round_up(ceil_div(L.total, 4 / L.ks), 8 * kListRun);
   // a multiple of 8 blocks, so that block b stays on XCD b % 8 through the
-  // whole loop; at most `grid_cap` waves (0: one wave per tile)
+  // whole loop; at most `grid_cap` waves (0: all)
   int64_t nblk = groups;
   if (L.grid_cap > 0 && nblk * 4 > L.grid_cap) nblk = round_up(ceil_div(L.grid_cap, 4), 8);
   const dim3 grid((unsigned)nblk);
   ProfScope prof(s, L.mode1 ? kProfMode1F64 : kProfModeBF64, L.flops, L.bytes);
-  SETD_LAUNCH_LIST(2, 2)
-  SETD_LAUNCH_LIST(2, 4)
-  SETD_LAUNCH_LIST(4, 2)
-  SETD_LAUNCH_LIST(4, 4)
-  set_error("unsupported tile %dx%d", L.tm, L.tn);
-  return SETD_EUNSUPPORTED;
+  const int key = 100 * L.ti + 10 * L.to + L.ks;
+  switch (key) {
+    case 224: launch_list_tile<2, 2, 4>(L, grid, groups, s); break;
+    case 222: launch_list_tile<2, 2, 2>(L, grid, groups, s); break;
+    case 221: launch_list_tile<2, 2, 1>(L, grid, groups, s); break;
+    case 241: launch_list_tile<2, 4, 1>(L, grid, groups, s); break;
+    case 424: launch_list_tile<4, 2, 4>(L, grid, groups, s); break;
+    case 422: launch_list_tile<4, 2, 2>(L, grid, groups, s); break;
+    case 421: launch_list_tile<4, 2, 1>(L, grid, groups, s); break;
+    case 441: launch_list_tile<4, 4, 1>(L, grid, groups, s); break;
+    default:
+      set_error("unsupported tile %dx%dx%d", L.ti, L.to, L.ks);
+      return SETD_EUNSUPPORTED;
+  }
+  SETD_LAUNCHED();
+  return SETD_OK;
 }
 
 }  // namespace setd

@@ -84,3 +84,28 @@ def test_nonfinite_stays_in_its_fibre(tile, monkeypatch):
         at[mu] = slice(None)
         bad[tuple(at)] = True
         assert np.array_equal(np.isnan(host(W, dims)), bad), (tile, mu)
+
+
+@pytest.mark.parametrize("tile", ["2x2x4", "2x2x2", "2x2x1", "2x4x1", "4x2x4", "4x2x2", "4x2x1", "4x4x1"])
+def test_every_tile_of_the_batch(tile, monkeypatch):
+    """The tiles that the batched integrator tries, whose waves may split the
+    contraction, over instances of unequal size (the last round of a workgroup
+    has waves without a tile), in two and three dimensions.  Tolerance: the
+    batched integrator's 1e-12 of the largest value."""
+    monkeypatch.setenv("SETD_TILE_MODE1", tile)
+    monkeypatch.setenv("SETD_TILE_MODEB", tile)
+    for probs in ([wl.schnakenberg_2d(n1, n2, instance=q, tau=1e-3)
+                   for q, (n1, n2) in enumerate([(16, 24), (7, 9), (33, 47), (128, 50), (2, 65)])],
+                  [wl.fhn_3d(dims=dims) for dims in [(5, 18, 9), (33, 16, 17)]]):
+        B = setd.Batch([p.dims for p in probs], [[[dev(M) for M in Ac] for Ac in p.A] for p in probs], probs[0].tau)
+        info = B.tune()
+        say("batch tile", tile, info)
+        u = torch().zeros(B.total, dtype=torch().float64, device="cuda")
+        for q, p in enumerate(probs):
+            for c in range(2):
+                B.field(u, q, c).copy_(dev(p.U0[c]))
+        B.step(u, 3, probs[0].g_kind, [p.params for p in probs])
+        for q, p in enumerate(probs):
+            ref = oracle.integrate(p.U0, p.A, p.tau, 3, p.g_kind, p.params)
+            for c in range(2):
+                assert rel_err(host(B.field(u, q, c), p.dims), ref[c]) < 1e-12, (p.dims, c)
