@@ -554,7 +554,9 @@ __global__ void __launch_bounds__(SUM ? 256 * kSlabTerms : 256, 2) slab_f64_kern
 // in LDS in the order the MFMA reads it (chunk of 16 p, row m, lane: 4 p),
 // so no wave holds P in registers; each wave then computes `reps` 64 x 64
 // tiles of the workgroup's column group (8 * reps column tiles), reading X
-// in 32-byte runs per lane (whole cache lines) through a two-deep ring.
+// in 32-byte runs per lane (whole cache lines) through a two-deep ring that
+// runs on from one tile into the next (FHN 256^3, 18 jobs: 2.31 ms when each
+// tile started its own, 2.29 now; bound by the matrix cores, 67.5 TFLOP/s).
 // Workgroup w of a job: panel w % tiles_i, column group w / tiles_i.
 constexpr int kLdsWaves = 8;
 constexpr int kLdsMinN = 192, kLdsMaxN = 256;
@@ -587,74 +589,72 @@ __global__ void __launch_bounds__(512, 1) mode1_lds_kernel(const ModeJobs J, int
     panel[q] = d4{lo[0], lo[1], hi[0], hi[1]};
   }
   __syncthreads();
-  const int wave = threadIdx.x >> 6;
-  for (int rep = 0; rep < reps; ++rep) {
-  const int64_t bt = (bg * reps + rep) * kLdsWaves + wave;
-  if (bt >= jb.tiles_a) return;
-  const int lane = threadIdx.x & 63, g = lane >> 4, l = lane & 15;
-  const int64_t b0 = bt * 64;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4, l = lane & 15;
   const double* __restrict__ X = (const double*)jb.X[0];
-  const double* pb[4];
+  // b-block of repetition r (past the job's blocks: not run), and the lane's
+  // first X element of it
+  auto block_of = [&](int r) { return (bg * reps + r) * kLdsWaves + wave; };
+  auto xbase = [&](int64_t bt) { return X + (bt * 64 + l) * (int64_t)n + 4 * g; };
+  auto load = [&](const double* xb, d4* xr) {
 #pragma unroll
-  for (int u = 0; u < 4; ++u) pb[u] = X + (b0 + 16 * u + l) * (int64_t)n + 4 * g;
-  d4 acc[4][4];
-#pragma unroll
-  for (int m = 0; m < 4; ++m)
-#pragma unroll
-    for (int u = 0; u < 4; ++u) acc[m][u] = d4{0.0, 0.0, 0.0, 0.0};
-  auto load = [&](int c, d4* xr) {
-#pragma unroll
-    for (int u = 0; u < 4; ++u) xr[u] = *(const d4*)(pb[u] + 16 * c);
+    for (int u = 0; u < 4; ++u) xr[u] = *(const d4*)(xb + 16 * u * (int64_t)n);
   };
-  auto mma = [&](int c, const d4* xr) {
-    d4 a[4];
-#pragma unroll
-    for (int m = 0; m < 4; ++m) a[m] = panel[(c * 4 + m) * 64 + lane];
-#pragma unroll
-    for (int jj = 0; jj < 4; ++jj)
-#pragma unroll
-      for (int m = 0; m < 4; ++m)
-#pragma unroll
-        for (int u = 0; u < 4; ++u) acc[m][u] = mfma(a[m][jj], xr[u][jj], acc[m][u]);
-  };
+  if (block_of(0) >= jb.tiles_a) return;   // no barrier follows
+  const double* xb = xbase(block_of(0));
   d4 x0[4], x1[4];
-  load(0, x0);
-  for (int c = 0; c < nchunk; c += 2) {
-    load(c + 1, x1);                                 // nchunk is even (n % 32 == 0)
-    mma(c, x0);
-    load(c + 2 < nchunk ? c + 2 : c, x0);
-    mma(c + 1, x1);
-  }
-  // epilogue as in mode1_tile: lane (g, l) owns rows i0 + 4 g + 16 r + (0..3)
-  // of column b0 + 16 u + l
-  const double sc = jb.scale[0];
-  double* __restrict__ Y = (double*)jb.Y;
-  const double* __restrict__ base = (const double*)jb.base;
+  load(xb, x0);
+  for (int rep = 0; rep < reps; ++rep) {
+    const int64_t b0 = block_of(rep) * 64;
+    // the next block's first chunk is loaded during this block's last one
+    const bool next = rep + 1 < reps && block_of(rep + 1) < jb.tiles_a;
+    const double* xn = next ? xbase(block_of(rep + 1)) : xb;
+    __builtin_amdgcn_s_setprio(1);   // products ahead of another wave's epilogue on the SIMD
+    d4 acc[4][4];
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int64_t col = (b0 + 16 * u + l) * (int64_t)n;
+    for (int m = 0; m < 4; ++m)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int ir = i0 + 4 * g + 16 * r;
-      if (ir + 4 <= n) {
+      for (int u = 0; u < 4; ++u) acc[m][u] = d4{0.0, 0.0, 0.0, 0.0};
+    auto mma = [&](int c, const d4* xr) {
+      d4 a[4];
 #pragma unroll
-        for (int m = 0; m < 4; m += 2) {
-          d2 v = d2{acc[m][u][r], acc[m + 1][u][r]} * sc;
-          if (base) v += *(const d2*)(base + col + ir + m);
-          *(d2*)(Y + col + ir + m) = v;
-        }
-      } else {
+      for (int m = 0; m < 4; ++m) a[m] = panel[(c * 4 + m) * 64 + lane];
 #pragma unroll
-        for (int m = 0; m < 4; ++m) {
-          if (ir + m < n) {
-            double v = acc[m][u][r] * sc;
-            if (base) v += base[col + ir + m];
-            Y[col + ir + m] = v;
+      for (int jj = 0; jj < 4; ++jj)
+#pragma unroll
+        for (int m = 0; m < 4; ++m)
+#pragma unroll
+          for (int u = 0; u < 4; ++u) acc[m][u] = mfma(a[m][jj], xr[u][jj], acc[m][u]);
+    };
+    for (int c = 0; c < nchunk; c += 2) {   // nchunk is even (n % 32 == 0)
+      load(xb + 16 * (c + 1), x1);
+      mma(c, x0);
+      load(c + 2 < nchunk ? xb + 16 * (c + 2) : xn, x0);   // unconditional: no branch
+      mma(c + 1, x1);
+    }
+    __builtin_amdgcn_s_setprio(0);
+    // epilogue: lane (g, l) owns rows i0 + 4 g + 16 r + (0..3) of column
+    // b0 + 16 u + l
+    const double sc = jb.scale[0];
+    double* __restrict__ Y = (double*)jb.Y;
+    const double* __restrict__ base = (const double*)jb.base;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int64_t col = (b0 + 16 * u + l) * (int64_t)n;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int ir = i0 + 4 * g + 16 * r;
+        if (ir < n) {   // n % 32 == 0: all four or none
+#pragma unroll
+          for (int m = 0; m < 4; m += 2) {
+            d2 v = d2{acc[m][u][r], acc[m + 1][u][r]} * sc;
+            if (base) v += *(const d2*)(base + col + ir + m);
+            *(d2*)(Y + col + ir + m) = v;
           }
         }
       }
     }
-  }
+    if (!next) return;
+    xb = xn;
   }
 }
 
