@@ -217,7 +217,7 @@ struct PackJob {
   double* out;
 };
 int pack_matrices_f64(const PackJob* jobs, int count, int n, hipStream_t s);
-int pack_matrix_f32(const double* M, int n, double scale, bool rowmajor, float* out, hipStream_t s);
+int pack_matrix_f32(const double* M, int n, double scale, bool mode1, float* out, hipStream_t s);
 int pack_matrix_bf16(const double* M, int n, double scale, bool rowmajor, int np, void* out, hipStream_t s);
 inline bool is_prec(int p) {
   return p == SETD_PREC_F64 || p == SETD_PREC_F32 || p == SETD_PREC_BF16X3 || p == SETD_PREC_BF16X2 ||

@@ -29,6 +29,8 @@
 
 #include "common.hpp"
 
+#include <algorithm>
+#include <cstdio>
 #include <cstdlib>
 
 namespace setd {
@@ -118,246 +120,231 @@ __device__ __forceinline__ void store_run(TOut* __restrict__ Y, const double* __
 }
 
 // ---------------------------------------------------------------------------
-// FP32 with the accumulation chained on the matrix cores (the layout and
-// load scheme of the FP64 kernels: lanes load 4 consecutive p, an interior
-// variant without masks in ping-pong registers).  FP32 MFMA accumulator
-// layout (probed): lane (g, l) register r holds D[4 g + r][l].
+// FP32 with the accumulation chained on the matrix cores
 // ---------------------------------------------------------------------------
+// One wave computes 16 TI values of i by 16 TO of the other index, four waves
+// per workgroup on neighbouring tiles; modes >= 2 tile a and b together as in
+// the FP64 kernels.  MFMA rows = i (matrix), columns = the other index: lane
+// (g, l) register r of the accumulator holds D[4 g + r][l].
+//
+// Packed FP32 matrix: entry (tile t, chunk c, lane, j) = M[16 t + l][p], zero
+// past n, p = 16 c + 4 g + j in mode 1 (whose lanes read four consecutive p of
+// X) and p = 16 c + 4 j + g in modes >= 2 (whose MFMA takes four consecutive
+// p): the order of every sum, and with it every bit of the result, depends on
+// the mode and n alone, not on the tile.
+//
+// Every size takes the same loop: columns and rows past the end are clamped to
+// the last one (their results are not stored), and the last n % 16 values of p
+// are one chunk, masked, loaded ahead of the loop (loading it in the ring
+// instead needs copies of the loop body, in which the compiler moves the
+// accumulators about: 200^3 3.65 -> 4.2 ms).  In modes >= 2 the TO columns of
+// a lane are neighbours (V), one load for all of them, wherever no slab ends
+// between them; one load each was what bound the large sizes (256^3 last mode
+// 1.78 -> 1.42 ms).  Whole steps against kernels of one 4 x 4 tile that
+// checked every load unless n was a multiple of 32: 200^3 4.83 -> 3.65 ms,
+// 150^3 2.74 -> 1.37, 256^3 8.02 -> 7.5, 100^3 0.52 -> 0.38, 300^2 0.40 -> 0.10.
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));   // four floats at any address
+
 __device__ __forceinline__ f4 mfma32(float a, float b, f4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
-template <int TM, int TN, int MODE, typename TOut>
-__global__ void __launch_bounds__(64, 2) mode1_f32c_kernel(const ModeJobs J, int64_t per_xcd) {
-  constexpr bool VEC = MODE >= 1;
-  const int64_t t = remap_xcd_lp(blockIdx.x, per_xcd);
-  if (t >= J.total_tiles) return;
+template <bool M1, bool V, int TI, int TO, typename Off, typename TOut>
+__global__ void __launch_bounds__(256, 2) mode_f32_kernel(const ModeJobs J, int64_t per_xcd) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const uint32_t t = (uint32_t)remap_xcd_lp(blockIdx.x, per_xcd) * 4 + wave;
+  if (t >= (uint32_t)J.total_tiles) return;
   const ModeJob& jb = J.job[find_job_lp(J, t)];
-  const int64_t lt = t - jb.tile_begin;
-  const int it = (int)(lt % jb.tiles_i);
-  const int64_t bt = lt / jb.tiles_i;
-  const int lane = threadIdx.x, g = lane >> 4, l = lane & 15;
-  const int n = jb.n, ldp = jb.ldp;
-  const int64_t nb = jb.nb;
-  const int i0 = it * 16 * TM;
-  const int64_t b0 = bt * 16 * TN;
-  const float* __restrict__ X = (const float*)jb.X[0];
-  const float* __restrict__ PT = (const float*)jb.P[0];
-  const float sc = (float)jb.scale[0];
-  const float* pa[TM];
-#pragma unroll
-  for (int m = 0; m < TM; ++m) pa[m] = PT + (int64_t)(i0 + TM * l + m) * ldp + 4 * g;
-  const float* pb[TN];
-  bool vb[TN];
-#pragma unroll
-  for (int u = 0; u < TN; ++u) {
-    const int64_t b = b0 + 16 * u + l;
-    vb[u] = b < nb;
-    pb[u] = X + (vb[u] ? b : 0) * (int64_t)n + 4 * g;
-  }
-  f4 acc[TM][TN];
-#pragma unroll
-  for (int m = 0; m < TM; ++m)
-#pragma unroll
-    for (int u = 0; u < TN; ++u) acc[m][u] = f4{0.f, 0.f, 0.f, 0.f};
-  auto mma = [&](const f4* ar, const f4* br) {
-#pragma unroll
-    for (int jj = 0; jj < 4; ++jj)
-#pragma unroll
-      for (int m = 0; m < TM; ++m)
-#pragma unroll
-        for (int u = 0; u < TN; ++u) acc[m][u] = mfma32(ar[m][jj], br[u][jj], acc[m][u]);
+  const uint32_t lt = t - (uint32_t)jb.tile_begin;
+  const int g = lane >> 4, l = lane & 15;
+  const int n = jb.n, nch = (n + 15) >> 4, nfull = n >> 4;
+  const uint32_t ti = (uint32_t)jb.tiles_i;
+  const uint32_t ot = lt / ti;
+  const int t0 = (int)(lt - ot * ti) * TI;
+  const int64_t na = M1 ? 1 : jb.na;
+  const int64_t ext = M1 ? jb.nb : na * jb.nb;
+  const int64_t q0 = (int64_t)ot * (16 * TO);
+  const uint32_t b0 = M1 || jb.nb == 1 ? 0 : (uint32_t)((uint64_t)q0 / (uint32_t)na);
+  const int64_t r0 = q0 - (int64_t)b0 * na;   // a of the tile's first column
+  const int64_t origin = M1 ? q0 * n : (int64_t)b0 * na * n + r0;
+  // element offset of column k of the tile (clamped to the extent) from its first
+  auto column = [&](int k) -> Off {
+    const int64_t rel = min(q0 + k, ext - 1) - q0;
+    if (M1) return (Off)(rel * n);
+    if (jb.nb == 1) return (Off)rel;
+    const Off q = (Off)(r0 + rel);
+    const Off bb = q / (Off)na;
+    return (Off)(bb * (Off)(na * n) + (q - bb * (Off)na) - (Off)r0);
   };
-  if constexpr (MODE == 2) {
-    auto load = [&](int p0, f4* ar, f4* br) {
+  // columns of the lane: 16 o + l, or with V the TO consecutive ones from
+  // TO l on (the last lanes move back to end with the last column; they keep
+  // the first `skip` of theirs to themselves)
+  constexpr int NX = V ? 1 : TO;
+  // the moved lanes of a tile with fewer than TO columns begin before it, so
+  // that with V offsets count from TO elements before the tile's first
+  constexpr int kBack = V ? TO : 0;
+  typedef float fv __attribute__((ext_vector_type(TO), aligned(4)));
+  const int k0 = V ? (int)(min(q0 + TO * l, ext - TO) - q0) : 0, skip = TO * l - k0;
+  Off xo[NX];   // byte offset of the lane's first element of each column block
 #pragma unroll
-      for (int m = 0; m < TM; ++m) ar[m] = *(const f4*)(pa[m] + p0);
+  for (int o = 0; o < NX; ++o) xo[o] = (column(V ? k0 : 16 * o + l) + (Off)kBack + (M1 ? (Off)(4 * g) : (Off)na * (Off)g)) * 4;
+  f4 acc[TI][TO];
 #pragma unroll
-      for (int u = 0; u < TN; ++u) br[u] = *(const f4*)(pb[u] + p0);
+  for (int i = 0; i < TI; ++i)
+#pragma unroll
+    for (int o = 0; o < TO; ++o) acc[i][o] = f4{0.f, 0.f, 0.f, 0.f};
+  __builtin_amdgcn_s_setprio(1);   // products ahead of another wave's epilogue on the SIMD
+  const int nterms = M1 ? 1 : jb.nterms;
+  const int nt = nch;              // tiles of i
+  for (int term = 0; term < nterms; ++term) {
+    const float* __restrict__ x0 = (const float*)jb.X[term] + (origin - kBack);
+    const float sc = (float)jb.scale[term];
+    const float* at[TI];
+#pragma unroll
+    for (int i = 0; i < TI; ++i)
+      at[i] = (const float*)jb.P[term] + (int64_t)min(t0 + i, nt - 1) * nch * 256 + 4 * lane;
+    auto load_m = [&](int c, f4 (&pr)[TI]) {
+#pragma unroll
+      for (int i = 0; i < TI; ++i) pr[i] = *(const f4*)(at[i] + (int64_t)c * 256);
     };
-    f4 a0[TM], b0r[TN], a1[TM], b1r[TN];
-    load(0, a0, b0r);
-    for (int p0 = 0; p0 < n; p0 += 32) {
-      load(p0 + 16, a1, b1r);
-      mma(a0, b0r);
-      load(p0 + 32 < n ? p0 + 32 : p0, a0, b0r);
-      mma(a1, b1r);
+    auto load = [&](int c, f4 (&xr)[TO], f4 (&pr)[TI]) {
+      load_m(c, pr);
+      if constexpr (M1) {
+        const char* xb = (const char*)(x0 + 16 * c);
+#pragma unroll
+        for (int o = 0; o < TO; ++o) xr[o] = *(const f4u*)(xb + xo[o]);
+      } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const char* xb = (const char*)(x0 + na * (16 * (int64_t)c + 4 * j));
+          if constexpr (V) {
+            const fv v = *(const fv*)(xb + xo[0]);
+#pragma unroll
+            for (int o = 0; o < TO; ++o) xr[o][j] = v[o];
+          } else {
+#pragma unroll
+            for (int o = 0; o < TO; ++o) xr[o][j] = *(const float*)(xb + xo[o]);
+          }
+        }
+      }
+    };
+    // the term's scale goes on the matrix in modes >= 2 and on the sum in mode 1
+    auto mma = [&](const f4 (&xr)[TO], const f4 (&pr)[TI]) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int i = 0; i < TI; ++i) {
+          const float pv = M1 ? pr[i][j] : pr[i][j] * sc;
+#pragma unroll
+          for (int o = 0; o < TO; ++o) acc[i][o] = mfma32(pv, xr[o][j], acc[i][o]);
+        }
+    };
+    f4 xr[2][TO], pr[2][TI], xt[TO], pt[TI];
+    const bool tail = nch > nfull;
+    if (nfull > 0) load(0, xr[0], pr[0]);
+    if (tail) {
+      load_m(nfull, pt);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int k = M1 ? 4 * g + j : 4 * j + g, p = 16 * nfull + k;
+        const float* xp = x0 + (M1 ? 1 : na) * (min(p, n - 1) - (M1 ? 4 * g : g));   // xo holds the lane's part
+#pragma unroll
+        for (int o = 0; o < TO; ++o) {
+          const float v = *(const float*)((const char*)(V ? xp + o : xp) + xo[V ? 0 : o]);
+          xt[o][j] = p < n ? v : 0.f;
+        }
+      }
+    }
+    int c = 0;
+    for (; c + 2 <= nfull; c += 2) {
+      load(c + 1, xr[1], pr[1]);
+      mma(xr[0], pr[0]);
+      load(min(c + 2, nfull - 1), xr[0], pr[0]);   // the last one re-reads a valid chunk: no branch
+      mma(xr[1], pr[1]);
+    }
+    if (c < nfull) mma(xr[0], pr[0]);
+    if (tail) mma(xt, pt);
+  }
+  __builtin_amdgcn_s_setprio(0);
+  const float sc1 = M1 ? (float)jb.scale[0] : 1.f;
+  const int imax = n - 16 * t0;                               // i of the tile below it
+  const int omax = (int)min(ext - q0, (int64_t)(16 * TO));    // columns of the tile
+  const double* __restrict__ base = (const double*)jb.base;
+  if constexpr (M1) {
+    TOut* __restrict__ Y = (TOut*)jb.Y + origin + 16 * t0;
+    const double* __restrict__ bs = base + origin + 16 * t0;
+#pragma unroll
+    for (int o = 0; o < TO; ++o) {
+      if (16 * o + l >= omax) continue;
+#pragma unroll
+      for (int i = 0; i < TI; ++i) {
+        const int i0 = 16 * i + 4 * g;
+        const int64_t at = (int64_t)(16 * o + l) * n + i0;
+        const f4 v = sc1 * acc[i][o];
+        if constexpr (sizeof(TOut) == 4) {
+          if (i0 + 4 <= imax) {
+            *(f4u*)(Y + at) = v;
+            continue;
+          }
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (i0 + r < imax) Y[at + r] = sizeof(TOut) == 8 && base ? (TOut)((double)v[r] + bs[at + r]) : (TOut)v[r];
+      }
     }
   } else {
-    auto load = [&](int p0, f4* ar, f4* br) {
+    TOut* __restrict__ Y = (TOut*)jb.Y + (origin - kBack) + na * 16 * t0;
+    const double* __restrict__ bs = base + (origin - kBack) + na * 16 * t0;
+    Off yo[NX];
 #pragma unroll
-      for (int m = 0; m < TM; ++m) ar[m] = *(const f4*)(pa[m] + p0);
-      const bool full = VEC && (p0 + 16 <= n);
+    for (int o = 0; o < NX; ++o) yo[o] = column(V ? k0 : 16 * o + l) + (Off)kBack;
 #pragma unroll
-      for (int u = 0; u < TN; ++u) {
-        if (full) {
-          br[u] = vb[u] ? *(const f4*)(pb[u] + p0) : f4{0.f, 0.f, 0.f, 0.f};
-        } else {
+    for (int i = 0; i < TI; ++i) {
+      // the base values of a block of rows are read together, from clamped
+      // indices, so that they are one wait and not one each
+      double bv[4][TO];
+      if (sizeof(TOut) == 8 && base) {
 #pragma unroll
-          for (int e = 0; e < 4; ++e) br[u][e] = (vb[u] && p0 + 4 * g + e < n) ? pb[u][p0 + e] : 0.f;
-        }
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int o = 0; o < TO; ++o)
+            bv[r][o] = bs[min(16 * i + 4 * g + r, imax - 1) * na + yo[V ? 0 : o] + (V ? o : 0)];
+      } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int o = 0; o < TO; ++o) bv[r][o] = -0.0;   // the sum is then the product itself
       }
-    };
-    f4 a[TM], bx[TN];
-    load(0, a, bx);
-    for (int p0 = 0; p0 < n; p0 += 16) {
-      f4 an[TM], bn[TN];
-      const bool more = p0 + 16 < n;
-      if (more) load(p0 + 16, an, bn);
-      mma(a, bx);
-      if (more) {
 #pragma unroll
-        for (int m = 0; m < TM; ++m) a[m] = an[m];
+      for (int r = 0; r < 4; ++r) {
+        const int row = 16 * i + 4 * g + r;
+        if (row >= imax) continue;
+        TOut w[TO];
 #pragma unroll
-        for (int u = 0; u < TN; ++u) bx[u] = bn[u];
-      }
-    }
-  }
-  // lane (g, l) owns the 4 TM consecutive rows i0 + 4 TM g + (TM r + m) of
-  // column b0 + 16 u + l
-  TOut* __restrict__ Y = (TOut*)jb.Y;
-  const double* __restrict__ base = (const double*)jb.base;
-  const int ir = i0 + 4 * TM * g;
-#pragma unroll
-  for (int u = 0; u < TN; ++u) {
-    if (!vb[u]) continue;
-    float v[4 * TM];
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-#pragma unroll
-      for (int m = 0; m < TM; ++m) v[TM * r + m] = sc * acc[m][u][r];
-    store_run<TOut>(Y, base, (b0 + 16 * u + l) * (int64_t)n + ir, v, 4 * TM, n - ir, VEC);
-  }
-}
-
-template <int TM, int TN, int MODE, typename TOut>
-__global__ void __launch_bounds__(64, 2) modeB_f32c_kernel(const ModeJobs J, int64_t per_xcd) {
-  constexpr bool VEC = MODE >= 1;
-  const int64_t t = remap_xcd_lp(blockIdx.x, per_xcd);
-  if (t >= J.total_tiles) return;
-  const ModeJob& jb = J.job[find_job_lp(J, t)];
-  const int64_t lt = t - jb.tile_begin;
-  const int it = (int)(lt % jb.tiles_i);
-  const int64_t rest = lt / jb.tiles_i;
-  const int64_t at = rest % jb.tiles_a;
-  const int64_t b = rest / jb.tiles_a;
-  const int lane = threadIdx.x, g = lane >> 4, l = lane & 15;
-  const int n = jb.n, ldp = jb.ldp, nterms = jb.nterms;
-  const int64_t na = jb.na;
-  const int64_t a0 = at * 16 * TM;
-  const int i0 = it * 16 * TN;
-  const int64_t arow = a0 + TM * l;
-  const bool lane_full = arow + TM <= na;
-  f4 acc[TM][TN];
-#pragma unroll
-  for (int m = 0; m < TM; ++m)
-#pragma unroll
-    for (int u = 0; u < TN; ++u) acc[m][u] = f4{0.f, 0.f, 0.f, 0.f};
-  const int64_t slab = na * (int64_t)n * b;
-  for (int term = 0; term < nterms; ++term) {
-    const float* __restrict__ xb = (const float*)jb.X[term] + slab + arow + na * g;
-    const float* __restrict__ pbp = (const float*)jb.P[term] + i0 + TN * l + (int64_t)ldp * g;
-    const float sc = (float)jb.scale[term];
-    // k-steps per register block: 2 (at 3D FHN 256^3 97.4 TFLOP/s against 95.3 for 4 and 96.5 for 8)
-    constexpr int KB = 2;
-    auto mmablk = [&](float (*xr)[TM], float (*pr)[TN]) {
-#pragma unroll
-      for (int k = 0; k < KB; ++k)
-#pragma unroll
-        for (int u = 0; u < TN; ++u) {
-          const float pv = pr[k][u] * sc;
-#pragma unroll
-          for (int m = 0; m < TM; ++m) acc[m][u] = mfma32(xr[k][m], pv, acc[m][u]);
+        for (int o = 0; o < TO; ++o) {
+          const float v = acc[i][o][r];
+          w[o] = sizeof(TOut) == 8 ? (TOut)((double)v + bv[r][o]) : (TOut)v;
         }
-    };
-    auto loadblk = [&](int p0, float (*xr)[TM], float (*pr)[TN]) {
+        if constexpr (V) {
+          typedef TOut tv __attribute__((ext_vector_type(TO), aligned(sizeof(TOut))));
+          TOut* y = Y + row * na + yo[0];
+          if (skip == 0) {
+            tv x;
 #pragma unroll
-      for (int k = 0; k < KB; ++k) {
-        const int p = p0 + 4 * k;
-        const float* xs = xb + na * (int64_t)p;
-        const float* ps = pbp + (int64_t)ldp * p;   // padded: always in range
-        if constexpr (MODE == 2) {
-          if constexpr (TM == 4) {
-            const f4 v = *(const f4*)xs;
-#pragma unroll
-            for (int m = 0; m < TM; ++m) xr[k][m] = v[m];
-          } else {
-            const f2 v = *(const f2*)xs;
-#pragma unroll
-            for (int m = 0; m < TM; ++m) xr[k][m] = v[m];
-          }
-        } else {
-          const bool vp = p + g < n;
-          if (VEC && TM == 4 && lane_full && vp) {
-            const f4 v = *(const f4*)xs;
-#pragma unroll
-            for (int m = 0; m < TM; ++m) xr[k][m] = v[m];
-          } else if (VEC && TM == 2 && (MODE == 2 || (lane_full && vp))) {
-            const f2 v = *(const f2*)xs;
-#pragma unroll
-            for (int m = 0; m < TM; ++m) xr[k][m] = v[m];
+            for (int o = 0; o < TO; ++o) x[o] = w[o];
+            *(tv*)y = x;
           } else {
 #pragma unroll
-            for (int m = 0; m < TM; ++m) xr[k][m] = (vp && arow + m < na) ? xs[m] : 0.f;
+            for (int o = 0; o < TO; ++o)
+              if (o >= skip) y[o] = w[o];
           }
-        }
-        if constexpr (TN == 2) {
-          const f2 w = *(const f2*)ps;
-          pr[k][0] = w[0];
-          pr[k][1] = w[1];
-        } else if constexpr (TN == 4) {
-          const f4 w = *(const f4*)ps;
-#pragma unroll
-          for (int u = 0; u < TN; ++u) pr[k][u] = w[u];
         } else {
 #pragma unroll
-          for (int u = 0; u < TN; ++u) pr[k][u] = ps[u];
-        }
-      }
-    };
-    if constexpr (MODE == 2) {
-      float x0[KB][TM], q0[KB][TN], x1[KB][TM], q1[KB][TN];
-      loadblk(0, x0, q0);
-      for (int p0 = 0; p0 < n; p0 += 8 * KB) {
-        loadblk(p0 + 4 * KB, x1, q1);
-        mmablk(x0, q0);
-        loadblk(p0 + 8 * KB < n ? p0 + 8 * KB : p0, x0, q0);
-        mmablk(x1, q1);
-      }
-    } else {
-      float xr[KB][TM], pr[KB][TN];
-      loadblk(0, xr, pr);
-      for (int p0 = 0; p0 < n; p0 += 4 * KB) {
-        float xn[KB][TM], pn[KB][TN];
-        const bool more = p0 + 4 * KB < n;
-        if (more) loadblk(p0 + 4 * KB, xn, pn);
-        mmablk(xr, pr);
-        if (more) {
-#pragma unroll
-          for (int k = 0; k < KB; ++k) {
-#pragma unroll
-            for (int m = 0; m < TM; ++m) xr[k][m] = xn[k][m];
-#pragma unroll
-            for (int u = 0; u < TN; ++u) pr[k][u] = pn[k][u];
-          }
+          for (int o = 0; o < TO; ++o)
+            if (16 * o + l < omax) Y[row * na + yo[o]] = w[o];
         }
       }
     }
-  }
-  TOut* __restrict__ Y = (TOut*)jb.Y;
-  const double* __restrict__ base = (const double*)jb.base;
-  const int64_t ar = a0 + 4 * TM * g;
-#pragma unroll
-  for (int u = 0; u < TN; ++u) {
-    const int i = i0 + TN * l + u;
-    if (i >= n) continue;
-    float v[4 * TM];
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-#pragma unroll
-      for (int m = 0; m < TM; ++m) v[TM * r + m] = acc[m][u][r];
-    store_run<TOut>(Y, base, slab + na * (int64_t)i + ar, v, 4 * TM, (int)(na - ar < 4 * TM ? na - ar : 4 * TM),
-                    VEC);
   }
 }
 
@@ -385,14 +372,15 @@ __global__ void __launch_bounds__(512, 1) mode1_lds32_kernel(const ModeJobs J, i
   const int64_t lw = w - jb.tile_begin;
   const int it = (int)(lw % jb.tiles_i);
   const int64_t bg = lw / jb.tiles_i;
-  const int n = jb.n, ldp = jb.ldp, nchunk = n / 16;
+  const int n = jb.n, nchunk = n / 16;
   const int i0 = it * 64;
   // fill: entry q = (c * 4 + m) * 64 + lane holds P[i0 + 4 l + m][16 c + 4 g + 0..3]
   {
     const float* __restrict__ PT = (const float*)jb.P[0];
     for (int q = threadIdx.x; q < nchunk * 256; q += 512) {
       const int ln = q & 63, m = (q >> 6) & 3, c = q >> 8;
-      panel[q] = *(const f4*)(PT + (int64_t)(i0 + 4 * (ln & 15) + m) * ldp + 16 * c + 4 * (ln >> 4));
+      const int i = i0 + 4 * (ln & 15) + m;
+      panel[q] = *(const f4*)(PT + ((int64_t)(i >> 4) * nchunk + c) * 256 + ((ln >> 4) * 16 + (i & 15)) * 4);
     }
   }
   __syncthreads();
@@ -724,67 +712,99 @@ void go_modeB_m(int mode, int prec, dim3 grid, hipStream_t s, const ModeJobs& J,
 
 namespace {
 
-// FP32 tile shapes: defaults from a sweep at 3D FHN 256^3 (mode 1 4 x 4,
-// modes >= 2 4 x 4: 96 TFLOP/s; 4 x 2 / 4 x 2: 90), overridable with
-// SETD_TILE_F32_MODE1 / SETD_TILE_F32_MODEB ("4x2" etc.).
-void f32_tile(const char* name, int& tm, int& tn) {
-  const char* e = std::getenv(name);
+// Tiles of the FP32 kernel {blocks of i, of the other index}, and the part of
+// the matrix-core rate that their loop reaches in mode 1 and in modes >= 2.
+// Measured with 18 jobs: 256^3 modes >= 2 1.42 ms with 8 x 2, 1.48 with 4 x 4
+// (16 tiles of i either way); 200^3 (13 tiles) mode 1 0.64 ms with 7 x 2, 0.68
+// with 5 x 4, 0.75 with 4 x 4; 150^3 (10 tiles) modes >= 2 0.26 ms with 5 x 2,
+// 0.30 with 4 x 4; 500 x 400, 6 jobs 38 us with 1 x 1, 96 with 4 x 4.
+struct TileF32 {
+  int ti, to;
+  double rate1, rateB;
+};
+constexpr TileF32 kTilesF32[] = {{1, 1, .50, .50}, {2, 2, .80, .80}, {4, 2, .85, .90}, {4, 4, .92, .94},
+                                 {5, 2, .88, .88}, {5, 4, .95, .87}, {7, 2, .93, .92}, {8, 2, .92, .97}};
+
+// The tile whose launch should take least time, by the model of the FP64
+// kernels (a chunk of 16 p is four MFMAs of 32 cycles per block); overridable
+// with SETD_TILE_F32_MODE1 / SETD_TILE_F32_MODEB ("4x2" etc.).
+TileF32 tile_f32(const ModeJobs& J, bool mode1) {
+  const char* e = std::getenv(mode1 ? "SETD_TILE_F32_MODE1" : "SETD_TILE_F32_MODEB");
   int a = 0, b = 0;
-  if (e && std::sscanf(e, "%dx%d", &a, &b) == 2 && (a == 2 || a == 4) && (b == 2 || b == 4)) {
-    tm = a;
-    tn = b;
+  if (e && std::sscanf(e, "%dx%d", &a, &b) == 2)
+    for (const TileF32& t : kTilesF32)
+      if (t.ti == a && t.to == b) return t;
+  TileF32 best = kTilesF32[0];
+  double bt = 1e300;
+  for (const TileF32& t : kTilesF32) {
+    double w = 0.0, wave = 0.0;
+    for (int j = 0; j < J.njobs; ++j) {
+      const ModeJob& jb = J.job[j];
+      w += (double)ceil_div(jb.n, 16 * t.ti) * ceil_div(mode1 ? jb.nb : jb.na * jb.nb, 16 * t.to);
+      wave = std::max(wave, t.ti * t.to * ((double)jb.nterms * ceil_div(jb.n, 16) * 128.0 / (mode1 ? t.rate1 : t.rateB) +
+                                           700.0 * (jb.base ? 1.6 : 1.0)));
+    }
+    w /= 1024.0;
+    const double time = ((w < 6.0 ? std::ceil(w) : w) + 0.3) * wave;
+    if (time < bt) {
+      bt = time;
+      best = t;
+    }
   }
+  return best;
 }
 
-#define SETD_F32C(KERNEL, TM_, TN_)                                                                  \
-  if (tm == TM_ && tn == TN_) {                                                                     \
-    if (mode == 2)                                                                                  \
-      hipLaunchKernelGGL((KERNEL<TM_, TN_, 2, T>), grid, dim3(64), 0, s, J, per);                    \
-    else if (mode == 1)                                                                             \
-      hipLaunchKernelGGL((KERNEL<TM_, TN_, 1, T>), grid, dim3(64), 0, s, J, per);                    \
-    else                                                                                            \
-      hipLaunchKernelGGL((KERNEL<TM_, TN_, 0, T>), grid, dim3(64), 0, s, J, per);                    \
-    return;                                                                                         \
-  }
-
-template <typename T>
-void go_mode1_f32c(int tm, int tn, int mode, dim3 grid, hipStream_t s, const ModeJobs& J, int64_t per) {
-  SETD_F32C(mode1_f32c_kernel, 4, 4)
-  SETD_F32C(mode1_f32c_kernel, 4, 2)
-  SETD_F32C(mode1_f32c_kernel, 2, 4)
-  SETD_F32C(mode1_f32c_kernel, 2, 2)
+int finish_tiles_f32(ModeJobs& J, bool mode1, const TileF32& t) {
+  J.total_tiles = assign_tiles_f64(J.job, J.njobs, mode1, t.ti, t.to);
+  J.tiles_per_job = J.njobs > 0 ? J.total_tiles / J.njobs : 0;
+  for (int j = 0; j < J.njobs; ++j)
+    if (J.job[j].tile_begin != (int64_t)j * J.tiles_per_job) J.tiles_per_job = 0;
+  return SETD_OK;
 }
-template <typename T>
-void go_modeB_f32c(int tm, int tn, int mode, dim3 grid, hipStream_t s, const ModeJobs& J, int64_t per) {
-  SETD_F32C(modeB_f32c_kernel, 4, 4)
-  SETD_F32C(modeB_f32c_kernel, 4, 2)
-  SETD_F32C(modeB_f32c_kernel, 2, 4)
-  SETD_F32C(modeB_f32c_kernel, 2, 2)
+
+template <bool M1, bool V, int TI, int TO, typename Off, typename T>
+int launch_tile_f32(const ModeJobs& J, hipStream_t s) {
+  const int64_t per = ceil_div(ceil_div(J.total_tiles, 4), 8);
+  hipLaunchKernelGGL((mode_f32_kernel<M1, V, TI, TO, Off, T>), dim3((unsigned)(per * 8)), dim3(256), 0, s, J, per);
+  SETD_LAUNCHED();
+  return SETD_OK;
+}
+
+template <bool M1, bool V, typename T>
+int launch_f32(const ModeJobs& J, const TileF32& t, hipStream_t s) {
+#define SETD_TILE(TI_, TO_) \
+  if (t.ti == TI_ && t.to == TO_) return launch_tile_f32<M1, V && (TO_ > 1), TI_, TO_, uint32_t, T>(J, s);
+  SETD_TILE(1, 1)
+  SETD_TILE(2, 2)
+  SETD_TILE(4, 2)
+  SETD_TILE(4, 4)
+  SETD_TILE(5, 2)
+  SETD_TILE(5, 4)
+  SETD_TILE(7, 2)
+  SETD_TILE(8, 2)
+#undef SETD_TILE
+  set_error("unsupported tile %dx%d", t.ti, t.to);
+  return SETD_EUNSUPPORTED;
 }
 
 int launch_mode1_f32c(ModeJobs& J, DType out, hipStream_t s) {
-  int tm = 4, tn = 4;
-  f32_tile("SETD_TILE_F32_MODE1", tm, tn);
-  finish_tiles_lp(J, true, tm, tn);
-  if (J.total_tiles == 0) return SETD_OK;
-  bool vec = true, interior = true;
-  for (int j = 0; j < J.njobs; ++j) {
-    const ModeJob& jb = J.job[j];
-    vec = vec && (jb.n % 4 == 0) && aligned_lp(jb.X[0], 16) && aligned_lp(jb.Y, 16) && aligned_lp(jb.base, 16);
-    interior = interior && jb.n % 32 == 0 && jb.nb % (16 * tn) == 0;
-  }
-  const int mode = vec ? (interior ? 2 : 1) : 0;
+  if (J.njobs == 0) return SETD_OK;
   double fl = 0.0, by = 0.0;
   if (prof_on()) job_work(J, 4, out == DType::F64 ? 8 : 4, 4, fl, by);
-  ProfScope prof(s, kProfMode1LP, fl, by);
-  bool lds = mode == 2 && tm == 4 && tn == 4;
-  for (int j = 0; j < J.njobs; ++j)
-    lds = lds && J.job[j].n >= kLds32MinN && J.job[j].n <= kLds32MaxN && J.job[j].n % 64 == 0;
+  const TileF32 cfg = tile_f32(J, true);
+  bool lds = std::getenv("SETD_TILE_F32_MODE1") == nullptr;
+  for (int j = 0; j < J.njobs; ++j) {
+    const ModeJob& jb = J.job[j];
+    lds = lds && jb.n >= kLds32MinN && jb.n <= kLds32MaxN && jb.n % 64 == 0 && jb.nb % 64 == 0 &&
+          aligned_lp(jb.X[0], 16) && aligned_lp(jb.Y, 16) && aligned_lp(jb.base, 16);
+  }
   if (lds) {   // workgroups: per job tiles_i panels x column groups of 8 * reps tiles
     const int reps = kLds32Reps;
     int64_t tot = 0;
     for (int j = 0; j < J.njobs; ++j) {
       ModeJob& jb = J.job[j];
+      jb.tiles_i = jb.n / 64;
+      jb.tiles_a = (int)(jb.nb / 64);
       jb.tile_begin = tot;
       tot += (int64_t)jb.tiles_i * ceil_div(jb.tiles_a, kLds32Waves * reps);
     }
@@ -792,6 +812,8 @@ int launch_mode1_f32c(ModeJobs& J, DType out, hipStream_t s) {
     J.tiles_per_job = J.njobs > 0 ? tot / J.njobs : 0;
     for (int j = 0; j < J.njobs; ++j)
       if (J.job[j].tile_begin != (int64_t)j * J.tiles_per_job) J.tiles_per_job = 0;
+    if (tot == 0) return SETD_OK;
+    ProfScope prof(s, kProfMode1LP, fl, by);
     const int64_t per = ceil_div(tot, 8);
     if (out == DType::F32)
       hipLaunchKernelGGL(mode1_lds32_kernel<float>, dim3((unsigned)(per * 8)), dim3(64 * kLds32Waves), 0, s, J, per,
@@ -802,36 +824,38 @@ int launch_mode1_f32c(ModeJobs& J, DType out, hipStream_t s) {
     SETD_LAUNCHED();
     return SETD_OK;
   }
-  const int64_t per = ceil_div(J.total_tiles, 8);
-  const dim3 grid((unsigned)(per * 8));
-  if (out == DType::F32) go_mode1_f32c<float>(tm, tn, mode, grid, s, J, per);
-  else go_mode1_f32c<double>(tm, tn, mode, grid, s, J, per);
-  SETD_LAUNCHED();
-  return SETD_OK;
+  finish_tiles_f32(J, true, cfg);
+  if (J.total_tiles == 0) return SETD_OK;
+  ProfScope prof(s, kProfMode1LP, fl, by);
+  return out == DType::F32 ? launch_f32<true, false, float>(J, cfg, s) : launch_f32<true, false, double>(J, cfg, s);
 }
 
 int launch_modeB_f32c(ModeJobs& J, DType out, hipStream_t s) {
-  int tm = 4, tn = 4;
-  f32_tile("SETD_TILE_F32_MODEB", tm, tn);
-  finish_tiles_lp(J, false, tm, tn);
-  if (J.total_tiles == 0) return SETD_OK;
-  bool vec = true, interior = true;
-  for (int j = 0; j < J.njobs; ++j) {
-    const ModeJob& jb = J.job[j];
-    vec = vec && (jb.na % 4 == 0) && aligned_lp(jb.Y, 16) && aligned_lp(jb.base, 16);
-    for (int t = 0; t < jb.nterms; ++t) vec = vec && aligned_lp(jb.X[t], 16);
-    interior = interior && jb.n % 32 == 0 && jb.na % (16 * tm) == 0;
-  }
-  const int mode = vec ? (interior ? 2 : 1) : 0;
+  if (J.njobs == 0) return SETD_OK;
   double fl = 0.0, by = 0.0;
   if (prof_on()) job_work(J, 4, out == DType::F64 ? 8 : 4, 4, fl, by);
+  bool big = false;   // a tile's byte offsets span more than 32 bits
+  for (int j = 0; j < J.njobs; ++j) {
+    const ModeJob& jb = J.job[j];
+    big = big || jb.na > (int64_t(1) << 26) ||
+          (jb.nb > 1 && (ceil_div(64, jb.na) + 1) * jb.na * jb.n > (int64_t(1) << 28));
+  }
+  const TileF32 cfg = big ? kTilesF32[2] : tile_f32(J, false);
+  finish_tiles_f32(J, false, cfg);
+  if (J.total_tiles == 0) return SETD_OK;
   ProfScope prof(s, kProfModeBLP, fl, by);
-  const int64_t per = ceil_div(J.total_tiles, 8);
-  const dim3 grid((unsigned)(per * 8));
-  if (out == DType::F32) go_modeB_f32c<float>(tm, tn, mode, grid, s, J, per);
-  else go_modeB_f32c<double>(tm, tn, mode, grid, s, J, per);
-  SETD_LAUNCHED();
-  return SETD_OK;
+  if (big)
+    return out == DType::F32 ? launch_tile_f32<false, false, 4, 2, uint64_t, float>(J, s)
+                             : launch_tile_f32<false, false, 4, 2, uint64_t, double>(J, s);
+  // a lane's neighbouring columns are neighbours in memory where no slab ends
+  // between them
+  bool vec = true;
+  for (int j = 0; j < J.njobs; ++j) {
+    const ModeJob& jb = J.job[j];
+    vec = vec && (jb.nb == 1 ? jb.na >= cfg.to : jb.na % cfg.to == 0);
+  }
+  if (vec) return out == DType::F32 ? launch_f32<false, true, float>(J, cfg, s) : launch_f32<false, true, double>(J, cfg, s);
+  return out == DType::F32 ? launch_f32<false, false, float>(J, cfg, s) : launch_f32<false, false, double>(J, cfg, s);
 }
 
 }  // namespace

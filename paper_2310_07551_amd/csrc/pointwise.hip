@@ -43,17 +43,17 @@ __global__ void pack_f64_kernel(const PackTable T, int n, double scale, int64_t 
   J.out[idx] = v;
 }
 
-template <typename T>
-__global__ void pack_kernel(const double* __restrict__ M, int n, int ldp, double scale, bool rowmajor,
-                            T* __restrict__ out) {
+// FP32: entry (tile t, chunk c, lane (g, l), j) = M[16 t + l][p], zero past n,
+// p = 16 c + 4 g + j for mode 1, 16 c + 4 j + g for modes >= 2.
+__global__ void pack_f32_kernel(const double* __restrict__ M, int n, double scale, bool mode1, int64_t tot,
+                                float* __restrict__ out) {
   const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (int64_t)ldp * ldp) return;
-  const int r = (int)(idx % ldp), c = (int)(idx / ldp);   // out index = r + ldp*c
-  // rowmajor: out[i*ldp + p] = M[i, p]  ->  r = p, c = i
-  // colmajor: out[i + ldp*p] = M[i, p]  ->  r = i, c = p
-  const int i = rowmajor ? c : r, p = rowmajor ? r : c;
-  double v = (i < n && p < n) ? scale * M[i + (int64_t)n * p] : 0.0;
-  out[idx] = (T)v;
+  if (idx >= tot) return;
+  const int nch = (n + 15) >> 4;
+  const int e = (int)(idx & 255), g = e >> 6, l = (e >> 2) & 15, j = e & 3;
+  const int64_t tc = idx >> 8;
+  const int i = 16 * (int)(tc / nch) + l, p = 16 * (int)(tc % nch) + (mode1 ? 4 * g + j : 4 * j + g);
+  out[idx] = i < n && p < n ? (float)(scale * M[i + (int64_t)n * p]) : 0.f;
 }
 
 // bf16 split: the packed buffer holds np planes of ldp*ldp bf16 values,
@@ -112,11 +112,10 @@ int pack_matrices_f64(const PackJob* jobs, int count, int n, hipStream_t s) {
   return SETD_OK;
 }
 
-int pack_matrix_f32(const double* M, int n, double scale, bool rowmajor, float* out, hipStream_t s) {
-  const int ldp = packed_ld(n);
-  const int64_t tot = (int64_t)ldp * ldp;
-  hipLaunchKernelGGL(pack_kernel<float>, dim3((unsigned)ceil_div(tot, 256)), dim3(256), 0, s, M, n, ldp, scale,
-                     rowmajor, out);
+int pack_matrix_f32(const double* M, int n, double scale, bool mode1, float* out, hipStream_t s) {
+  const int64_t tot = ceil_div(n, 16) * ceil_div(n, 16) * 256;
+  hipLaunchKernelGGL(pack_f32_kernel, dim3((unsigned)ceil_div(tot, 256)), dim3(256), 0, s, M, n, scale, mode1, tot,
+                     out);
   SETD_LAUNCHED();
   return SETD_OK;
 }

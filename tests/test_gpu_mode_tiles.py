@@ -109,3 +109,51 @@ def test_every_tile_of_the_batch(tile, monkeypatch):
             ref = oracle.integrate(p.U0, p.A, p.tau, 3, p.g_kind, p.params)
             for c in range(2):
                 assert rel_err(host(B.field(u, q, c), p.dims), ref[c]) < 1e-12, (p.dims, c)
+
+
+F32_TILES = ["1x1", "2x2", "4x2", "4x4", "5x2", "5x4", "7x2", "8x2"]
+
+
+def test_every_f32_tile_same_bits(monkeypatch):
+    """The FP32 kernels form every sum in an order that depends on the mode and
+    the size alone: every tile gives the same bits, with neighbouring columns
+    that end inside a slab (n1 odd, even, a multiple of 4), fewer columns than
+    a tile's lane holds, and remainders of 16 of every kind.  Against the
+    oracle 1e-5 of the largest entry (2^-24 times sums of up to 300 terms)."""
+    for dims in [(3, 5, 2), (16, 16, 16), (31, 100, 5), (34, 9, 33), (113, 7, 1), (1, 300, 2), (300, 1, 3), (65, 47, 3),
+                 (64, 130, 18), (129,), (2, 2), (300, 50)]:
+        T, W0 = wl.random_tensor(dims, 1), wl.random_tensor(dims, 2)
+        Ls = [wl.random_matrix(n, 3 + k, scale=1.0 / np.sqrt(n)) for k, n in enumerate(dims)]
+        ref = 0.7 * oracle.tucker(T, Ls) + W0
+        first = None
+        for tile in F32_TILES:
+            monkeypatch.setenv("SETD_TILE_F32_MODE1", tile)
+            monkeypatch.setenv("SETD_TILE_F32_MODEB", tile)
+            W = dev(W0)
+            setd.tucker_apply(dev(T), W, dims, [dev(L) for L in Ls], alpha=0.7, beta=1.0, prec=setd.PREC_F32)
+            got = host(W, dims)
+            say("f32 tile", tile, dims, "rel_inf %.2e" % rel_err(got, ref))
+            assert rel_err(got, ref) < 1e-5, (tile, dims)
+            first = got if first is None else first
+            assert np.array_equal(got, first), (tile, dims)
+
+
+@pytest.mark.parametrize("dims", [(33, 50), (21, 18, 17), (20, 18, 40)])
+def test_every_f32_tile_sums_terms(dims, monkeypatch):
+    """As above for the sums of terms of a step: the same bits with every tile."""
+    prob = wl.fhn_3d(dims=dims) if len(dims) == 3 else wl.schnakenberg_2d(*dims)
+    ref = oracle.integrate(prob.U0, prob.A, prob.tau, 2, prob.g_kind, prob.params)
+    first = None
+    for tile in F32_TILES:
+        monkeypatch.setenv("SETD_TILE_F32_MODE1", tile)
+        monkeypatch.setenv("SETD_TILE_F32_MODEB", tile)
+        ctx = setd.Context(dims, [[dev(M) for M in Ac] for Ac in prob.A], prob.tau, setd.PREC_F32)
+        u = torch().cat([dev(f) for f in prob.U0])
+        ctx.step(u, 2, prob.g_kind, prob.params)
+        got = u.cpu().numpy()
+        first = got if first is None else first
+        assert np.array_equal(got, first), tile
+    for c in range(2):
+        e = rel_err(first[c * ctx.N:(c + 1) * ctx.N], np.asarray(ref[c]).ravel(order="F"))
+        say("f32 terms", dims, "field", c, "rel_inf %.2e" % e)
+        assert e < 1e-3   # the error of FP32 products over a step is checked elsewhere
