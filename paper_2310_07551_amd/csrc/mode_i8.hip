@@ -317,6 +317,83 @@ __global__ void __launch_bounds__(256) slice_i8_kernel(const ModeJobs J, int64_t
   slice_emit<kSliceCols>(v, mk, n, ldp, nv, fib0, pc, ps, stage, red, colexp, D, Dexp, load);
 }
 
+// ---- slicing of modes >= 2, n <= 256 ----
+// The same digits for 32 fibres that are consecutive in the digit buffer,
+// whichever slabs they lie in, one thread for each run of 16 values of a
+// fibre: 32 ceil(n / 16) threads, none idle whatever n is, whose 16 loads are
+// in flight together.  Runs past n are written as zeros without being cut.
+// Bound by HBM; 18 tensors of 128 x 90 x 54: mode 2 38 -> 31 us, mode 3
+// 50 -> 30 us against the kernel above, whose 8 threads of 32 values per fibre
+// are idle past n; 228^3 530 -> 523 us (16 or 64 fibres: the same).
+__global__ void __launch_bounds__(512) slice_runs_i8_kernel(const ModeJobs J, int64_t per_xcd) {
+  constexpr int COLS = kSliceCols;
+  extern __shared__ __attribute__((aligned(16))) uint8_t stage[];   // COLS rows of 4 ldp + 16 bytes
+  __shared__ int red[16][COLS];
+  __shared__ int colexp[COLS];
+  const int64_t t = remap_xcd_i8(blockIdx.x, per_xcd);
+  if (t >= J.total_tiles) return;   // uniform over the block
+  const ModeJob& jb = J.job[find_job(J, t)];
+  const int n = jb.n, ldp = jb.ldp, nrun = (n + 15) >> 4;
+  const int64_t na = jb.na, ntot = na * jb.nb;
+  const int64_t fib0 = (t - jb.tile_begin) * COLS;
+  const int nv = (int)min(ntot - fib0, (int64_t)COLS);   // fibres of this workgroup
+  const int tid = threadIdx.x, nthr = COLS * nrun;       // blockDim.x: the largest nthr of the jobs, in whole waves
+  const int pc = tid % COLS, ps = tid / COLS;            // fibre of this thread, its run
+  const int row = 4 * ldp + 16;
+  uint8_t* __restrict__ D = (uint8_t*)jb.Y;
+  int* __restrict__ Dexp = (int*)(D + ((ntot + 15) & ~(int64_t)15) * 4 * (int64_t)ldp);
+  double v[16];
+  if (tid < nthr) {
+    const int64_t fib = fib0 + min(pc, nv - 1), b = jb.nb == 1 ? 0 : fib / na;
+    const double* src = (const double*)jb.X[0] + (fib + b * na * (n - 1));   // a + na n b
+#pragma unroll
+    for (int j = 0; j < 16; ++j) v[j] = src[na * min(16 * ps + j, n - 1)];
+    int mk = 0;
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      v[j] = 16 * ps + j < n ? v[j] : 0.0;
+      mk = max(mk, mag_key(v[j]));
+    }
+    red[ps][pc] = mk;
+  }
+  __syncthreads();
+  if (tid < COLS) {
+    int mm = red[0][tid];
+    for (int q = 1; q < nrun; ++q) mm = max(mm, red[q][tid]);
+    const int e = fibre_exp(mm);
+    colexp[tid] = e;
+    if (tid < nv) Dexp[fib0 + tid] = e;
+  }
+  __syncthreads();
+  if (tid < nthr) {
+    const int E = colexp[pc];
+    uint32_t d[4][4];   // [group of 4 values][plane]
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      uint32_t w[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const uint32_t x = digit_word(v[4 * q + e], E);   // unconditional: no branch
+        w[e] = E != kBadExp ? x : 0u;
+      }
+      digit_planes(w[0], w[1], w[2], w[3], d[q]);
+    }
+#pragma unroll
+    for (int sp = 0; sp < 4; ++sp)
+      *(v4i*)(stage + pc * row + 64 * ps + 16 * sp) = v4i{(int)d[0][sp], (int)d[1][sp], (int)d[2][sp], (int)d[3][sp]};
+  }
+  __syncthreads();
+  // 16-byte units in tile order (block of 16 fibres, k-step, plane, slot)
+  const int nks = ldp / 64;
+  for (int e = tid; e < COLS * nks * 16; e += blockDim.x) {
+    const int ln = e & 63, sp = (e >> 6) & 3, bk = e >> 8, cbl = bk / nks, ks = bk - cbl * nks;
+    const int fw = 16 * cbl + (ln >> 2), run = 4 * ks + (ln & 3);
+    if (fw >= nv) continue;
+    const v4i x = run < nrun ? *(const v4i*)(stage + fw * row + 64 * run + 16 * sp) : v4i{0, 0, 0, 0};
+    *(v4i*)(D + (((fib0 >> 4) + cbl) * nks + ks) * (int64_t)kTileBytes + sp * kPlaneBytes + 16 * ln) = x;
+  }
+}
+
 // ---- stage difference and its digits in one pass ----
 // D_c = g_c(U_s) - G_c for both components (the stage difference of
 // Algorithm 2, formed as the stage kernel forms it), cut straight into the
@@ -379,8 +456,11 @@ __global__ void __launch_bounds__(256) stage_slice_i8_kernel(const double* __res
 // ---- digit GEMM ----
 // Job j: X[t] = digit buffer of term t (slicing kernel layout), P[t] = packed
 // matrix digits, Y = base + sum_t scale_t P_t X_t.  A workgroup owns row
-// panel `it` (64 rows) and a run of `sup` consecutive column groups of 128
-// (for modes >= 2 the groups of all slabs in order, tiles_a per slab).  It
+// panel `it` (64 rows) and a run of `sup` consecutive column groups of 128.
+// For modes >= 2 the columns of all slabs are one row of columns, so that only
+// the last group is ragged (groups that end with each slab left 44% of the
+// lanes idle at 144^3: its mode 2, 18 jobs, took 246 us, now 194); the fused
+// form, whose slabs are whole groups, has tiles_a of them per slab.  It
 // walks the items (group, term, 256-chunk of the contraction) of its run as
 // one software pipeline: the tensor digits of the next k-step are always in
 // flight, across item and group boundaries, and when the next item needs
@@ -405,9 +485,10 @@ __global__ void __launch_bounds__(512, 1) gemm_i8_kernel(const ModeJobs J, int64
   const int n = jb.n, ldp = jb.ldp;
   const int nterms = SWAP ? jb.nterms : 1;   // without SWAP the host guarantees one term, n <= 256
   const int64_t na = jb.na, nb = jb.nb;
-  const int64_t nfib = MODE1 ? nb : na;
+  constexpr bool SLABS = !MODE1 && FUSE;   // groups slab by slab; else of all columns in a row
   const int64_t ntot = MODE1 ? nb : na * nb;
-  const int64_t ngroups = (int64_t)jb.tiles_a * (MODE1 ? 1 : nb);
+  const int64_t nfib = SLABS ? na : ntot;
+  const int64_t ngroups = (int64_t)jb.tiles_a * (SLABS ? nb : 1);
   const int64_t grp0 = (lt / jb.tiles_i) * sup;
   const int ngrp = (int)(ngroups - grp0 < sup ? ngroups - grp0 : sup);
   const int nch = SWAP ? (n + kPanelK - 1) / kPanelK : 1;   // 256-chunks of the contraction
@@ -427,7 +508,7 @@ __global__ void __launch_bounds__(512, 1) gemm_i8_kernel(const ModeJobs J, int64
     int64_t ct, bslab;
   };
   auto first_pos = [&]() __attribute__((always_inline)) {
-    Pos p{0, 0, MODE1 ? grp0 : grp0 % jb.tiles_a, MODE1 ? 0 : grp0 / jb.tiles_a};
+    Pos p{0, 0, SLABS ? grp0 % jb.tiles_a : grp0, SLABS ? grp0 / jb.tiles_a : 0};
     return p;
   };
   auto advance = [&](Pos p) __attribute__((always_inline)) {
@@ -435,7 +516,7 @@ __global__ void __launch_bounds__(512, 1) gemm_i8_kernel(const ModeJobs J, int64
       p.ci = 0;
       if (++p.tm == nterms) {
         p.tm = 0;
-        if (++p.ct == jb.tiles_a && !MODE1) {
+        if (++p.ct == jb.tiles_a && SLABS) {
           p.ct = 0;
           ++p.bslab;
         }
@@ -446,7 +527,7 @@ __global__ void __launch_bounds__(512, 1) gemm_i8_kernel(const ModeJobs J, int64
   // column of this lane in the item's group (validity, global fibre index)
   auto column = [&](const Pos& p, int64_t& ca, int64_t& fib) __attribute__((always_inline)) {
     ca = p.ct * kGroupCols + kWaveCols * wave + l;
-    fib = MODE1 ? ca : ca + na * p.bslab;
+    fib = SLABS ? ca + na * p.bslab : ca;
   };
   // tensor digits of an item, k-step k: this lane's 4 x 16 bytes (1 KB apart)
   auto bptr = [&](const Pos& p, int k64) __attribute__((always_inline)) {
@@ -716,7 +797,12 @@ __global__ void __launch_bounds__(512, 1) gemm_i8_kernel(const ModeJobs J, int64
         } else if (ca < nfib) {
           double* __restrict__ Y = (double*)jb.Y;
           const double* __restrict__ base = (const double*)jb.base;
-          const int64_t slab = MODE1 ? 0 : na * (int64_t)n * cur.bslab;
+          // column a + na b begins at a + na n b = column + na (n - 1) b
+          int64_t slab = 0;
+          if (!MODE1 && nb > 1) {
+            const int64_t b = ntot >> 32 ? ca / na : (int64_t)((uint32_t)ca / (uint32_t)na);
+            slab = na * (n - 1) * b;
+          }
           if (!MODE1 && row0 + kPanelRows <= n) {
             // modes >= 2, every row inside: one per-lane offset per item plus
             // uniform row steps (no per-row offsets held across the loop)
@@ -944,8 +1030,9 @@ int launch_gemm_i8(const ModeJobs& J, bool mode1, hipStream_t s, int fuse_next) 
   for (int j = 0; j < G.njobs; ++j) {
     ModeJob& jb = G.job[j];
     jb.tiles_i = (int)ceil_div(jb.n, kPanelRows);
-    jb.tiles_a = (int)ceil_div(mode1 ? jb.nb : jb.na, kGroupCols);
+    jb.tiles_a = (int)ceil_div(mode1 ? jb.nb : fuse_next ? jb.na : jb.na * jb.nb, kGroupCols);
   }
+  const bool slabs = !mode1 && fuse_next;
   // Run length: one 8-wave workgroup fits a CU, so the launch takes about
   // ceil(workgroups / CUs) rounds of (sup + 1) group-times (the one: the
   // panel fill and pipeline start of a workgroup).  The shortest such time,
@@ -958,7 +1045,7 @@ int launch_gemm_i8(const ModeJobs& J, bool mode1, hipStream_t s, int fuse_next) 
     int64_t wgs = 0;
     for (int j = 0; j < G.njobs; ++j) {
       const ModeJob& jb = G.job[j];
-      wgs += (int64_t)jb.tiles_i * ceil_div((int64_t)jb.tiles_a * (mode1 ? 1 : jb.nb), c);
+      wgs += (int64_t)jb.tiles_i * ceil_div((int64_t)jb.tiles_a * (slabs ? jb.nb : 1), c);
     }
     const double t = (double)ceil_div(wgs, kCus) * (c + 1);
     if (best == 0.0 || t < best) {
@@ -970,7 +1057,7 @@ int launch_gemm_i8(const ModeJobs& J, bool mode1, hipStream_t s, int fuse_next) 
   for (int j = 0; j < G.njobs; ++j) {
     ModeJob& jb = G.job[j];
     jb.tile_begin = tot;
-    tot += (int64_t)jb.tiles_i * ceil_div((int64_t)jb.tiles_a * (mode1 ? 1 : jb.nb), sup);
+    tot += (int64_t)jb.tiles_i * ceil_div((int64_t)jb.tiles_a * (slabs ? jb.nb : 1), sup);
   }
   G.total_tiles = tot;
   G.tiles_per_job = G.njobs > 0 ? tot / G.njobs : 0;
@@ -1037,6 +1124,12 @@ int launch_mode_i8(ModeJobs& J, bool mode1, void* ws, size_t ws_bytes, hipStream
   }
   // 2. slicing launches: one job per distinct input (all jobs of a launch
   // share the regime; inputs shared by several jobs have equal shapes)
+  bool runs = !mode1;   // modes >= 2 up to one chunk: a thread per run of 16 values
+  int nmax = 0;
+  for (int j = 0; j < J.njobs; ++j) {
+    runs = runs && J.job[j].n <= kSliceChunk;
+    nmax = std::max(nmax, J.job[j].n);
+  }
   for (int k0 = 0; k0 < ninputs; k0 += kMaxJobs) {
     ModeJobs S;
     S.njobs = 0;
@@ -1052,18 +1145,24 @@ int launch_mode_i8(ModeJobs& J, bool mode1, void* ws, size_t ws_bytes, hipStream
       sj.Y = (char*)ws + (size_t)k * per;
       sj.base = nullptr;
       sj.tiles_i = 1;
-      sj.tiles_a = (int)ceil_div(mode1 ? sj.nb : sj.na, kSliceCols);
+      sj.tiles_a = (int)ceil_div(mode1 ? sj.nb : sj.na, kSliceCols);   // runs: not used
       sj.tile_begin = tot;
-      tot += (int64_t)sj.tiles_a * (mode1 ? 1 : sj.nb);
+      tot += runs ? ceil_div(sj.na * sj.nb, kSliceCols) : (int64_t)sj.tiles_a * (mode1 ? 1 : sj.nb);
       S.job[S.njobs++] = sj;
     }
     S.total_tiles = tot;
     S.tiles_per_job = 0;
     const int64_t pxcd = ceil_div(tot, 8);
-    if (mode1)
-      hipLaunchKernelGGL(slice_i8_kernel<true>, dim3((unsigned)(pxcd * 8)), dim3(256), 0, s, S, pxcd);
-    else
-      hipLaunchKernelGGL(slice_i8_kernel<false>, dim3((unsigned)(pxcd * 8)), dim3(256), 0, s, S, pxcd);
+    const dim3 grid((unsigned)(pxcd * 8));
+    if (runs) {
+      const dim3 block((unsigned)round_up(kSliceCols * ceil_div(nmax, 16), 64));
+      const size_t lds = (size_t)kSliceCols * (4 * packed_ld(nmax) + 16);
+      hipLaunchKernelGGL(slice_runs_i8_kernel, grid, block, lds, s, S, pxcd);
+    } else if (mode1) {
+      hipLaunchKernelGGL(slice_i8_kernel<true>, grid, dim3(256), 0, s, S, pxcd);
+    } else {
+      hipLaunchKernelGGL(slice_i8_kernel<false>, grid, dim3(256), 0, s, S, pxcd);
+    }
     SETD_LAUNCHED();
   }
   for (int j = 0; j < J.njobs; ++j)
