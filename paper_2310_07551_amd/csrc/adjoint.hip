@@ -110,37 +110,57 @@ __global__ void __launch_bounds__(kRedThreads) adj_stage_kernel(const double* __
 //   Ubar = Wbar + U3bar + U2bar + K^T Fbar + J_g(U)^T (Gbar + Fbar)
 // (in place on ubar), parameter partials (rows kRowP3..) and the K part of
 // the diffusion-size derivative <Fbar_c, K_c U_c> = <Fbar_c, F_c - G_c>.
+// The component count is a template argument and every neighbour is loaded
+// without a branch, from a clamped index with a zero coefficient past the
+// boundary, so that the loads of a point are in flight together (64^3: 18.8
+// us with each behind its branch, now 10.5).
+template <int NC>
 __global__ void __launch_bounds__(kRedThreads) adj_final_kernel(
     const double* __restrict__ U, double* __restrict__ ubar, const double* __restrict__ U3bar,
     const double* __restrict__ U2bar, const double* __restrict__ Fbar, const double* __restrict__ Gbar,
-    const double* __restrict__ F, const double* __restrict__ G, const double* __restrict__ KtF, int ncomp, int64_t N,
+    const double* __restrict__ F, const double* __restrict__ G, const double* __restrict__ KtF, int64_t N,
     int d, int n1, int n2, int n3, StencilSet S, GParams gp, double* __restrict__ part) {
   double acc[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
   const int ns[3] = {n1, n2, n3};
   const int64_t strides[3] = {1, (int64_t)n1, (int64_t)n1 * n2};
   for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < N;
        idx += (int64_t)gridDim.x * blockDim.x) {
-    const int i1 = (int)(idx % n1);
-    const int64_t r = idx / n1;
-    const int idxs[3] = {i1, (int)(r % n2), d == 3 ? (int)(r / n2) : 0};
-    double gb[2] = {0.0, 0.0}, uc[2] = {0.0, 0.0}, kt[2] = {0.0, 0.0};
-    for (int c = 0; c < ncomp; ++c) {
+    int idxs[3];
+    if (N >> 32) {
+      idxs[0] = (int)(idx % n1);
+      const int64_t r = idx / n1;
+      idxs[1] = (int)(r % n2);
+      idxs[2] = d == 3 ? (int)(r / n2) : 0;
+    } else {
+      const uint32_t i = (uint32_t)idx, r = i / (uint32_t)n1, q = r / (uint32_t)n2;
+      idxs[0] = (int)(i - r * (uint32_t)n1);
+      idxs[1] = (int)(r - q * (uint32_t)n2);
+      idxs[2] = d == 3 ? (int)q : 0;
+    }
+    double gb[2] = {0.0, 0.0}, uc[2] = {0.0, 0.0}, kt[2] = {0.0, 0.0}, sum[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
       const int64_t o = (int64_t)c * N + idx;
+      const double f = Fbar[o];
       uc[c] = U[o];
-      gb[c] = Gbar[o] + Fbar[o];
-      acc[4 + c] += Fbar[o] * (F[o] - G[o]);
+      gb[c] = Gbar[o] + f;
+      acc[4 + c] += f * (F[o] - G[o]);
+      sum[c] = ubar[o] + U3bar[o] + U2bar[o];
       if (KtF) {
         kt[c] = KtF[o];
       } else {
         // (A^T x)_i = A[i-1, i] x_{i-1} + A[i, i] x_i + A[i+1, i] x_{i+1}
-        const double* __restrict__ fb = Fbar + (int64_t)c * N;
         double k = 0.0;
-        for (int mu = 0; mu < d; ++mu) {
-          const int i = idxs[mu];
-          const int off = c * 3 + mu;
-          double t = S.di[off][i] * fb[idx];
-          if (i > 0) t += S.up[off][i - 1] * fb[idx - strides[mu]];
-          if (i + 1 < ns[mu]) t += S.lo[off][i + 1] * fb[idx + strides[mu]];
+#pragma unroll
+        for (int mu = 0; mu < 3; ++mu) {
+          if (mu >= d) break;
+          const int i = idxs[mu], off = c * 3 + mu;
+          const bool lo = i > 0, hi = i + 1 < ns[mu];
+          const double up = S.up[off][lo ? i - 1 : 0], dn = S.lo[off][hi ? i + 1 : i];
+          const double xl = Fbar[o - (lo ? strides[mu] : 0)], xh = Fbar[o + (hi ? strides[mu] : 0)];
+          double t = S.di[off][i] * f;
+          t += (lo ? up : 0.0) * xl;
+          t += (hi ? dn : 0.0) * xh;
           k += t;
         }
         kt[c] = k;
@@ -150,10 +170,8 @@ __global__ void __launch_bounds__(kRedThreads) adj_final_kernel(
     reaction_vjp(gp, uc[0], uc[1], gb[0], gb[1], ub, vb, dp);
     for (int k = 0; k < 4; ++k) acc[k] += dp[k];
     const double gv[2] = {ub, vb};
-    for (int c = 0; c < ncomp; ++c) {
-      const int64_t o = (int64_t)c * N + idx;
-      ubar[o] = ubar[o] + U3bar[o] + U2bar[o] + kt[c] + gv[c];
-    }
+#pragma unroll
+    for (int c = 0; c < NC; ++c) ubar[(int64_t)c * N + idx] = sum[c] + kt[c] + gv[c];
   }
   block_partials<6>(acc, part, kRowP3);
 }
@@ -176,17 +194,22 @@ __global__ void __launch_bounds__(kRedThreads) adj_dots_kernel(const double* __r
 }
 
 // grad[k] += parameter partials (k < nparams); grad[nparams + c] += diffusion
-// partials for the components in sigma_mask.  One wave; row sums in a fixed
-// order, so the result does not depend on scheduling.
-__global__ void adj_reduce_kernel(const double* __restrict__ part, int nparams, int ncomp, int sigma_mask, bool dots,
-                                  double* __restrict__ grad) {
+// partials for the components in sigma_mask.  One wave per row, the row sums
+// in a fixed order, so the result does not depend on scheduling (one thread
+// per row waited for 512 loads in turn: 15 us, now 4).
+__global__ void __launch_bounds__(64 * kRows) adj_reduce_kernel(const double* __restrict__ part, int nparams,
+                                                                int ncomp, int sigma_mask, bool dots,
+                                                                double* __restrict__ grad) {
   __shared__ double rs[kRows];
-  const int r = threadIdx.x;
-  if (r < kRows) {
-    double s = 0.0;
-    for (int b = 0; b < kRedBlocks; ++b) s += part[r * kRedBlocks + b];
-    rs[r] = s;
-  }
+  const int r = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  double v[kRedBlocks / 64], s = 0.0;
+#pragma unroll
+  for (int b = 0; b < kRedBlocks / 64; ++b) v[b] = part[r * kRedBlocks + 64 * b + lane];
+#pragma unroll
+  for (int b = 0; b < kRedBlocks / 64; ++b) s += v[b];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+  if (lane == 0) rs[r] = s;
   __syncthreads();
   if (threadIdx.x != 0) return;
   for (int k = 0; k < nparams && k < 4; ++k) grad[k] += rs[kRowP1 + k] + rs[kRowP2 + k] + rs[kRowP3 + k];
@@ -283,11 +306,10 @@ int alloc_adjoint_buffers(setd_ctx* c) {
 }
 
 // d = 3: E = sum_k sum_t s_t sum_mu T(V_k, {P_kt with mode mu -> dP_kt,mu})
-// for each chain (output k, term t) of one component, sharing the partial
+// for each chain (output k, term t) of every component, sharing the partial
 // products between the three derivative Tuckers of a term: with
-// X0 = V x1 P1, X1 = V x1 dP1 (mode 1), then X0 <- X0 x2 P2 and
-// X1 <- X1 x2 P2 + X0 x2 dP2 (mode 2), the sum is X1 x3 P3 + X0 x3 dP3
-// (mode 3): 7 mode products per term instead of 9.
+// X0 = V x1 P1 x2 P2 and X1 = V x1 dP1 x2 P2 + V x1 P1 x2 dP2, the sum is
+// X1 x3 P3 + X0 x3 dP3.
 struct SigmaChain {
   const double* V;
   void* const* P;    // packed bank matrices of the term
@@ -295,43 +317,86 @@ struct SigmaChain {
   double scale;
   double* A0;        // mode-1 partials
   double* A1;
-  double* B0;        // mode-2 partials
+  double* B0;        // X0 and X1
   double* B1;
 };
+struct SigmaOut {
+  double* E;
+  const double* base;   // nullable
+};
 
-int sigma_chains_d3(const int* dims, SigmaChain* ch, int nch, double* const* E, const double* const* Ebase,
-                    int nout, int T, hipStream_t s) {
+// X0 and X1 of the chains in passes over slabs, modes 1 and 2 at once: 6
+// products a chain instead of the 5 with shared mode-1 partials, but none of
+// those in memory and a launch less (64^3, 18 chains: 79 us against 111).  Up
+// to kSlabSumN the two parts of X1 are the terms of one job, else the second
+// is added to the first.
+int sigma_slabs(const int* dims, const std::vector<SigmaChain>& ch, hipStream_t s) {
+  const bool sum = dims[0] <= kSlabSumN;
+  for (int pass = 0; pass < (sum ? 2 : 3); ++pass) {   // X0; X1, or its two parts
+    SlabJobs J;
+    J.njobs = 0;
+    for (size_t k = 0; k < ch.size(); ++k) {
+      const SigmaChain& q = ch[k];
+      SlabJob& jb = J.job[J.njobs++];
+      jb = SlabJob{};
+      jb.n1 = dims[0];
+      jb.n2 = dims[1];
+      jb.nb = dims[2];
+      jb.nterms = pass == 1 && sum ? 2 : 1;
+      jb.X[0] = jb.X[1] = q.V;
+      jb.P1[0] = pass == 1 ? q.dP[0] : q.P[0];
+      jb.P2[0] = pass == 2 ? q.dP[1] : q.P[1];
+      jb.P1[1] = q.P[0];
+      jb.P2[1] = q.dP[1];
+      jb.scale[0] = jb.scale[1] = q.scale;
+      jb.Y = pass == 0 ? q.B0 : q.B1;
+      jb.base = pass == 2 ? q.B1 : nullptr;
+      if (J.njobs == kMaxJobs || k + 1 == ch.size()) {
+        SETD_TRY(launch_slab_f64(J, s));
+        J.njobs = 0;
+      }
+    }
+  }
+  return SETD_OK;
+}
+
+int sigma_chains_d3(const int* dims, const std::vector<SigmaChain>& ch, const std::vector<SigmaOut>& outs, int T,
+                    hipStream_t s) {
   const int64_t N = (int64_t)dims[0] * dims[1] * dims[2];
   std::vector<ModeJob> jobs;
-  for (int k = 0; k < nch; ++k) {
-    jobs.push_back(mk_job(ch[k].V, ch[k].P[0], ch[k].scale, ch[k].A0, nullptr, 1, dims[0], N / dims[0]));
-    jobs.push_back(mk_job(ch[k].V, ch[k].dP[0], ch[k].scale, ch[k].A1, nullptr, 1, dims[0], N / dims[0]));
+  if (use_slab_3d(dims)) {
+    SETD_TRY(sigma_slabs(dims, ch, s));
+  } else {
+    for (const SigmaChain& q : ch) {
+      jobs.push_back(mk_job(q.V, q.P[0], q.scale, q.A0, nullptr, 1, dims[0], N / dims[0]));
+      jobs.push_back(mk_job(q.V, q.dP[0], q.scale, q.A1, nullptr, 1, dims[0], N / dims[0]));
+    }
+    SETD_TRY(launch_f64_jobs(jobs, true, s));
+    for (const SigmaChain& q : ch) {
+      jobs.push_back(mk_job(q.A0, q.P[1], 1.0, q.B0, nullptr, dims[0], dims[1], dims[2]));
+      ModeJob jb = mk_job(q.A1, q.P[1], 1.0, q.B1, nullptr, dims[0], dims[1], dims[2]);
+      jb.nterms = 2;
+      jb.X[1] = q.A0;
+      jb.P[1] = q.dP[1];
+      jb.scale[1] = 1.0;
+      jobs.push_back(jb);
+    }
+    SETD_TRY(launch_f64_jobs(jobs, false, s));
   }
-  SETD_TRY(launch_f64_jobs(jobs, true, s));
-  for (int k = 0; k < nch; ++k) {
-    jobs.push_back(mk_job(ch[k].A0, ch[k].P[1], 1.0, ch[k].B0, nullptr, dims[0], dims[1], dims[2]));
-    ModeJob jb = mk_job(ch[k].A1, ch[k].P[1], 1.0, ch[k].B1, nullptr, dims[0], dims[1], dims[2]);
-    jb.nterms = 2;
-    jb.X[1] = ch[k].A0;
-    jb.P[1] = ch[k].dP[1];
-    jb.scale[1] = 1.0;
-    jobs.push_back(jb);
-  }
-  SETD_TRY(launch_f64_jobs(jobs, false, s));
   // mode 3: output o sums chains o*T .. o*T+T-1; first the X1 x3 P3 terms
-  // (onto Ebase[o], or none), then the X0 x3 dP3 terms onto E[o]
+  // (onto its base, or none), then the X0 x3 dP3 terms onto E
   for (int pass = 0; pass < 2; ++pass) {
-    for (int o = 0; o < nout; ++o) {
+    for (size_t o = 0; o < outs.size(); ++o) {
       ModeJob jb{};
       jb.nterms = T;
       for (int t = 0; t < T; ++t) {
-        const SigmaChain& q = ch[o * T + t];   // s_t is in the mode-1 partials
+        const SigmaChain& q = ch[o * T + t];   // s_t is in the partials
         jb.X[t] = pass == 0 ? q.B1 : q.B0;
         jb.P[t] = pass == 0 ? q.P[2] : q.dP[2];
         jb.scale[t] = 1.0;
       }
-      jb.Y = E[o];
-      jb.base = pass == 0 ? Ebase[o] : E[o];
+      jb.Y = outs[o].E;
+      jb.base = pass == 0 ? outs[o].base : outs[o].E;
       jb.na = (int64_t)dims[0] * dims[1];
       jb.nb = 1;
       jb.n = dims[2];
@@ -404,7 +469,9 @@ int adjoint_step(setd_ctx* c, const double* u_in, const double* rec, double* uba
   // E2 = tau/3 dS1(2) F; dS V = sum_i eta_i sum_mu T(V, {P_i with P_{i,mu} -> dP_{i,mu}}).
   const bool dots = sigma_mask != 0;
   if (dots && d == 3) {
-    for (int a = 0; a < 2; ++a)
+    for (int a = 0; a < 2; ++a) {
+      std::vector<SigmaChain> ch;
+      std::vector<SigmaOut> outs;
       for (int cc = 0; cc < nc; ++cc) {
         if (!(sigma_mask & (1 << cc))) continue;
         struct {
@@ -419,20 +486,18 @@ int adjoint_step(setd_ctx* c, const double* u_in, const double* rec, double* uba
              a == 0 ? eta1 : eta2},
             {c->E2, sF, e21, tau / 3.0, eta1}};
         const int nout = a == 0 ? 3 : 2;   // E2 has a phi_1 action only
-        SigmaChain ch[9];
-        double* E[3];
-        const double* Eb[3];
         for (int k = 0; k < nout; ++k) {
-          E[k] = at(spec[k].E, cc);
-          Eb[k] = a == 0 ? nullptr : E[k];   // the first pass overwrites
+          double* E = at(spec[k].E, cc);
+          outs.push_back({E, a == 0 ? nullptr : E});   // the first pass overwrites
           for (int t = 0; t < T; ++t) {
             const int j = k * T + t;
-            ch[j] = {at(spec[k].X, cc), c->bank[cc][spec[k].e][t], c->dbank[cc][spec[k].e][t],
-                     spec[k].mult * spec[k].eta[t], c->Y1[cc][j], c->Y2[cc][j], c->sY[cc][j][0], c->sY[cc][j][1]};
+            ch.push_back({at(spec[k].X, cc), c->bank[cc][spec[k].e][t], c->dbank[cc][spec[k].e][t],
+                          spec[k].mult * spec[k].eta[t], c->Y1[cc][j], c->Y2[cc][j], c->sY[cc][j][0], c->sY[cc][j][1]});
           }
         }
-        SETD_TRY(sigma_chains_d3(c->dims, ch, nout * T, E, Eb, nout, T, s));
       }
+      SETD_TRY(sigma_chains_d3(c->dims, ch, outs, T, s));
+    }
   } else if (dots) {
     void* mats[3][3][3];   // [output][term][mu]
     for (int a = 0; a < 2; ++a)
@@ -541,10 +606,10 @@ int adjoint_step(setd_ctx* c, const double* u_in, const double* rec, double* uba
     ktf = c->KtF;
   }
   const int n3 = d == 3 ? c->dims[2] : 1;
-  hipLaunchKernelGGL(adj_final_kernel, rg, rb, 0, s, u, ubar, c->U3bar, c->U2bar, c->Fbar, c->Gbar, sF, sG, ktf,
-                     nc, N, d, c->dims[0], c->dims[1], n3, c->st, gp, c->part);
+  hipLaunchKernelGGL(nc == 2 ? adj_final_kernel<2> : adj_final_kernel<1>, rg, rb, 0, s, u, ubar, c->U3bar, c->U2bar,
+                     c->Fbar, c->Gbar, sF, sG, ktf, N, d, c->dims[0], c->dims[1], n3, c->st, gp, c->part);
   SETD_LAUNCHED();
-  hipLaunchKernelGGL(adj_reduce_kernel, dim3(1), dim3(64), 0, s, c->part, nparams, nc, sigma_mask, dots, grad);
+  hipLaunchKernelGGL(adj_reduce_kernel, dim3(1), dim3(64 * kRows), 0, s, c->part, nparams, nc, sigma_mask, dots, grad);
   SETD_LAUNCHED();
   return SETD_OK;
 }

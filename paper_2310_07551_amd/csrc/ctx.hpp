@@ -121,6 +121,8 @@ struct StageBufs {
 int step_with(setd_ctx* c, double* u, const GParams& gp, hipStream_t s, const StageBufs& b);
 // Launches FP64 mode-product jobs of one regime in groups of kMaxJobs.
 int launch_f64_jobs(std::vector<ModeJob>& jobs, bool mode1, hipStream_t s);
+// Whether an FP64 product of a 3D tensor runs modes 1 and 2 as one pass over slabs.
+bool use_slab_3d(const int* dims);
 // exprk3ds_cplx (cplx.hip): complex phi bank for step size tau (synchronises
 // s; no-op when already built for tau) and one step.
 int prepare_cplx(setd_ctx* c, double tau, hipStream_t s);

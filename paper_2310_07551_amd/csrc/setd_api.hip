@@ -211,10 +211,14 @@ bool use_slab(int d, const int* dims, const TuckerOut* outs, int nouts) {
       if (outs[o].nterms != 2) return false;
     return dims[0] <= kSlabSumN && dims[1] <= kSlabSumN;
   }
-  const bool panels = dims[0] >= 192 && dims[0] % 64 == 0 && dims[1] >= 192 && dims[1] <= 256 && dims[1] % 64 == 0;
-  return d == 3 && dims[0] <= kSlabMaxN1 && !panels && slab_rows(dims[0], (int64_t)dims[0] * dims[1] * dims[2]);
+  return d == 3 && use_slab_3d(dims);
 }
 }  // namespace
+
+bool setd::use_slab_3d(const int* dims) {
+  const bool panels = dims[0] >= 192 && dims[0] % 64 == 0 && dims[1] >= 192 && dims[1] <= 256 && dims[1] % 64 == 0;
+  return dims[0] <= kSlabMaxN1 && !panels && slab_rows(dims[0], (int64_t)dims[0] * dims[1] * dims[2]);
+}
 
 int setd::run_tucker_group(int d, const int* dims, TuckerOut* outs, int nouts, int prec, hipStream_t s,
                            void* i8ws, size_t i8bytes) {
