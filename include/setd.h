@@ -130,6 +130,9 @@ int setd_tucker_apply(const double* V, double* W, int d, const int64_t* dims,
                       const double* const* M, double alpha, double beta, int prec,
                       void* ws, size_t ws_bytes, void* stream);
 size_t setd_tucker_workspace_bytes(int d, const int64_t* dims, int prec);
+/* Gives back what the library keeps on the current device between calls:
+ * workspaces, and up to 512 MiB of destroyed contexts' memory (which an
+ * allocation that would fail gives back by itself). */
 int setd_release_workspace(void);
 
 /*

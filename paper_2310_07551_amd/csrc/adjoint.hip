@@ -273,7 +273,9 @@ int build_adjoint_bank(setd_ctx* c, hipStream_t s) {
       jobs.push_back({(const double*)A.p, nullptr, 0.0, true, (double*)q});
       q += pb;
       SETD_TRY(pack_matrices_f64(jobs.data(), (int)jobs.size(), n, s));
-      SETD_HIP(hipStreamSynchronize(s));   // A and raw are released at scope exit
+      SETD_HIP(hipStreamSynchronize(s));   // all work on A and raw
+      A.keep();
+      raw.keep();
     }
   }
   c->adj_tau = c->tau;

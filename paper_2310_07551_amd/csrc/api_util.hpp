@@ -20,18 +20,26 @@ inline int bank_index(int stage, int ell) {
   return -1;
 }
 
+// Device memory (setd_api.hip).  release() frees it; keep(), for a caller that
+// has waited for all work on it, keeps the block for a later allocation of
+// half its size to its size.  At most kKeptBytes per device are kept, the
+// oldest go first; setd_release_workspace or a failing allocation gives them
+// all back.  Safe with several threads and streams: a block is in the list,
+// idle, or belongs to one owner.  A differentiated run makes and drops a
+// context per pass, which allocates about 13 times (18 us each) and frees as
+// often (53 us each, 0.2 GB at 64^3; a pass of 5 steps 5.34 -> 4.57 ms).
+constexpr size_t kKeptBytes = (size_t)512 << 20;
+int device_alloc(size_t bytes, void** p, size_t* capacity, int* dev);
+void device_keep(void* p, size_t capacity, int dev);
+int device_release_kept(int dev);
+
 struct DevBuf {
   void* p = nullptr;
   size_t bytes = 0;
   int alloc(size_t b) {
     release();
     if (b == 0) return SETD_OK;
-    hipError_t e = hipMalloc(&p, b);
-    if (e != hipSuccess) {
-      p = nullptr;
-      set_error("hipMalloc(%zu) failed: %s", b, hipGetErrorString(e));
-      return SETD_ENOMEM;
-    }
+    SETD_TRY(device_alloc(b, &p, &capacity_, &dev_));
     bytes = b;
     return SETD_OK;
   }
@@ -40,7 +48,16 @@ struct DevBuf {
     p = nullptr;
     bytes = 0;
   }
+  void keep() {
+    if (p) device_keep(p, capacity_, dev_);
+    p = nullptr;
+    bytes = 0;
+  }
   ~DevBuf() { release(); }
+
+ private:
+  size_t capacity_ = 0;
+  int dev_ = 0;
 };
 
 // One mu-mode product job with a single term (see ModeJob).

@@ -51,6 +51,12 @@ struct setd_ctx {
   setd::DevBuf cplx_bank_mem, cplx_mem;
   void* cbank[2][5][2][3][2] = {};   // [comp][entry][term][mu][re, im]; last mu: eta folded in
   double* cY[2][24] = {};            // complex intermediates (re, im planes)
+  // Keeps the memory for a later context; every stream must be idle.
+  void keep_memory() {
+    for (setd::DevBuf* b : {&i8_mem, &A_mem, &stencil_mem, &bank_mem, &work_mem, &adj_bank_mem, &adj_mem,
+                            &cplx_bank_mem, &cplx_mem})
+      b->keep();
+  }
   ~setd_ctx() {
     if (gexec) (void)hipGraphExecDestroy(gexec);
     if (ev_in) (void)hipEventDestroy(ev_in);

@@ -152,6 +152,96 @@ namespace {
 // `prec`, term inputs and Y1/Y2 are FP32 and the outputs FP64.
 }  // namespace
 
+namespace {
+// Kept device blocks (api_util.hpp).  Never destroyed: objects may be freed
+// while the process ends.
+struct KeptBlocks {
+  struct Block {
+    void* p;
+    size_t bytes;
+    int dev;
+  };
+  std::mutex mu;
+  std::vector<Block> blocks;   // oldest first
+};
+KeptBlocks& kept() {
+  static KeptBlocks* k = new KeptBlocks();
+  return *k;
+}
+
+// Takes the oldest blocks of `dev` off the list (its lock held) until those
+// left hold at most `limit` bytes.
+std::vector<void*> drop_kept(int dev, size_t limit) {
+  std::vector<void*> out;
+  std::vector<KeptBlocks::Block>& b = kept().blocks;
+  size_t sum = 0;
+  for (const auto& k : b) sum += k.dev == dev ? k.bytes : 0;
+  for (size_t k = 0; k < b.size() && sum > limit;) {
+    if (b[k].dev != dev) {
+      ++k;
+      continue;
+    }
+    sum -= b[k].bytes;
+    out.push_back(b[k].p);
+    b.erase(b.begin() + k);
+  }
+  return out;
+}
+}  // namespace
+
+int setd::device_alloc(size_t bytes, void** p, size_t* capacity, int* dev) {
+  *p = nullptr;
+  SETD_HIP(hipGetDevice(dev));
+  {
+    std::lock_guard<std::mutex> lk(kept().mu);
+    std::vector<KeptBlocks::Block>& b = kept().blocks;
+    size_t best = b.size();
+    for (size_t k = 0; k < b.size(); ++k)
+      if (b[k].dev == *dev && b[k].bytes >= bytes && b[k].bytes / 2 <= bytes &&
+          (best == b.size() || b[k].bytes < b[best].bytes))
+        best = k;
+    if (best < b.size()) {
+      *p = b[best].p;
+      *capacity = b[best].bytes;
+      b.erase(b.begin() + best);
+      return SETD_OK;
+    }
+  }
+  hipError_t e = hipMalloc(p, bytes);
+  if (e != hipSuccess) {   // once more without the kept blocks
+    (void)hipGetLastError();
+    SETD_TRY(device_release_kept(*dev));
+    e = hipMalloc(p, bytes);
+  }
+  if (e != hipSuccess) {
+    *p = nullptr;
+    set_error("hipMalloc(%zu) failed: %s", bytes, hipGetErrorString(e));
+    return SETD_ENOMEM;
+  }
+  *capacity = bytes;
+  return SETD_OK;
+}
+
+void setd::device_keep(void* p, size_t capacity, int dev) {
+  std::vector<void*> out;
+  {
+    std::lock_guard<std::mutex> lk(kept().mu);
+    kept().blocks.push_back({p, capacity, dev});
+    out = drop_kept(dev, kKeptBytes);   // p itself, if it is larger
+  }
+  for (void* q : out) (void)hipFree(q);
+}
+
+int setd::device_release_kept(int dev) {
+  std::vector<void*> out;
+  {
+    std::lock_guard<std::mutex> lk(kept().mu);
+    out = drop_kept(dev, 0);
+  }
+  for (void* q : out) SETD_HIP(hipFree(q));
+  return SETD_OK;
+}
+
 int setd::launch_f64_jobs(std::vector<ModeJob>& jobs, bool mode1, hipStream_t s) {
   ModeJobs J;
   J.njobs = 0;
@@ -512,7 +602,8 @@ int build_bank(setd_ctx* c, hipStream_t s) {
       jobs.push_back({Adev(cc, mu), nullptr, 0.0, false, (double*)c->Apk[cc][mu]});
       SETD_TRY(pack_matrices_f64(jobs.data(), (int)jobs.size(), n, s));
     }
-    SETD_HIP(hipStreamSynchronize(s));   // raw buffers are released at scope exit
+    SETD_HIP(hipStreamSynchronize(s));   // all work on the raw buffers
+    for (DevBuf& r : raw) r.keep();
   }
   SETD_HIP(hipStreamSynchronize(s));
   return SETD_OK;
@@ -938,6 +1029,7 @@ int setd_release_workspace(void) {
   hipMemPool_t pool;
   SETD_HIP(hipDeviceGetDefaultMemPool(&pool, dev));
   SETD_HIP(hipMemPoolTrimTo(pool, 0));
+  SETD_TRY(device_release_kept(dev));
   return phi_release_workspace(dev);
 }
 
@@ -1231,7 +1323,7 @@ int setd_ctx_create(setd_ctx** out, int d, const int64_t* dims, int ncomp, const
 int setd_ctx_destroy(setd_ctx* ctx) {
   clear_error();
   if (!ctx) return SETD_OK;
-  (void)hipDeviceSynchronize();
+  if (hipDeviceSynchronize() == hipSuccess) ctx->keep_memory();
   delete ctx;
   return SETD_OK;
 }
