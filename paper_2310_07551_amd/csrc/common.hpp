@@ -175,12 +175,9 @@ int launch_modeB_f64(ModeJobs& jobs, hipStream_t s, bool raw = false);
 int launch_mode1_lp(ModeJobs& jobs, int prec, DType out, hipStream_t s);
 int launch_modeB_lp(ModeJobs& jobs, int prec, DType out, hipStream_t s);
 
-// Tile bookkeeping shared by the launchers and the batched work lists:
-// fills tiles_i / tiles_a / tile_begin for a TM x TN tile (16 TM rows of the
-// MFMA row index, 16 TN columns) and returns the total tile count.
-int64_t assign_tiles(ModeJob* jobs, int njobs, bool mode1, int TM, int TN);
-// The same for the FP64 kernels: blocks of 16 ti values of i and 16 to of the
-// other index (b in mode 1, a and b together else).
+// Tile bookkeeping shared by the launchers and the batched work lists: fills
+// tiles_i and tile_begin for tiles of 16 ti values of i and 16 to of the other
+// index (b in mode 1, a and b together else) and returns the number of tiles.
 int64_t assign_tiles_f64(ModeJob* jobs, int njobs, bool mode1, int ti, int to);
 
 // A work list in device memory (FP64): one persistent launch walks all tiles
@@ -218,7 +215,7 @@ struct PackJob {
 };
 int pack_matrices_f64(const PackJob* jobs, int count, int n, hipStream_t s);
 int pack_matrix_f32(const double* M, int n, double scale, bool mode1, float* out, hipStream_t s);
-int pack_matrix_bf16(const double* M, int n, double scale, bool rowmajor, int np, void* out, hipStream_t s);
+int pack_matrix_bf16(const double* M, int n, double scale, int np, void* out, hipStream_t s);
 inline bool is_prec(int p) {
   return p == SETD_PREC_F64 || p == SETD_PREC_F32 || p == SETD_PREC_BF16X3 || p == SETD_PREC_BF16X2 ||
          p == SETD_PREC_I8X4;

@@ -781,23 +781,6 @@ int64_t assign_tiles_f64(ModeJob* jobs, int njobs, bool mode1, int ti, int to) {
   return tot;
 }
 
-int64_t assign_tiles(ModeJob* jobs, int njobs, bool mode1, int TM, int TN) {
-  int64_t tot = 0;
-  for (int j = 0; j < njobs; ++j) {
-    ModeJob& jb = jobs[j];
-    if (mode1) {
-      jb.tiles_i = (int)ceil_div(jb.n, 16 * TM);
-      jb.tiles_a = (int)ceil_div(jb.nb, 16 * TN);     // tiles along b
-    } else {
-      jb.tiles_i = (int)ceil_div(jb.n, 16 * TN);
-      jb.tiles_a = (int)ceil_div(jb.na, 16 * TM);
-    }
-    jb.tile_begin = tot;
-    tot += (int64_t)jb.tiles_i * jb.tiles_a * (mode1 ? 1 : jb.nb);
-  }
-  return tot;
-}
-
 namespace {
 
 bool aligned(const void* p, uintptr_t a) { return ((uintptr_t)p % a) == 0; }

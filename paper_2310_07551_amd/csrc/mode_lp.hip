@@ -20,18 +20,13 @@
 // tile row 4 g + r in register r of lane (g, l); in the bf16 form lane (g, l)
 // supplies A[l][8 g + j] and B[8 g + j][l] in slot j.
 //
-// mode 1 (contraction index contiguous):  MFMA rows = i (matrix, packed
-//   row-major), columns = b (tensor columns), k = p.
-// modes >= 2:  MFMA rows = a (contiguous tensor index), columns = i, k = p;
-//   the FP32 form reads the matrix column-major packed, the bf16 form
-//   row-major packed (it needs 8 consecutive p of one row per lane).
-#include <cstring>
-
-#include "common.hpp"
-
+// Every mode has MFMA rows = i (matrix, packed tile by tile in the order the
+// lanes read it), columns = the other index, k = p.
 #include <algorithm>
 #include <cstdio>
 #include <cstdlib>
+
+#include "common.hpp"
 
 namespace setd {
 namespace {
@@ -75,17 +70,19 @@ __device__ __forceinline__ f4 mfma_bf(const bf8& a, const bf8& b, f4 c) {
 // (NP = 2) or <= 2^-16 (NP = 3) chain in their own, 2^8 times smaller,
 // accumulator `small` (unscaled; the caller applies the term's scale to it
 // once).  `main` receives sc * (chunk of h*h).
-template <int NP>
-__device__ __forceinline__ void mfma_split(const bf8 (&a)[NP], const bf8 (&b)[NP], float sc, f4& main,
-                                           f4& small) {
+// p: matrix pieces, x: tensor pieces.  Of two cross products of one order the
+// first is the one with the leading piece of the matrix in mode 1, of the
+// tensor in modes >= 2.
+template <int NP, bool M1>
+__device__ __forceinline__ void mfma_split(const bf8 (&p)[NP], const bf8 (&x)[NP], float sc, f4& main, f4& small) {
   if constexpr (NP == 3) {
-    small = mfma_bf(a[1], b[1], small);
-    small = mfma_bf(a[0], b[2], small);
-    small = mfma_bf(a[2], b[0], small);
+    small = mfma_bf(p[1], x[1], small);
+    small = M1 ? mfma_bf(p[0], x[2], small) : mfma_bf(p[2], x[0], small);
+    small = M1 ? mfma_bf(p[2], x[0], small) : mfma_bf(p[0], x[2], small);
   }
-  small = mfma_bf(a[0], b[1], small);
-  small = mfma_bf(a[1], b[0], small);
-  main += sc * mfma_bf(a[0], b[0], f4{0.f, 0.f, 0.f, 0.f});
+  small = M1 ? mfma_bf(p[0], x[1], small) : mfma_bf(p[1], x[0], small);
+  small = M1 ? mfma_bf(p[1], x[0], small) : mfma_bf(p[0], x[1], small);
+  main += sc * mfma_bf(p[0], x[0], f4{0.f, 0.f, 0.f, 0.f});
 }
 
 // Writes `cnt` consecutive results starting at Y + off (all in range when
@@ -439,278 +436,264 @@ __global__ void __launch_bounds__(512, 1) mode1_lds32_kernel(const ModeJobs J, i
 }
 
 // ---------------------------------------------------------------------------
-// MODE as for the modes >= 2 kernel (2: n % 32 == 0, nb % (16 TN) == 0).
-// One wave per SIMD: bounding these kernels to two (128 registers) made them
-// spill and run at a fifth of the speed (3D FHN 256^3: 26 against 115 steps/s).
-template <int NP, int TM, int TN, int MODE, typename TOut>
-__global__ void __launch_bounds__(64) mode1_bf16_kernel(const ModeJobs J, int64_t per_xcd) {
-  constexpr bool VEC = MODE >= 1;
-  const int64_t t = remap_xcd_lp(blockIdx.x, per_xcd);
-  if (t >= J.total_tiles) return;
+// BF16 splits
+// ---------------------------------------------------------------------------
+// The FP32 kernel's tiling and addressing with chunks of 32 p (lane (g, l)
+// holds p = 32 c + 8 g + j in both operands) and the tensor operand split in
+// registers.  Packed matrix: plane k, entry (tile t, chunk c, lane, j) = piece
+// k of M[16 t + l][p], zero past n.  SUM: jobs of several terms, whose cross
+// products are scaled term by term.  Tiles of 8 blocks or more run one wave per
+// SIMD: bounded to two (256 registers) they spill (3D FHN 256^3: 26 against
+// 115 steps/s).
+template <int NP, bool M1, bool V, bool SUM, int TI, int TO, typename Off, typename TOut>
+__global__ void __launch_bounds__(256, TI * TO >= 8 ? 1 : 2) mode_bf16_kernel(const ModeJobs J, int64_t per_xcd) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const uint32_t t = (uint32_t)remap_xcd_lp(blockIdx.x, per_xcd) * 4 + wave;
+  if (t >= (uint32_t)J.total_tiles) return;
   const ModeJob& jb = J.job[find_job_lp(J, t)];
-  const int64_t lt = t - jb.tile_begin;
-  const int it = (int)(lt % jb.tiles_i);
-  const int64_t bt = lt / jb.tiles_i;
-  const int lane = threadIdx.x, g = lane >> 4, l = lane & 15;
-  const int n = jb.n, ldp = jb.ldp;
-  const int64_t nb = jb.nb;
-  const int64_t plane = (int64_t)ldp * ldp;
-  const int i0 = it * 16 * TM;
-  const int64_t b0 = bt * 16 * TN;
-  const float* __restrict__ X = (const float*)jb.X[0];
-  const __bf16* __restrict__ PH = (const __bf16*)jb.P[0];
-  const float sc = (float)jb.scale[0];
-
-  int64_t poff[TM];
+  const uint32_t lt = t - (uint32_t)jb.tile_begin;
+  const int g = lane >> 4, l = lane & 15;
+  const int n = jb.n, nch = (n + 31) >> 5, nfull = n >> 5;
+  const uint32_t ti = (uint32_t)jb.tiles_i;
+  const uint32_t ot = lt / ti;
+  const int t0 = (int)(lt - ot * ti) * TI;
+  const int64_t na = M1 ? 1 : jb.na;
+  const int64_t ext = M1 ? jb.nb : na * jb.nb;
+  const int64_t q0 = (int64_t)ot * (16 * TO);
+  const uint32_t b0 = M1 || jb.nb == 1 ? 0 : (uint32_t)((uint64_t)q0 / (uint32_t)na);
+  const int64_t r0 = q0 - (int64_t)b0 * na;   // a of the tile's first column
+  const int64_t origin = M1 ? q0 * n : (int64_t)b0 * na * n + r0;
+  // element offset of column k of the tile (clamped to the extent) from its first
+  auto column = [&](int k) -> Off {
+    const int64_t rel = min(q0 + k, ext - 1) - q0;
+    if (M1) return (Off)(rel * n);
+    if (jb.nb == 1) return (Off)rel;
+    const Off q = (Off)(r0 + rel);
+    const Off bb = q / (Off)na;
+    return (Off)(bb * (Off)(na * n) + (q - bb * (Off)na) - (Off)r0);
+  };
+  // columns of the lane: 16 o + l, or with V the TO consecutive ones from
+  // TO l on (the last lanes move back to end with the last column; they keep
+  // the first `skip` of theirs to themselves)
+  constexpr int NX = V ? 1 : TO;
+  // the moved lanes of a tile with fewer than TO columns begin before it, so
+  // that with V offsets count from TO elements before the tile's first
+  constexpr int kBack = V ? TO : 0;
+  typedef float fv __attribute__((ext_vector_type(TO), aligned(4)));
+  const int k0 = V ? (int)(min(q0 + TO * l, ext - TO) - q0) : 0, skip = TO * l - k0;
+  Off xo[NX];   // byte offset of the lane's first element of each column block
 #pragma unroll
-  for (int m = 0; m < TM; ++m) poff[m] = (int64_t)(i0 + TM * l + m) * ldp + 8 * g;
-  const float* pb[TN];
-  bool vb[TN];
+  for (int o = 0; o < NX; ++o) xo[o] = (column(V ? k0 : 16 * o + l) + (Off)kBack + (M1 ? (Off)(8 * g) : (Off)na * (Off)(8 * g))) * 4;
+  f4 acc[TI][TO], accs[TI][TO], acct[SUM ? TI : 1][SUM ? TO : 1];   // leading, cross, finished terms' cross products
 #pragma unroll
-  for (int u = 0; u < TN; ++u) {
-    const int64_t b = b0 + 16 * u + l;
-    vb[u] = b < nb;
-    pb[u] = X + (vb[u] ? b : 0) * (int64_t)n + 8 * g;
-  }
-  f4 acc[TM][TN], accs[TM][TN];   // leading and cross products (see mfma_split)
+  for (int i = 0; i < TI; ++i)
 #pragma unroll
-  for (int m = 0; m < TM; ++m)
+    for (int o = 0; o < TO; ++o) {
+      acc[i][o] = accs[i][o] = f4{0.f, 0.f, 0.f, 0.f};
+      if constexpr (SUM) acct[i][o] = f4{0.f, 0.f, 0.f, 0.f};
+    }
+  __builtin_amdgcn_s_setprio(1);   // products ahead of another wave's epilogue on the SIMD
+  const int nterms = SUM ? jb.nterms : 1;
+  const int nt = (n + 15) >> 4;    // tiles of i
+  const int64_t plane = (int64_t)nt * nch * 512;
+  float sc = 0.f;
+  for (int term = 0; term < nterms; ++term) {
+    const float* __restrict__ x0 = (const float*)jb.X[term] + (origin - kBack);
+    sc = (float)jb.scale[term];
+    const __bf16* at[TI];
 #pragma unroll
-    for (int u = 0; u < TN; ++u) acc[m][u] = accs[m][u] = f4{0.f, 0.f, 0.f, 0.f};
-
-  // One chunk = 32 p: the matrix pieces and the tensor operand's 8 p values
-  // per lane in FP32; chunks alternate between two register sets so that
-  // each is loaded one chunk of MFMAs before use.
-  auto ldc = [&](int p0, bf8 (&ap)[TM][NP], f8 (&xr)[TN]) {
+    for (int i = 0; i < TI; ++i)
+      at[i] = (const __bf16*)jb.P[term] + (int64_t)min(t0 + i, nt - 1) * nch * 512 + 8 * lane;
+    auto load_m = [&](int c, bf8 (&pr)[TI][NP]) {
 #pragma unroll
-    for (int m = 0; m < TM; ++m)
+      for (int i = 0; i < TI; ++i)
 #pragma unroll
-      for (int k = 0; k < NP; ++k) ap[m][k] = *(const bf8*)(PH + k * plane + poff[m] + p0);
-    const bool full = MODE == 2 || (VEC && (p0 + 32 <= n));
+        for (int k = 0; k < NP; ++k) pr[i][k] = *(const bf8*)(at[i] + k * plane + (int64_t)c * 512);
+    };
+    auto load = [&](int c, f8 (&xr)[TO], bf8 (&pr)[TI][NP]) {
+      load_m(c, pr);
+      if constexpr (M1) {
+        const char* xb = (const char*)(x0 + 32 * c);
 #pragma unroll
-    for (int u = 0; u < TN; ++u) {
-      if (MODE == 2 || (full && vb[u])) {
-        xr[u] = *(const f8*)(pb[u] + p0);
+        for (int o = 0; o < TO; ++o) {
+          const f4 lo = *(const f4u*)(xb + xo[o]), hi = *(const f4u*)(xb + xo[o] + 16);
+          xr[o] = f8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+        }
       } else {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) xr[u][e] = (vb[u] && p0 + 8 * g + e < n) ? pb[u][p0 + e] : 0.f;
-      }
-    }
-  };
-  auto cmp = [&](const bf8 (&ap)[TM][NP], const f8 (&xr)[TN]) {
-    bf8 bp[TN][NP];
+        for (int j = 0; j < 8; ++j) {
+          const char* xb = (const char*)(x0 + na * (32 * (int64_t)c + j));
+          if constexpr (V) {
+            const fv v = *(const fv*)(xb + xo[0]);
 #pragma unroll
-    for (int u = 0; u < TN; ++u) split_bf16<NP>(xr[u], bp[u]);
+            for (int o = 0; o < TO; ++o) xr[o][j] = v[o];
+          } else {
 #pragma unroll
-    for (int m = 0; m < TM; ++m)
-#pragma unroll
-      for (int u = 0; u < TN; ++u) mfma_split<NP>(ap[m], bp[u], sc, acc[m][u], accs[m][u]);
-  };
-  bf8 a0[TM][NP], a1[TM][NP];
-  f8 x0[TN], x1[TN];
-  ldc(0, a0, x0);
-  int p0 = 0;
-  for (; p0 + 32 < n; p0 += 64) {
-    ldc(p0 + 32, a1, x1);
-    __builtin_amdgcn_sched_barrier(0);
-    cmp(a0, x0);
-    ldc(p0 + 64 < n ? p0 + 64 : p0, a0, x0);   // the last one re-reads a valid chunk
-    __builtin_amdgcn_sched_barrier(0);
-    cmp(a1, x1);
-  }
-  if (p0 < n) cmp(a0, x0);
-  TOut* __restrict__ Y = (TOut*)jb.Y;
-  const double* __restrict__ base = (const double*)jb.base;
-  const int ir = i0 + 4 * TM * g;
-#pragma unroll
-  for (int u = 0; u < TN; ++u) {
-    if (!vb[u]) continue;
-    float v[4 * TM];
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-#pragma unroll
-      for (int m = 0; m < TM; ++m) v[TM * r + m] = acc[m][u][r] + sc * accs[m][u][r];
-    store_run<TOut>(Y, base, (b0 + 16 * u + l) * (int64_t)n + ir, v, 4 * TM, n - ir, VEC);
-  }
-}
-
-// ---------------------------------------------------------------------------
-// BF16x3, modes >= 2
-// ---------------------------------------------------------------------------
-// MODE 0: masked element loads; 1: vector loads; 2: additionally every tile
-// interior and n % 32 == 0 (no masks in the k loop).
-template <int NP, int TM, int TN, int MODE, typename TOut>
-__global__ void __launch_bounds__(64) modeB_bf16_kernel(const ModeJobs J, int64_t per_xcd) {
-  constexpr bool VEC = MODE >= 1;
-  const int64_t t = remap_xcd_lp(blockIdx.x, per_xcd);
-  if (t >= J.total_tiles) return;
-  const ModeJob& jb = J.job[find_job_lp(J, t)];
-  const int64_t lt = t - jb.tile_begin;
-  const int it = (int)(lt % jb.tiles_i);
-  const int64_t rest = lt / jb.tiles_i;
-  const int64_t at = rest % jb.tiles_a;
-  const int64_t b = rest / jb.tiles_a;
-  const int lane = threadIdx.x, g = lane >> 4, l = lane & 15;
-  const int n = jb.n, ldp = jb.ldp, nterms = jb.nterms;
-  const int64_t na = jb.na;
-  const int64_t plane = (int64_t)ldp * ldp;
-  const int64_t a0 = at * 16 * TM;
-  const int i0 = it * 16 * TN;
-  const int64_t arow = a0 + TM * l;
-  const bool lane_full = arow + TM <= na;
-  f4 acc[TM][TN], accs[TM][TN];   // leading and cross products (see mfma_split)
-#pragma unroll
-  for (int m = 0; m < TM; ++m)
-#pragma unroll
-    for (int u = 0; u < TN; ++u) acc[m][u] = accs[m][u] = f4{0.f, 0.f, 0.f, 0.f};
-  const int64_t slab = na * (int64_t)n * b;
-  f4 acct[TM][TN];   // scaled cross products of the finished terms
-#pragma unroll
-  for (int m = 0; m < TM; ++m)
-#pragma unroll
-    for (int u = 0; u < TN; ++u) acct[m][u] = f4{0.f, 0.f, 0.f, 0.f};
-  for (int term = 0; term < nterms; ++term) {
-    const float* __restrict__ xb = (const float*)jb.X[term] + slab + arow;
-    const __bf16* __restrict__ PH = (const __bf16*)jb.P[term];
-    const float sc = (float)jb.scale[term];
-    if (term > 0) {
-#pragma unroll
-      for (int m = 0; m < TM; ++m)
-#pragma unroll
-        for (int u = 0; u < TN; ++u) accs[m][u] = f4{0.f, 0.f, 0.f, 0.f};
-    }
-    // One chunk = 32 p: the tensor operand's 8 p values (8 g + j) x TM rows
-    // per lane in FP32 and the matrix pieces; chunks alternate between two
-    // register sets so that each is loaded one chunk of MFMAs before use.
-    auto ldc = [&](int p0, f8 (&xm)[TM], bf8 (&bp)[TN][NP]) {
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int p = p0 + 8 * g + j;
-        const bool vp = MODE == 2 || p < n;
-        const float* xs = xb + na * (int64_t)p;
-        if (VEC && TM == 4 && (MODE == 2 || (lane_full && vp))) {
-          const f4 v = *(const f4*)xs;
-#pragma unroll
-          for (int m = 0; m < TM; ++m) xm[m][j] = v[m];
-        } else if (VEC && TM == 2 && (MODE == 2 || (lane_full && vp))) {
-          const f2 v = *(const f2*)xs;
-#pragma unroll
-          for (int m = 0; m < TM; ++m) xm[m][j] = v[m];
-        } else {
-#pragma unroll
-          for (int m = 0; m < TM; ++m) xm[m][j] = (vp && arow + m < na) ? xs[m] : 0.f;
+            for (int o = 0; o < TO; ++o) xr[o][j] = *(const float*)(xb + xo[o]);
+          }
         }
       }
+    };
+    // the last n % 32 values of p: clamped loads, zero past n
+    auto load_tail = [&](f8 (&xr)[TO], bf8 (&pr)[TI][NP]) {
+      load_m(nfull, pr);
 #pragma unroll
-      for (int u = 0; u < TN; ++u) {
-        const int64_t off = (int64_t)(i0 + TN * l + u) * ldp + p0 + 8 * g;
+      for (int j = 0; j < 8; ++j) {
+        const int p = 32 * nfull + 8 * g + j;
+        const float* xp = x0 + (M1 ? 1 : na) * (min(p, n - 1) - 8 * g);   // xo holds the lane's part
 #pragma unroll
-        for (int k = 0; k < NP; ++k) bp[u][k] = *(const bf8*)(PH + k * plane + off);
+        for (int o = 0; o < TO; ++o) {
+          const float v = *(const float*)((const char*)(V ? xp + o : xp) + xo[V ? 0 : o]);
+          xr[o][j] = p < n ? v : 0.f;
+        }
       }
     };
-    auto cmp = [&](const f8 (&xm)[TM], const bf8 (&bp)[TN][NP]) {
-      bf8 ap[TM][NP];
+    auto mma = [&](const f8 (&xr)[TO], const bf8 (&pr)[TI][NP]) {
+      bf8 xp[TO][NP];
 #pragma unroll
-      for (int m = 0; m < TM; ++m) split_bf16<NP>(xm[m], ap[m]);
+      for (int o = 0; o < TO; ++o) split_bf16<NP>(xr[o], xp[o]);
 #pragma unroll
-      for (int m = 0; m < TM; ++m)
+      for (int i = 0; i < TI; ++i)
 #pragma unroll
-        for (int u = 0; u < TN; ++u) mfma_split<NP>(ap[m], bp[u], sc, acc[m][u], accs[m][u]);
+        for (int o = 0; o < TO; ++o) mfma_split<NP, M1>(pr[i], xp[o], sc, acc[i][o], accs[i][o]);
     };
-    f8 x0[TM], x1[TM];
-    bf8 q0[TN][NP], q1[TN][NP];
-    ldc(0, x0, q0);
-    int p0 = 0;
-    for (; p0 + 32 < n; p0 += 64) {
-      ldc(p0 + 32, x1, q1);
+    // chunks alternate between two register sets, each loaded one chunk ahead
+    f8 xa[TO], xc[TO];
+    bf8 pa[TI][NP], pc[TI][NP];
+    if (nfull > 0) load(0, xa, pa);
+    int c = 0;
+    for (; c + 2 <= nfull; c += 2) {
+      load(c + 1, xc, pc);
       __builtin_amdgcn_sched_barrier(0);
-      cmp(x0, q0);
-      ldc(p0 + 64 < n ? p0 + 64 : p0, x0, q0);   // the last one re-reads a valid chunk
+      mma(xa, pa);
+      load(min(c + 2, nfull - 1), xa, pa);   // the last one re-reads a valid chunk: no branch
       __builtin_amdgcn_sched_barrier(0);
-      cmp(x1, q1);
+      mma(xc, pc);
     }
-    if (p0 < n) cmp(x0, q0);
+    const bool tail = nch > nfull;
+    if (tail) load_tail(xc, pc);
+    if (c < nfull) mma(xa, pa);
+    if (tail) mma(xc, pc);
+    if constexpr (SUM) {
 #pragma unroll
-    for (int m = 0; m < TM; ++m)
+      for (int i = 0; i < TI; ++i)
 #pragma unroll
-      for (int u = 0; u < TN; ++u) acct[m][u] += sc * accs[m][u];
+        for (int o = 0; o < TO; ++o) {
+          acct[i][o] += sc * accs[i][o];
+          accs[i][o] = f4{0.f, 0.f, 0.f, 0.f};
+        }
+    }
   }
-  TOut* __restrict__ Y = (TOut*)jb.Y;
+  __builtin_amdgcn_s_setprio(0);
+  // one value: mode 1 adds the scaled cross products in one rounding, modes >= 2
+  // round them first
+  auto value = [&](int i, int o, int r) {
+    if constexpr (M1) return acc[i][o][r] + sc * accs[i][o][r];
+    else if constexpr (SUM) return acc[i][o][r] + acct[i][o][r];
+    else return acc[i][o][r] + __builtin_fmaf(sc, accs[i][o][r], 0.f);
+  };
+  const int imax = n - 16 * t0;                               // i of the tile below it
+  const int omax = (int)min(ext - q0, (int64_t)(16 * TO));    // columns of the tile
   const double* __restrict__ base = (const double*)jb.base;
-  const int64_t ar = a0 + 4 * TM * g;
+  if constexpr (M1) {
+    TOut* __restrict__ Y = (TOut*)jb.Y + origin + 16 * t0;
+    const double* __restrict__ bs = base + origin + 16 * t0;
 #pragma unroll
-  for (int u = 0; u < TN; ++u) {
-    const int i = i0 + TN * l + u;
-    if (i >= n) continue;
-    float v[4 * TM];
+    for (int o = 0; o < TO; ++o) {
+      if (16 * o + l >= omax) continue;
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
+      for (int i = 0; i < TI; ++i) {
+        const int i0 = 16 * i + 4 * g;
+        const int64_t at = (int64_t)(16 * o + l) * n + i0;
+        const f4 v = f4{value(i, o, 0), value(i, o, 1), value(i, o, 2), value(i, o, 3)};
+        if constexpr (sizeof(TOut) == 4) {
+          if (i0 + 4 <= imax) {
+            *(f4u*)(Y + at) = v;
+            continue;
+          }
+        }
 #pragma unroll
-      for (int m = 0; m < TM; ++m) v[TM * r + m] = acc[m][u][r] + acct[m][u][r];
-    store_run<TOut>(Y, base, slab + na * (int64_t)i + ar, v, 4 * TM, (int)(na - ar < 4 * TM ? na - ar : 4 * TM),
-                    VEC);
+        for (int r = 0; r < 4; ++r)
+          if (i0 + r < imax) Y[at + r] = sizeof(TOut) == 8 && base ? (TOut)((double)v[r] + bs[at + r]) : (TOut)v[r];
+      }
+    }
+  } else {
+    TOut* __restrict__ Y = (TOut*)jb.Y + (origin - kBack) + na * 16 * t0;
+    const double* __restrict__ bs = base + (origin - kBack) + na * 16 * t0;
+    Off yo[NX];
+#pragma unroll
+    for (int o = 0; o < NX; ++o) yo[o] = column(V ? k0 : 16 * o + l) + (Off)kBack;
+#pragma unroll
+    for (int i = 0; i < TI; ++i) {
+      // the base values of a block of rows are read together, from clamped
+      // indices, so that they are one wait and not one each
+      double bv[4][TO];
+      if (sizeof(TOut) == 8 && base) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int o = 0; o < TO; ++o)
+            bv[r][o] = bs[min(16 * i + 4 * g + r, imax - 1) * na + yo[V ? 0 : o] + (V ? o : 0)];
+      } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int o = 0; o < TO; ++o) bv[r][o] = -0.0;   // the sum is then the product itself
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = 16 * i + 4 * g + r;
+        if (row >= imax) continue;
+        TOut w[TO];
+#pragma unroll
+        for (int o = 0; o < TO; ++o) {
+          const float v = value(i, o, r);
+          w[o] = sizeof(TOut) == 8 ? (TOut)((double)v + bv[r][o]) : (TOut)v;
+        }
+        if constexpr (V) {
+          typedef TOut tv __attribute__((ext_vector_type(TO), aligned(sizeof(TOut))));
+          TOut* y = Y + row * na + yo[0];
+          if (skip == 0) {
+            tv x;
+#pragma unroll
+            for (int o = 0; o < TO; ++o) x[o] = w[o];
+            *(tv*)y = x;
+          } else {
+#pragma unroll
+            for (int o = 0; o < TO; ++o)
+              if (o >= skip) y[o] = w[o];
+          }
+        } else {
+#pragma unroll
+          for (int o = 0; o < TO; ++o)
+            if (16 * o + l < omax) Y[row * na + yo[o]] = w[o];
+        }
+      }
+    }
   }
-}
-
-int finish_tiles_lp(ModeJobs& J, bool mode1, int TM, int TN) {
-  const int64_t tot = assign_tiles(J.job, J.njobs, mode1, TM, TN);
-  J.total_tiles = tot;
-  J.tiles_per_job = J.njobs > 0 ? tot / J.njobs : 0;
-  for (int j = 0; j < J.njobs; ++j)
-    if (J.job[j].tile_begin != (int64_t)j * J.tiles_per_job) J.tiles_per_job = 0;
-  return SETD_OK;
 }
 
 bool aligned_lp(const void* p, uintptr_t a) { return ((uintptr_t)p % a) == 0; }
 
-// bf16 wave tiles (rows x columns of 16): 4 x 4 on the interior path (one
-// wave per SIMD; swept at 3D FHN 256^3: BF16x3 113 steps/s against 97 for
-// 4 x 2 / 2 x 4 and 78 for 2 x 4 / 2 x 2), smaller ones on the masked paths,
-// whose larger register needs would spill at 4 x 4.
-constexpr int kTM1 = 4, kTN1 = 4;     // mode 1, interior
-constexpr int kTM1s = 4, kTN1s = 2;   // mode 1, masked
-constexpr int kTMB = 4, kTNB = 4;     // modes >= 2, interior
-constexpr int kTMBs = 2, kTNBs = 2;   // modes >= 2, masked
-
-}  // namespace
-
-namespace {
-
-template <int MODE, typename T>
-void go_mode1(int prec, dim3 grid, hipStream_t s, const ModeJobs& J, int64_t per) {
-  constexpr int TM = MODE == 2 ? kTM1 : kTM1s, TN = MODE == 2 ? kTN1 : kTN1s;
-  if (prec == SETD_PREC_BF16X3)
-    hipLaunchKernelGGL((mode1_bf16_kernel<3, TM, TN, MODE, T>), grid, dim3(64), 0, s, J, per);
-  else
-    hipLaunchKernelGGL((mode1_bf16_kernel<2, TM, TN, MODE, T>), grid, dim3(64), 0, s, J, per);
+// A tile's byte offsets span more than 32 bits.
+bool big_tiles(const ModeJobs& J) {
+  for (int j = 0; j < J.njobs; ++j) {
+    const ModeJob& jb = J.job[j];
+    if (jb.na > (int64_t(1) << 26) / 8 || (jb.nb > 1 && (ceil_div(64, jb.na) + 1) * jb.na * jb.n > (int64_t(1) << 28)))
+      return true;
+  }
+  return false;
 }
 
-template <int MODE, typename T>
-void go_modeB(int prec, dim3 grid, hipStream_t s, const ModeJobs& J, int64_t per) {
-  constexpr int TM = MODE == 2 ? kTMB : kTMBs, TN = MODE == 2 ? kTNB : kTNBs;
-  if (prec == SETD_PREC_BF16X3)
-    hipLaunchKernelGGL((modeB_bf16_kernel<3, TM, TN, MODE, T>), grid, dim3(64), 0, s, J, per);
-  else
-    hipLaunchKernelGGL((modeB_bf16_kernel<2, TM, TN, MODE, T>), grid, dim3(64), 0, s, J, per);
+// A lane's `to` neighbouring columns are neighbours in memory: no slab ends
+// between them.
+bool vector_columns(const ModeJobs& J, int to) {
+  for (int j = 0; j < J.njobs; ++j) {
+    const ModeJob& jb = J.job[j];
+    if (jb.nb == 1 ? jb.na < to : jb.na % to != 0) return false;
+  }
+  return true;
 }
-
-template <typename T>
-void go_mode1_m(int mode, int prec, dim3 grid, hipStream_t s, const ModeJobs& J, int64_t per) {
-  if (mode == 2) go_mode1<2, T>(prec, grid, s, J, per);
-  else if (mode == 1) go_mode1<1, T>(prec, grid, s, J, per);
-  else go_mode1<0, T>(prec, grid, s, J, per);
-}
-
-template <typename T>
-void go_modeB_m(int mode, int prec, dim3 grid, hipStream_t s, const ModeJobs& J, int64_t per) {
-  if (mode == 2) go_modeB<2, T>(prec, grid, s, J, per);
-  else if (mode == 1) go_modeB<1, T>(prec, grid, s, J, per);
-  else go_modeB<0, T>(prec, grid, s, J, per);
-}
-
-}  // namespace
-
-namespace {
 
 // Tiles of the FP32 kernel {blocks of i, of the other index}, and the part of
 // the matrix-core rate that their loop reaches in mode 1 and in modes >= 2.
@@ -834,12 +817,7 @@ int launch_modeB_f32c(ModeJobs& J, DType out, hipStream_t s) {
   if (J.njobs == 0) return SETD_OK;
   double fl = 0.0, by = 0.0;
   if (prof_on()) job_work(J, 4, out == DType::F64 ? 8 : 4, 4, fl, by);
-  bool big = false;   // a tile's byte offsets span more than 32 bits
-  for (int j = 0; j < J.njobs; ++j) {
-    const ModeJob& jb = J.job[j];
-    big = big || jb.na > (int64_t(1) << 26) ||
-          (jb.nb > 1 && (ceil_div(64, jb.na) + 1) * jb.na * jb.n > (int64_t(1) << 28));
-  }
+  const bool big = big_tiles(J);
   const TileF32 cfg = big ? kTilesF32[2] : tile_f32(J, false);
   finish_tiles_f32(J, false, cfg);
   if (J.total_tiles == 0) return SETD_OK;
@@ -847,64 +825,110 @@ int launch_modeB_f32c(ModeJobs& J, DType out, hipStream_t s) {
   if (big)
     return out == DType::F32 ? launch_tile_f32<false, false, 4, 2, uint64_t, float>(J, s)
                              : launch_tile_f32<false, false, 4, 2, uint64_t, double>(J, s);
-  // a lane's neighbouring columns are neighbours in memory where no slab ends
-  // between them
-  bool vec = true;
-  for (int j = 0; j < J.njobs; ++j) {
-    const ModeJob& jb = J.job[j];
-    vec = vec && (jb.nb == 1 ? jb.na >= cfg.to : jb.na % cfg.to == 0);
-  }
+  const bool vec = vector_columns(J, cfg.to);
   if (vec) return out == DType::F32 ? launch_f32<false, true, float>(J, cfg, s) : launch_f32<false, true, double>(J, cfg, s);
   return out == DType::F32 ? launch_f32<false, false, float>(J, cfg, s) : launch_f32<false, false, double>(J, cfg, s);
+}
+
+// Tiles of the bf16 kernel and the part of its rate that their loop reaches
+// (the larger the tile, the less often a value is split and a piece read).
+// Measured, three pieces, 18 jobs: 256^3 mode 1 1.17 ms with 4 x 4, 1.44 with
+// 4 x 2, 1.67 with 2 x 2; 96 x 226 x 66 mode 1 78 us with 4 x 4 (6 tiles of i),
+// 60 with 2 x 2; 128 x 82, 6 jobs 4.4 us with 1 x 1, 11 with 4 x 4.
+constexpr TileF32 kTilesBf16[] = {{1, 1, .25, .25}, {2, 2, .60, .60}, {4, 2, .70, .70}, {4, 4, 1.0, 1.0}};
+
+TileF32 tile_bf16(const ModeJobs& J, bool mode1, int np) {
+  const char* e = std::getenv(mode1 ? "SETD_TILE_BF16_MODE1" : "SETD_TILE_BF16_MODEB");
+  int a = 0, b = 0;
+  if (e && std::sscanf(e, "%dx%d", &a, &b) == 2)
+    for (const TileF32& t : kTilesBf16)
+      if (t.ti == a && t.to == b) return t;
+  TileF32 best = kTilesBf16[0];
+  double bt = 1e300;
+  for (const TileF32& t : kTilesBf16) {
+    double w = 0.0, wave = 0.0;
+    for (int j = 0; j < J.njobs; ++j) {
+      const ModeJob& jb = J.job[j];
+      w += (double)ceil_div(jb.n, 16 * t.ti) * ceil_div(mode1 ? jb.nb : jb.na * jb.nb, 16 * t.to);
+      wave = std::max(wave, t.ti * t.to * ((double)jb.nterms * ceil_div(jb.n, 32) * (np == 3 ? 112.0 : 64.0) / t.rate1 +
+                                           700.0 * (jb.base ? 1.6 : 1.0)));
+    }
+    w /= 1024.0;
+    const double time = ((w < 6.0 ? std::ceil(w) : w) + 0.3) * wave;
+    if (time < bt) {
+      bt = time;
+      best = t;
+    }
+  }
+  return best;
+}
+
+template <int NP, bool M1, bool V, bool SUM, int TI, int TO, typename Off, typename T>
+int launch_tile_bf16(const ModeJobs& J, hipStream_t s) {
+  const int64_t per = ceil_div(ceil_div(J.total_tiles, 4), 8);
+  hipLaunchKernelGGL((mode_bf16_kernel<NP, M1, V, SUM, TI, TO, Off, T>), dim3((unsigned)(per * 8)), dim3(256), 0, s, J,
+                     per);
+  SETD_LAUNCHED();
+  return SETD_OK;
+}
+
+template <int NP, bool M1, bool V, bool SUM, typename T>
+int launch_bf16(const ModeJobs& J, const TileF32& t, hipStream_t s) {
+#define SETD_TILE(TI_, TO_) \
+  if (t.ti == TI_ && t.to == TO_) return launch_tile_bf16<NP, M1, V && (TO_ > 1), SUM, TI_, TO_, uint32_t, T>(J, s);
+  SETD_TILE(1, 1)
+  SETD_TILE(2, 2)
+  SETD_TILE(4, 2)
+  SETD_TILE(4, 4)
+#undef SETD_TILE
+  set_error("unsupported tile %dx%d", t.ti, t.to);
+  return SETD_EUNSUPPORTED;
+}
+
+template <int NP, typename T>
+int launch_modeB_bf16(const ModeJobs& J, const TileF32& t, bool big, bool vec, bool sum, hipStream_t s) {
+  if (big) return launch_tile_bf16<NP, false, false, true, 4, 2, uint64_t, T>(J, s);
+  if (vec) return sum ? launch_bf16<NP, false, true, true, T>(J, t, s) : launch_bf16<NP, false, true, false, T>(J, t, s);
+  return sum ? launch_bf16<NP, false, false, true, T>(J, t, s) : launch_bf16<NP, false, false, false, T>(J, t, s);
 }
 
 }  // namespace
 
 int launch_mode1_lp(ModeJobs& J, int prec, DType out, hipStream_t s) {
   if (prec == SETD_PREC_F32) return launch_mode1_f32c(J, out, s);
-  bool vec = true, interior = true;
-  for (int j = 0; j < J.njobs; ++j) {
-    const ModeJob& jb = J.job[j];
-    vec = vec && (jb.n % 8 == 0) && aligned_lp(jb.X[0], 32) && aligned_lp(jb.Y, 16) && aligned_lp(jb.base, 16);
-    interior = interior && jb.n % 32 == 0 && jb.nb % (16 * kTN1) == 0;
-  }
-  const int mode = vec ? (interior ? 2 : 1) : 0;
-  if (mode == 2) finish_tiles_lp(J, true, kTM1, kTN1);
-  else finish_tiles_lp(J, true, kTM1s, kTN1s);
+  if (J.njobs == 0) return SETD_OK;
+  const bool x3 = prec == SETD_PREC_BF16X3;
+  const TileF32 cfg = tile_bf16(J, true, x3 ? 3 : 2);
+  finish_tiles_f32(J, true, cfg);
   if (J.total_tiles == 0) return SETD_OK;
   double fl = 0.0, by = 0.0;
   if (prof_on()) job_work(J, 4, out == DType::F64 ? 8 : 4, 4, fl, by);
   ProfScope prof(s, kProfMode1LP, fl, by);
-  const int64_t per = ceil_div(J.total_tiles, 8);
-  const dim3 grid((unsigned)(per * 8));
-  if (out == DType::F32) go_mode1_m<float>(mode, prec, grid, s, J, per);
-  else go_mode1_m<double>(mode, prec, grid, s, J, per);
-  SETD_LAUNCHED();
-  return SETD_OK;
+  if (x3)
+    return out == DType::F32 ? launch_bf16<3, true, false, false, float>(J, cfg, s)
+                             : launch_bf16<3, true, false, false, double>(J, cfg, s);
+  return out == DType::F32 ? launch_bf16<2, true, false, false, float>(J, cfg, s)
+                           : launch_bf16<2, true, false, false, double>(J, cfg, s);
 }
 
 int launch_modeB_lp(ModeJobs& J, int prec, DType out, hipStream_t s) {
   if (prec == SETD_PREC_F32) return launch_modeB_f32c(J, out, s);
-  bool vec = true, interior = true;
-  for (int j = 0; j < J.njobs; ++j) {
-    const ModeJob& jb = J.job[j];
-    vec = vec && (jb.na % 4 == 0) && aligned_lp(jb.Y, 16) && aligned_lp(jb.base, 16);
-    for (int t = 0; t < jb.nterms; ++t) vec = vec && aligned_lp(jb.X[t], 16);
-    interior = interior && jb.n % 32 == 0 && jb.na % (16 * kTMB) == 0;
-  }
-  const int mode = vec ? (interior ? 2 : 1) : 0;
-  if (mode == 2) finish_tiles_lp(J, false, kTMB, kTNB);
-  else finish_tiles_lp(J, false, kTMBs, kTNBs);
+  if (J.njobs == 0) return SETD_OK;
+  const bool x3 = prec == SETD_PREC_BF16X3, big = big_tiles(J);
+  const TileF32 cfg = big ? kTilesBf16[2] : tile_bf16(J, false, x3 ? 3 : 2);
+  finish_tiles_f32(J, false, cfg);
   if (J.total_tiles == 0) return SETD_OK;
   double fl = 0.0, by = 0.0;
   if (prof_on()) job_work(J, 4, out == DType::F64 ? 8 : 4, 4, fl, by);
   ProfScope prof(s, kProfModeBLP, fl, by);
-  const int64_t per = ceil_div(J.total_tiles, 8);
-  const dim3 grid((unsigned)(per * 8));
-  if (out == DType::F32) go_modeB_m<float>(mode, prec, grid, s, J, per);
-  else go_modeB_m<double>(mode, prec, grid, s, J, per);
-  SETD_LAUNCHED();
-  return SETD_OK;
+  bool sum = false;
+  for (int j = 0; j < J.njobs; ++j) sum = sum || J.job[j].nterms > 1;
+  const bool vec = vector_columns(J, cfg.to);
+  if (x3)
+    return out == DType::F32 ? launch_modeB_bf16<3, float>(J, cfg, big, vec, sum, s)
+                             : launch_modeB_bf16<3, double>(J, cfg, big, vec, sum, s);
+  return out == DType::F32 ? launch_modeB_bf16<2, float>(J, cfg, big, vec, sum, s)
+                           : launch_modeB_bf16<2, double>(J, cfg, big, vec, sum, s);
 }
 
 }  // namespace setd

@@ -56,9 +56,10 @@ __global__ void pack_f32_kernel(const double* __restrict__ M, int n, double scal
   out[idx] = i < n && p < n ? (float)(scale * M[i + (int64_t)n * p]) : 0.f;
 }
 
-// bf16 split: the packed buffer holds np planes of ldp*ldp bf16 values,
-// plane k the round-to-nearest-even bf16 of what planes 0..k-1 leave of the
-// (FP64) matrix entry, so the entry is ~ the sum of its np pieces.
+// bf16 split: np planes, plane k the round-to-nearest-even bf16 of what planes
+// 0..k-1 leave of the (FP64) matrix entry, so the entry is ~ the sum of its np
+// pieces.  In a plane, entry (tile t, chunk c, lane (g, l), j) is that of
+// M[16 t + l][32 c + 8 g + j], zero past n.
 __device__ __forceinline__ uint16_t f32_to_bf16_rne(float x) {
   uint32_t u = __float_as_uint(x);
   uint32_t lsb = (u >> 16) & 1u;
@@ -67,13 +68,14 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float x) {
 }
 __device__ __forceinline__ float bf16_to_f32(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
-__global__ void pack_bf16_kernel(const double* __restrict__ M, int n, int ldp, double scale, bool rowmajor, int np,
+__global__ void pack_bf16_kernel(const double* __restrict__ M, int n, double scale, int np, int64_t tot,
                                  uint16_t* __restrict__ out) {
   const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t tot = (int64_t)ldp * ldp;
   if (idx >= tot) return;
-  const int r = (int)(idx % ldp), c = (int)(idx / ldp);
-  const int i = rowmajor ? c : r, p = rowmajor ? r : c;
+  const int nch = (n + 31) >> 5;
+  const int e = (int)(idx & 511), g = e >> 7, l = (e >> 3) & 15, j = e & 7;
+  const int64_t tc = idx >> 9;
+  const int i = 16 * (int)(tc / nch) + l, p = 32 * (int)(tc % nch) + 8 * g + j;
   double rem = (i < n && p < n) ? scale * M[i + (int64_t)n * p] : 0.0;
   for (int k = 0; k < np; ++k) {
     const uint16_t h = f32_to_bf16_rne((float)rem);
@@ -120,11 +122,10 @@ int pack_matrix_f32(const double* M, int n, double scale, bool mode1, float* out
   return SETD_OK;
 }
 
-int pack_matrix_bf16(const double* M, int n, double scale, bool rowmajor, int np, void* out, hipStream_t s) {
-  const int ldp = packed_ld(n);
-  const int64_t tot = (int64_t)ldp * ldp;
-  hipLaunchKernelGGL(pack_bf16_kernel, dim3((unsigned)ceil_div(tot, 256)), dim3(256), 0, s, M, n, ldp, scale,
-                     rowmajor, np, (uint16_t*)out);
+int pack_matrix_bf16(const double* M, int n, double scale, int np, void* out, hipStream_t s) {
+  const int64_t tot = ceil_div(n, 16) * ceil_div(n, 32) * 512;
+  hipLaunchKernelGGL(pack_bf16_kernel, dim3((unsigned)ceil_div(tot, 256)), dim3(256), 0, s, M, n, scale, np, tot,
+                     (uint16_t*)out);
   SETD_LAUNCHED();
   return SETD_OK;
 }

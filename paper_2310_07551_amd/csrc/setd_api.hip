@@ -142,7 +142,7 @@ int setd::pack_for(int prec, const double* M, int n, double scale, int mu, void*
   if (prec == SETD_PREC_F64) return pack_matrix_f64(M, n, scale, false, (double*)out, s);
   if (prec == SETD_PREC_F32) return pack_matrix_f32(M, n, scale, mu == 0, (float*)out, s);
   if (prec == SETD_PREC_I8X4) return pack_matrix_i8(M, n, scale, out, s);
-  return pack_matrix_bf16(M, n, scale, true, prec == SETD_PREC_BF16X3 ? 3 : 2, out, s);
+  return pack_matrix_bf16(M, n, scale, prec == SETD_PREC_BF16X3 ? 3 : 2, out, s);
 }
 
 namespace {

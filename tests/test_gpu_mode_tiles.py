@@ -157,3 +157,39 @@ def test_every_f32_tile_sums_terms(dims, monkeypatch):
         e = rel_err(first[c * ctx.N:(c + 1) * ctx.N], np.asarray(ref[c]).ravel(order="F"))
         say("f32 terms", dims, "field", c, "rel_inf %.2e" % e)
         assert e < 1e-3   # the error of FP32 products over a step is checked elsewhere
+
+
+@pytest.mark.parametrize("prec,tol", [(setd.PREC_BF16X3, 1e-5), (setd.PREC_BF16X2, 1e-3)])
+def test_every_bf16_tile_same_bits(prec, tol, monkeypatch):
+    """The bf16 forms as the FP32 ones: the same bits with every tile, single
+    products and sums of terms.  Against the oracle 1e-5 for three pieces
+    (about FP32), 1e-3 for two (2^-16 times sums of up to 300 terms)."""
+    tiles = ["1x1", "2x2", "4x2", "4x4"]
+    for dims in [(3, 5, 2), (32, 32, 32), (31, 100, 5), (34, 9, 33), (113, 7, 1), (1, 300, 2), (33, 50), (64, 130, 18),
+                 (129,), (2, 2), (65, 47, 3)]:
+        T, W0 = wl.random_tensor(dims, 1), wl.random_tensor(dims, 2)
+        Ls = [wl.random_matrix(n, 3 + k, scale=1.0 / np.sqrt(n)) for k, n in enumerate(dims)]
+        ref = 0.7 * oracle.tucker(T, Ls) + W0
+        first = None
+        for tile in tiles:
+            monkeypatch.setenv("SETD_TILE_BF16_MODE1", tile)
+            monkeypatch.setenv("SETD_TILE_BF16_MODEB", tile)
+            W = dev(W0)
+            setd.tucker_apply(dev(T), W, dims, [dev(L) for L in Ls], alpha=0.7, beta=1.0, prec=prec)
+            got = host(W, dims)
+            say("bf16 tile", tile, dims, "rel_inf %.2e" % rel_err(got, ref))
+            assert rel_err(got, ref) < tol, (tile, dims)
+            first = got if first is None else first
+            assert np.array_equal(got, first), (tile, dims)
+    for dims in [(33, 50), (21, 18, 17)]:
+        prob = wl.fhn_3d(dims=dims) if len(dims) == 3 else wl.schnakenberg_2d(*dims)
+        first = None
+        for tile in tiles:
+            monkeypatch.setenv("SETD_TILE_BF16_MODE1", tile)
+            monkeypatch.setenv("SETD_TILE_BF16_MODEB", tile)
+            ctx = setd.Context(dims, [[dev(M) for M in Ac] for Ac in prob.A], prob.tau, prec)
+            u = torch().cat([dev(f) for f in prob.U0])
+            ctx.step(u, 2, prob.g_kind, prob.params)
+            got = u.cpu().numpy()
+            first = got if first is None else first
+            assert np.isfinite(got).all() and np.array_equal(got, first), tile
