@@ -132,14 +132,15 @@ __device__ __forceinline__ void store_run(TOut* __restrict__ Y, const double* __
 //
 // Every size takes the same loop: columns and rows past the end are clamped to
 // the last one (their results are not stored), and the last n % 16 values of p
-// are one chunk, masked, loaded ahead of the loop (loading it in the ring
-// instead needs copies of the loop body, in which the compiler moves the
-// accumulators about: 200^3 3.65 -> 4.2 ms).  In modes >= 2 the TO columns of
-// a lane are neighbours (V), one load for all of them, wherever no slab ends
-// between them; one load each was what bound the large sizes (256^3 last mode
-// 1.78 -> 1.42 ms).  Whole steps against kernels of one 4 x 4 tile that
-// checked every load unless n was a multiple of 32: 200^3 4.83 -> 3.65 ms,
-// 150^3 2.74 -> 1.37, 256^3 8.02 -> 7.5, 100^3 0.52 -> 0.38, 300^2 0.40 -> 0.10.
+// are one masked chunk.  Mode 1 loads it ahead of the loop, modes >= 2 after it:
+// without the registers that hold it 7 x 2 tiles run three waves per SIMD, which
+// takes modes >= 2 from 0.68 to 0.61 ms at 200^3, and mode 1, whose lanes read
+// half-lines of 16 rows that three waves push out of the L1, from 0.64 to 0.97.
+// In modes >= 2 the TO columns of a lane are neighbours (V), one load for all of
+// them, wherever no slab ends between them; one load each was what bound the
+// large sizes (256^3 last mode 1.78 -> 1.42 ms).  Whole steps against kernels of one 4 x 4 tile that
+// checked every load unless n was a multiple of 32: 200^3 4.83 -> 3.40 ms,
+// 150^3 2.74 -> 1.37, 256^3 8.02 -> 7.4, 100^3 0.52 -> 0.38, 300^2 0.40 -> 0.10.
 typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));   // four floats at any address
 
 __device__ __forceinline__ f4 mfma32(float a, float b, f4 c) {
@@ -236,10 +237,8 @@ __global__ void __launch_bounds__(256, 2) mode_f32_kernel(const ModeJobs J, int6
           for (int o = 0; o < TO; ++o) acc[i][o] = mfma32(pv, xr[o][j], acc[i][o]);
         }
     };
-    f4 xr[2][TO], pr[2][TI], xt[TO], pt[TI];
-    const bool tail = nch > nfull;
-    if (nfull > 0) load(0, xr[0], pr[0]);
-    if (tail) {
+    // the last n % 16 values of p: clamped loads, zero past n
+    auto load_tail = [&](f4 (&xt)[TO], f4 (&pt)[TI]) {
       load_m(nfull, pt);
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
@@ -251,6 +250,14 @@ __global__ void __launch_bounds__(256, 2) mode_f32_kernel(const ModeJobs J, int6
           xt[o][j] = p < n ? v : 0.f;
         }
       }
+    };
+    // chunks alternate between two register sets, each loaded one chunk ahead
+    f4 xr[2][TO], pr[2][TI];
+    const bool tail = nch > nfull;
+    if (nfull > 0) load(0, xr[0], pr[0]);
+    f4 xt[M1 ? TO : 1], pt[M1 ? TI : 1];
+    if constexpr (M1) {
+      if (tail) load_tail(xt, pt);
     }
     int c = 0;
     for (; c + 2 <= nfull; c += 2) {
@@ -259,8 +266,14 @@ __global__ void __launch_bounds__(256, 2) mode_f32_kernel(const ModeJobs J, int6
       load(min(c + 2, nfull - 1), xr[0], pr[0]);   // the last one re-reads a valid chunk: no branch
       mma(xr[1], pr[1]);
     }
-    if (c < nfull) mma(xr[0], pr[0]);
-    if (tail) mma(xt, pt);
+    if constexpr (M1) {
+      if (c < nfull) mma(xr[0], pr[0]);
+      if (tail) mma(xt, pt);
+    } else {
+      if (tail) load_tail(xr[1], pr[1]);
+      if (c < nfull) mma(xr[0], pr[0]);
+      if (tail) mma(xr[1], pr[1]);
+    }
   }
   __builtin_amdgcn_s_setprio(0);
   const float sc1 = M1 ? (float)jb.scale[0] : 1.f;
@@ -697,15 +710,16 @@ bool vector_columns(const ModeJobs& J, int to) {
 
 // Tiles of the FP32 kernel {blocks of i, of the other index}, and the part of
 // the matrix-core rate that their loop reaches in mode 1 and in modes >= 2.
-// Measured with 18 jobs: 256^3 modes >= 2 1.42 ms with 8 x 2, 1.48 with 4 x 4
-// (16 tiles of i either way); 200^3 (13 tiles) mode 1 0.64 ms with 7 x 2, 0.68
-// with 5 x 4, 0.75 with 4 x 4; 150^3 (10 tiles) modes >= 2 0.26 ms with 5 x 2,
-// 0.30 with 4 x 4; 500 x 400, 6 jobs 38 us with 1 x 1, 96 with 4 x 4.
+// Measured with 18 jobs: 128^3 modes >= 2 110 us with 4 x 4, 117 with 8 x 2, 140
+// with 4 x 2 (8 tiles of i); 200^3 (13 tiles) mode 1 0.64 ms with 7 x 2, 0.68
+// with 5 x 4, 0.76 with 4 x 4, modes >= 2 0.61, 0.73 and 0.72; 150^3 (10 tiles)
+// modes >= 2 0.25 ms with 5 x 2, 0.29 with 5 x 4; 500 x 400, 6 jobs 38 us with
+// 1 x 1, 96 with 4 x 4.
 struct TileF32 {
   int ti, to;
   double rate1, rateB;
 };
-constexpr TileF32 kTilesF32[] = {{1, 1, .50, .50}, {2, 2, .80, .80}, {4, 2, .85, .90}, {4, 4, .92, .94},
+constexpr TileF32 kTilesF32[] = {{1, 1, .50, .50}, {2, 2, .80, .80}, {4, 2, .85, .90}, {4, 4, .92, .98},
                                  {5, 2, .88, .88}, {5, 4, .95, .87}, {7, 2, .93, .92}, {8, 2, .92, .97}};
 
 // The tile whose launch should take least time, by the model of the FP64
