@@ -164,6 +164,17 @@ struct SlabJobs {
 };
 int launch_slab_f64(SlabJobs& jobs, hipStream_t s, bool raw = false);
 
+// Modes >= 2: whether every `to` neighbouring columns from a multiple of `to`
+// on are neighbours in memory (no slab ends between them), so that a lane can
+// load and store its columns together.
+inline bool vector_columns(const ModeJobs& J, int to) {
+  for (int j = 0; j < J.njobs; ++j) {
+    const ModeJob& jb = J.job[j];
+    if (jb.nb == 1 ? jb.na < to : jb.na % to != 0) return false;
+  }
+  return true;
+}
+
 // Mode-product launchers (implemented in mode_f64.hip / mode_lp.hip).
 // `jobs` is filled by the caller except for the tile fields, which the
 // launcher computes.  All jobs of one launch share regime (mode 1 or not).

@@ -44,7 +44,7 @@
 // against kernels with one fixed tile per contraction length and vector
 // accesses for aligned sizes only: 64^2 107 -> 52 us, 300^2 595 -> 112 us
 // (the last mode alone 151 -> 20 and 9 us), 100^3 739 -> 559 us, 128^3 1060
-// -> 1031 us, 256^3 11.93 -> 11.97 ms.
+// -> 893 us, 256^3 11.93 -> 11.69 ms.
 #include "common.hpp"
 
 #include <algorithm>
@@ -121,8 +121,9 @@ struct MatrixTiles {
 // the chunks lo .. hi - 1.  x0 is the tile's first element, xo[o] the byte
 // offset of the lane's first element of column (row) block o from it; M1:
 // consecutive p are adjacent, else `na` elements apart.
-template <bool M1, bool RAW, int TI, int TO, int D, typename Off>
-__device__ __forceinline__ void add_term(d4 (&acc)[TI][TO], const double* __restrict__ x0, const Off (&xo)[TO],
+template <bool M1, bool RAW, int TI, int TO, int D, typename Off, bool V = false>
+__device__ __forceinline__ void add_term(d4 (&acc)[TI][TO], const double* __restrict__ x0,
+                                         const Off (&xo)[V ? 1 : TO],
                                          int64_t na, const MatrixTiles<RAW, TI>& mat, int n, int lane, int lo,
                                          int hi) {
   const int g = lane >> 4;
@@ -136,10 +137,17 @@ __device__ __forceinline__ void add_term(d4 (&acc)[TI][TO], const double* __rest
     } else {
       const char* xb0 = (const char*)(x0 + na * (8 * (int64_t)c));
       const char* xb1 = (const char*)(x0 + na * (8 * (int64_t)c + 1));
+      if constexpr (V) {
+        typedef double dv __attribute__((ext_vector_type(TO), aligned(8)));
+        const dv v0 = *(const dv*)(xb0 + xo[0]), v1 = *(const dv*)(xb1 + xo[0]);
 #pragma unroll
-      for (int o = 0; o < TO; ++o) xr[o][0] = *(const double*)(xb0 + xo[o]);
+        for (int o = 0; o < TO; ++o) xr[o] = d2{v0[o], v1[o]};
+      } else {
 #pragma unroll
-      for (int o = 0; o < TO; ++o) xr[o][1] = *(const double*)(xb1 + xo[o]);
+        for (int o = 0; o < TO; ++o) xr[o][0] = *(const double*)(xb0 + xo[o]);
+#pragma unroll
+        for (int o = 0; o < TO; ++o) xr[o][1] = *(const double*)(xb1 + xo[o]);
+      }
     }
   };
   auto mma = [&](const d2 (&xr)[TO], const d2 (&pr)[TI]) {
@@ -163,7 +171,8 @@ __device__ __forceinline__ void add_term(d4 (&acc)[TI][TO], const double* __rest
       const int p = 8 * nfull + 2 * g + j;
       const double* xp = x0 + ps * (min(p, n - 1) - 2 * g);   // xo holds the lane's 2 g
 #pragma unroll
-      for (int o = 0; o < TO; ++o) xr[D - 1][o][j] = *(const double*)((const char*)xp + xo[o]);
+      for (int o = 0; o < TO; ++o)
+        xr[D - 1][o][j] = *(const double*)((const char*)(V ? xp + o : xp) + xo[V ? 0 : o]);
 #pragma unroll
       for (int o = 0; o < TO; ++o) xr[D - 1][o][j] = p < n ? xr[D - 1][o][j] : 0.0;
     }
@@ -190,7 +199,7 @@ __device__ __forceinline__ void add_term(d4 (&acc)[TI][TO], const double* __rest
 
 // One wave computes tile `lt` of job `jb` (part kw of ks of its contraction;
 // `red` is the LDS the waves of one tile add up in when ks > 1).
-template <bool M1, bool RAW, int TI, int TO, int D, int KS, typename Off>
+template <bool M1, bool RAW, int TI, int TO, int D, int KS, typename Off, bool V = false>
 __device__ __forceinline__ void mode_tile(const ModeJob& jb, uint32_t lt, int lane, int kw, d4* red) {
   const int g = lane >> 4, l = lane & 15;
   const int n = jb.n;
@@ -216,9 +225,17 @@ __device__ __forceinline__ void mode_tile(const ModeJob& jb, uint32_t lt, int la
     const Off bb = q / (Off)na;
     return (Off)(bb * (Off)(na * n) + (q - bb * (Off)na) - (Off)r0);
   };
-  Off xo[TO];
+  // columns of the lane: 16 o + l, or with V the TO consecutive ones from TO l
+  // on (the last lanes move back to end with the last column; they keep the
+  // first `skip` of theirs to themselves).  The moved lanes of a tile with
+  // fewer than TO columns begin before it: with V offsets count from TO
+  // elements before the tile's first.
+  constexpr int NX = V ? 1 : TO, kBack = V ? TO : 0;
+  const int k0 = V ? (int)(min(q0 + TO * l, ext - TO) - q0) : 0, skip = TO * l - k0;
+  Off xo[NX];
 #pragma unroll
-  for (int o = 0; o < TO; ++o) xo[o] = (column(16 * o + l) + (M1 ? (Off)(2 * g) : (Off)na * (Off)(2 * g))) * 8;
+  for (int o = 0; o < NX; ++o)
+    xo[o] = (column(V ? k0 : 16 * o + l) + (Off)kBack + (M1 ? (Off)(2 * g) : (Off)na * (Off)(2 * g))) * 8;
   d4 acc[TI][TO];
 #pragma unroll
   for (int i = 0; i < TI; ++i)
@@ -238,7 +255,7 @@ __device__ __forceinline__ void mode_tile(const ModeJob& jb, uint32_t lt, int la
     }
     const int lo = max(first - term * nch, 0), hi = min(last - term * nch, nch);
     if (lo < hi)
-      add_term<M1, RAW, TI, TO, D, Off>(acc, (const double*)jb.X[term] + origin_x, xo, na,
+      add_term<M1, RAW, TI, TO, D, Off, V>(acc, (const double*)jb.X[term] + (origin_x - kBack), xo, na,
                                         MatrixTiles<RAW, TI>(jb.P[term], n, t0, lane), n, lane, lo, hi);
   }
   const double sc = jb.scale[nterms - 1];
@@ -256,6 +273,36 @@ __device__ __forceinline__ void mode_tile(const ModeJob& jb, uint32_t lt, int la
   const double* __restrict__ bs = (const double*)jb.base + origin;
   const bool has_base = jb.base != nullptr;
   const int64_t ld = M1 ? n : na;
+  if constexpr (V) {
+    typedef double dv __attribute__((ext_vector_type(TO), aligned(8)));
+    const Off y0 = column(k0) + (Off)kBack;
+#pragma unroll
+    for (int m = 0; m < TI; ++m) {
+      dv bv[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        if (has_base) bv[r] = *(const dv*)(bs - kBack + min(16 * m + 4 * r + g, imax - 1) * ld + y0);
+        else bv[r] = dv(-0.0);
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = 16 * m + 4 * r + g;
+        if (row >= imax) continue;
+        dv v;
+#pragma unroll
+        for (int u = 0; u < TO; ++u) v[u] = acc[m][u][r] * sc + bv[r][u];
+        double* y = Y - kBack + row * ld + y0;
+        if (skip == 0) {
+          *(dv*)y = v;
+        } else {
+#pragma unroll
+          for (int u = 0; u < TO; ++u)
+            if (u >= skip) y[u] = v[u];
+        }
+      }
+    }
+    return;
+  }
   Off yo[TC];   // column of each block
 #pragma unroll
   for (int u = 0; u < TC; ++u) yo[u] = M1 ? (Off)min(16 * u + l, imax - 1) : column(16 * u + l);
@@ -320,7 +367,7 @@ constexpr int red_size(int ti, int to, int ks) { return ks > 1 ? 4 * ti * to * 6
 // register budget the accumulators stay in place through the k loop (a
 // tighter default made the compiler copy all of them between register files
 // every iteration).
-template <bool M1, bool RAW, int TI, int TO, int KS, typename Off>
+template <bool M1, bool RAW, int TI, int TO, int KS, typename Off, bool V>
 __global__ void __launch_bounds__(256, 2) mode_f64_kernel(const ModeJobs J, int64_t per_xcd) {
   __shared__ d4 red[red_size(TI, TO, KS)];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -330,7 +377,7 @@ __global__ void __launch_bounds__(256, 2) mode_f64_kernel(const ModeJobs J, int6
     return;
   }
   const ModeJob& jb = J.job[find_job(J, t)];
-  mode_tile<M1, RAW, TI, TO, ring_depth(TI, TO), KS, Off>(jb, t - (uint32_t)jb.tile_begin, lane, wave % KS,
+  mode_tile<M1, RAW, TI, TO, ring_depth(TI, TO), KS, Off, V>(jb, t - (uint32_t)jb.tile_begin, lane, wave % KS,
                                                           red + (wave / KS) * KS * TI * TO * 64);
 }
 
@@ -794,7 +841,7 @@ struct TileCfg {
   int ti, to, ks;
   double rate, block;
 };
-constexpr TileCfg kTiles[] = {{1, 1, 4, .50, 550}, {2, 2, 4, .92, 550}, {2, 2, 2, .86, 600}, {2, 2, 1, .80, 700},
+constexpr TileCfg kTiles[] = {{1, 1, 4, .50, 550}, {2, 2, 4, .92, 550}, {2, 2, 2, .86, 600}, {2, 2, 1, .84, 700},
                               {4, 2, 4, .92, 550}, {4, 2, 2, .92, 600}, {4, 2, 1, .90, 700}, {5, 2, 4, .92, 550},
                               {5, 2, 1, .92, 700}, {7, 1, 4, .92, 550}, {7, 2, 1, .92, 700}, {4, 4, 1, .94, 700}};
 
@@ -821,7 +868,7 @@ int64_t tile_count(const ModeJobs& J, bool mode1, const TileCfg& t) {
 // partial one counts whole while there are few), each as long as one wave, 64
 // cycles per MFMA.  Measured against each other at the two ends: 300^2, 4
 // jobs of mode 1: 2 x 2 tiles with 4 waves each 9.2 us, 4 x 4 41.9; 256^3, 6
-// jobs of 3 terms: 4 x 4 2.32 ms, 4 x 2 2.46, 2 x 2 with 4 waves 3.4.
+// jobs of 3 terms: 4 x 4 2.17 ms, 4 x 2 2.27, 2 x 2 with 4 waves 3.4.
 TileCfg choose_tile(const ModeJobs& J, bool mode1) {
   TileCfg best = kTiles[0];
   double bt = 1e300;
@@ -850,18 +897,26 @@ int finish_tiles(ModeJobs& J, bool mode1, const TileCfg& t) {
   return SETD_OK;
 }
 
-template <bool M1, bool RAW, int TI, int TO, int KS, typename Off>
+template <bool M1, bool RAW, int TI, int TO, int KS, typename Off, bool V = false>
 int launch_tile(const ModeJobs& J, hipStream_t s) {
   const int64_t per = ceil_div(ceil_div(J.total_tiles, 4 / KS), 8);
-  hipLaunchKernelGGL((mode_f64_kernel<M1, RAW, TI, TO, KS, Off>), dim3((unsigned)(per * 8)), dim3(256), 0, s, J, per);
+  hipLaunchKernelGGL((mode_f64_kernel<M1, RAW, TI, TO, KS, Off, V>), dim3((unsigned)(per * 8)), dim3(256), 0, s, J, per);
   SETD_LAUNCHED();
   return SETD_OK;
 }
 
+// Modes >= 2 whose contraction is not split load and store a lane's TO columns
+// together where no slab ends between them: at 256^3 (6 jobs of 3 terms) 4 x 4
+// tiles take 2.17 ms and not 2.29, 4 x 2 2.27 and not 2.38; 200^3 2 x 2 1.02 and
+// not 1.08; but 7 x 2, whose matrix loads are most of it, 1.007 and not 0.996.
 template <bool M1, bool RAW>
 int launch_cfg(const ModeJobs& J, const TileCfg& t, hipStream_t s) {
 #define SETD_TILE(TI_, TO_, KS_) \
-  if (t.ti == TI_ && t.to == TO_ && t.ks == KS_) return launch_tile<M1, RAW, TI_, TO_, KS_, uint32_t>(J, s);
+  if (t.ti == TI_ && t.to == TO_ && t.ks == KS_) {                                              \
+    if constexpr (!M1 && !RAW && KS_ == 1 && TI_ <= 5)                                         \
+      if (vector_columns(J, TO_)) return launch_tile<M1, RAW, TI_, TO_, KS_, uint32_t, true>(J, s); \
+    return launch_tile<M1, RAW, TI_, TO_, KS_, uint32_t>(J, s);                                \
+  }
   SETD_TILE(1, 1, 4)
   SETD_TILE(2, 2, 4)
   SETD_TILE(2, 2, 2)

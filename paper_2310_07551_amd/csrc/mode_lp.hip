@@ -698,16 +698,6 @@ bool big_tiles(const ModeJobs& J) {
   return false;
 }
 
-// A lane's `to` neighbouring columns are neighbours in memory: no slab ends
-// between them.
-bool vector_columns(const ModeJobs& J, int to) {
-  for (int j = 0; j < J.njobs; ++j) {
-    const ModeJob& jb = J.job[j];
-    if (jb.nb == 1 ? jb.na < to : jb.na % to != 0) return false;
-  }
-  return true;
-}
-
 // Tiles of the FP32 kernel {blocks of i, of the other index}, and the part of
 // the matrix-core rate that their loop reaches in mode 1 and in modes >= 2.
 // Measured with 18 jobs: 128^3 modes >= 2 110 us with 4 x 4, 117 with 8 x 2, 140
