@@ -49,6 +49,8 @@ struct DevBuf {
     bytes = 0;
   }
   void keep() {
+    int cur = -1;   // the caller has waited for work on the current device
+    if (p && (hipGetDevice(&cur) != hipSuccess || cur != dev_)) release();
     if (p) device_keep(p, capacity_, dev_);
     p = nullptr;
     bytes = 0;
