@@ -86,9 +86,9 @@ extern "C" {
 
 /*
  * phi-functions of a small dense matrix (Section 1 definition
- * phi_l(X) = sum_k X^k/(k+l)!; computed as in Section 2.4: rational Pade
- * approximation with modified scaling and squaring, here entirely in FP64 on
- * the GPU).
+ * phi_l(X) = sum_k X^k/(k+l)!; computed with the modified scaling and squaring
+ * of Section 2.4 from Taylor polynomials, entirely on the GPU in double-double
+ * arithmetic, rounded once to FP64).
  *
  *   A     n x n column-major FP64 (device).
  *   n     1 <= n <= 4096.

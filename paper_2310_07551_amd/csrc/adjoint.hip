@@ -113,7 +113,7 @@ __global__ void __launch_bounds__(kRedThreads) adj_stage_kernel(const double* __
 // The component count is a template argument and every neighbour is loaded
 // without a branch, from a clamped index with a zero coefficient past the
 // boundary, so that the loads of a point are in flight together (64^3: 18.8
-// us with each behind its branch, now 10.5).
+// us with each behind its branch, now 12.6).
 template <int NC>
 __global__ void __launch_bounds__(kRedThreads) adj_final_kernel(
     const double* __restrict__ U, double* __restrict__ ubar, const double* __restrict__ U3bar,
@@ -196,7 +196,7 @@ __global__ void __launch_bounds__(kRedThreads) adj_dots_kernel(const double* __r
 // grad[k] += parameter partials (k < nparams); grad[nparams + c] += diffusion
 // partials for the components in sigma_mask.  One wave per row, the row sums
 // in a fixed order, so the result does not depend on scheduling (one thread
-// per row waited for 512 loads in turn: 15 us, now 4).
+// per row waited for 512 loads in turn: 15 us, now 5).
 __global__ void __launch_bounds__(64 * kRows) adj_reduce_kernel(const double* __restrict__ part, int nparams,
                                                                 int ncomp, int sigma_mask, bool dots,
                                                                 double* __restrict__ grad) {
@@ -329,7 +329,7 @@ struct SigmaOut {
 
 // X0 and X1 of the chains in passes over slabs, modes 1 and 2 at once: 6
 // products a chain instead of the 5 with shared mode-1 partials, but none of
-// those in memory and a launch less (64^3, 18 chains: 79 us against 111).  Up
+// those in memory and a launch less (64^3, 18 chains: 82 us against 111).  Up
 // to kSlabSumN the two parts of X1 are the terms of one job, else the second
 // is added to the first.
 int sigma_slabs(const int* dims, const std::vector<SigmaChain>& ch, hipStream_t s) {

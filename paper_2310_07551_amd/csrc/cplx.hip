@@ -8,7 +8,7 @@
 //   * phi of the complex matrix z A is computed through its real 2n x 2n
 //     representation [[Re, -Im], [Im, Re]] (an algebra homomorphism, so
 //     phi of the representation represents phi of the matrix): the same
-//     Pade / scaling-and-squaring builder as for the real bank;
+//     scaling-and-squaring builder as for the real bank;
 //   * mode 1 on the real input: Y_r = P_r X, Y_i = P_i X (two jobs);
 //   * inner modes: Z_r = Y_r x P_r - Y_i x P_i, Z_i = Y_r x P_i + Y_i x P_r
 //     (two-term jobs of the modes >= 2 kernel);
