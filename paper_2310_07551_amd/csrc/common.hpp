@@ -155,6 +155,7 @@ struct SlabJob {
   const void* base;   // nullable
   int64_t nb;
   int n1, n2, nterms;
+  int comp;               // with a stage difference as input: its component (X is not used)
 };
 struct SlabJobs {
   SlabJob job[kMaxJobs];

@@ -92,9 +92,10 @@ struct TuckerOut {
 // distinct input of a launch, and for the fused forms one (mode 1 -> mode 2,
 // n2 in {128, 256}) or two (d = 3 in the order 3, 1, 2 with n1 and n2 in
 // {128, 256}) per chain (term of an output) besides; without room for them
-// a group runs the less fused form.
+// a group runs the less fused form.  diff: output o's input is component o of
+// that stage difference (2D FP64 groups of one pass over the slab only).
 int run_tucker_group(int d, const int* dims, TuckerOut* outs, int nouts, int prec, hipStream_t s,
-                     void* i8ws = nullptr, size_t i8bytes = 0);
+                     void* i8ws = nullptr, size_t i8bytes = 0, const StageDiff* diff = nullptr);
 // Bytes of one int8 digit buffer for any mode of the grid.
 size_t i8_slot_bytes(int d, const int* dims);
 // Whether run_tucker_group takes a d = 3 group of nchains chains in the

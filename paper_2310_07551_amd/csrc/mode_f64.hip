@@ -46,6 +46,7 @@
 // (the last mode alone 151 -> 20 and 9 us), 100^3 739 -> 559 us, 128^3 1060
 // -> 893 us, 256^3 11.93 -> 11.69 ms.
 #include "common.hpp"
+#include "pointwise.hpp"
 
 #include <algorithm>
 #include <cstdlib>
@@ -427,9 +428,10 @@ __global__ void __launch_bounds__(256, 2) mode_f64_list_kernel(const ModeJob* __
 // the SIMDs from one workgroup to the next.
 constexpr int slab_ring(int tj, int ni) { return tj * ni >= 6 ? 2 : 3; }
 
-template <bool RAW, bool SUM, int TJ, int NI, int LD>
+// X: the slab, in LDS, of a stage difference; nullptr: the term's tensor.
+template <bool RAW, bool SUM, int TJ, int NI, int LD, bool DIFF = false>
 __device__ __forceinline__ void slab_body(const SlabJob& jb, uint32_t b, int tj0, int w, int term, int lane,
-                                          double* Zall) {
+                                          double* Zall, const double* X = nullptr) {
   const int g = lane >> 4, l = lane & 15;
   const int n1 = jb.n1, n2 = jb.n2, nch1 = chunks_of(n1);
   const int64_t slab = (int64_t)n1 * n2 * b;
@@ -444,7 +446,7 @@ __device__ __forceinline__ void slab_body(const SlabJob& jb, uint32_t b, int tj0
 #pragma unroll
       for (int o = 0; o < NI; ++o) z[m][o] = d4{0.0, 0.0, 0.0, 0.0};
     add_term<false, RAW, TJ, NI, slab_ring(TJ, NI), uint32_t>(
-        z, (const double*)jb.X[term] + slab, xo, n1, MatrixTiles<RAW, TJ>(jb.P2[term], n2, tj0, lane), n2, lane, 0,
+        z, DIFF ? X : (const double*)jb.X[term] + slab, xo, n1, MatrixTiles<RAW, TJ>(jb.P2[term], n2, tj0, lane), n2, lane, 0,
         chunks_of(n2));
     const double sc = jb.scale[term];
 #pragma unroll
@@ -591,6 +593,48 @@ __global__ void __launch_bounds__(SUM ? 256 * kSlabTerms : 256, 2) slab_f64_kern
     if (ni == NI) slab_body<RAW, SUM, TJ - 1, NI, LD>(jb, b, tj0, w, term, lane, Z);
     else if constexpr (NI > 1) slab_body<RAW, SUM, TJ - 1, NI - 1, LD>(jb, b, tj0, w, term, lane, Z);
   }
+}
+
+// The two-term pass over one slab of up to kSlabSumN x kSlabSumN whose tensor
+// is a component of a stage difference: every workgroup forms all of it in LDS
+// (it reads all of it anyway), which saves the kernel that formed it before: two
+// of the six of a 64^2 step, 43.0 -> 38.6 us.  Bound by latency (cold first
+// loads, the barriers between the phases).
+__global__ void __launch_bounds__(256 * kSlabTerms, 2) slab_diff_f64_kernel(const SlabJobs J, const StageDiff sd,
+                                                                            int64_t per_xcd) {
+  constexpr int LD = 66, kPer = kSlabSumN * kSlabSumN / (256 * kSlabTerms);
+  __shared__ double Z[kSlabTerms * 16 * LD];
+  __shared__ double X[kSlabSumN * kSlabSumN];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t t = (uint32_t)remap_xcd(blockIdx.x, per_xcd);
+  if (t >= (uint32_t)J.total) return;   // uniform over the workgroup
+  const uint32_t jj = t / (uint32_t)J.tiles_per_job;
+  const SlabJob& jb = J.job[jj];
+  const uint32_t lt = t - jj * (uint32_t)J.tiles_per_job;   // its column block: one slab
+  const int nn = jb.n1 * jb.n2, comp = jb.comp;
+  double u[kPer], v[kPer], g[kPer];
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    const int i = min((int)threadIdx.x + 256 * kSlabTerms * k, nn - 1);
+    u[k] = sd.Us[i];
+    v[k] = sd.Us[(sd.ncomp > 1 ? sd.N : 0) + i];
+    g[k] = sd.G[comp * sd.N + i];
+  }
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    const int i = (int)threadIdx.x + 256 * kSlabTerms * k;
+    double r[2];
+    reaction(sd.gp, u[k], sd.ncomp > 1 ? v[k] : 0.0, r[0], r[1]);
+    if (i < nn) X[i] = (comp == 0 ? r[0] : r[1]) - g[k];
+  }
+  __syncthreads();
+  const int nt1 = (jb.n1 + 15) >> 4;
+  const int w = ((wave & 3) + (int)(lt & 3)) & 3, term = wave >> 2;
+  if (w >= nt1) {   // a wave without i_1 blocks only keeps the barriers
+    for (int k = 0; k < 3; ++k) __syncthreads();
+    return;
+  }
+  slab_body<false, true, 1, 1, LD, true>(jb, 0, (int)lt, w, term, lane, Z, X);
 }
 
 // ---------------------------------------------------------------------------
@@ -1062,6 +1106,30 @@ int launch_slab_f64(SlabJobs& J, hipStream_t s, bool raw) {
     return SETD_EUNSUPPORTED;
   }
   return sum ? launch_slab_ni<false, true>(J, s) : launch_slab_ni<false, false>(J, s);
+}
+
+int launch_slab_diff_f64(SlabJobs& J, const StageDiff& diff, hipStream_t s) {
+  if (J.njobs == 0) return SETD_OK;
+  double fl = 0.0, by = 0.0;
+  for (int j = 0; j < J.njobs; ++j) {
+    const SlabJob& q = J.job[j];
+    if (q.nterms != kSlabTerms || q.nb != 1 || q.n1 > kSlabSumN || q.n2 > kSlabSumN || q.n1 != J.job[0].n1 ||
+        q.n2 != J.job[0].n2 || (int64_t)q.n1 * q.n2 != diff.N || q.comp < 0 || q.comp >= diff.ncomp) {
+      set_error("slab product of a stage difference: two terms on one slab of up to %d x %d", kSlabSumN, kSlabSumN);
+      return SETD_EUNSUPPORTED;
+    }
+    const double N = (double)q.n1 * q.n2;
+    fl += q.nterms * 2.0 * N * (q.n1 + q.n2);
+    by += 24.0 * N + q.nterms * (8.0 * q.n1 * q.n1 + 8.0 * q.n2 * q.n2) + N * (q.base ? 16.0 : 8.0);
+  }
+  ProfScope prof(s, kProfMode1F64, fl, by);
+  J.nblk = (int)ceil_div(J.job[0].n2, 16);
+  J.tiles_per_job = J.nblk;
+  J.total = J.tiles_per_job * J.njobs;
+  const int64_t per = ceil_div(J.total, 8);
+  hipLaunchKernelGGL(slab_diff_f64_kernel, dim3((unsigned)(per * 8)), dim3(256 * kSlabTerms), 0, s, J, diff, per);
+  SETD_LAUNCHED();
+  return SETD_OK;
 }
 
 namespace {

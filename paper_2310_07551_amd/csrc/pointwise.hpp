@@ -68,6 +68,18 @@ int launch_gf_stencil(const double* u, int ncomp, int64_t N, int d, const int* d
 int launch_g(const double* u, int ncomp, int64_t N, const GParams& gp, double* G, hipStream_t s);
 int launch_stage_d(const double* Us, const double* G, int ncomp, int64_t N, const GParams& gp, void* D,
                    DType dtype, hipStream_t s);
+// The stage difference D_c = g_c(Us) - G_c as the input of a group, formed
+// where it is read.
+struct StageDiff {
+  const double* Us;
+  const double* G;
+  int64_t N;   // points of a component
+  int ncomp;
+  GParams gp;
+};
+// launch_slab_f64 (mode_f64.hip) for jobs of two terms on one slab of up to
+// kSlabSumN x kSlabSumN whose tensor is a component of `diff`.
+int launch_slab_diff_f64(SlabJobs& jobs, const StageDiff& diff, hipStream_t s);
 // SETD_PREC_I8X4 (mode_i8.hip): D_c = g_c(Us) - G_c for the ncomp (1 or 2)
 // components, written only as the int8 digits of its fibres along the last
 // mode of size n (n <= 256, dividing N) into the digit buffers D[c]; the

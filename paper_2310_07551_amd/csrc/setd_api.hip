@@ -311,7 +311,7 @@ bool setd::use_slab_3d(const int* dims) {
 }
 
 int setd::run_tucker_group(int d, const int* dims, TuckerOut* outs, int nouts, int prec, hipStream_t s,
-                           void* i8ws, size_t i8bytes) {
+                           void* i8ws, size_t i8bytes, const StageDiff* diff) {
   int64_t N = 1;
   for (int mu = 0; mu < d; ++mu) N *= dims[mu];
   const DType mid = fp32_storage(prec) ? DType::F32 : DType::F64;
@@ -420,6 +420,7 @@ int setd::run_tucker_group(int d, const int* dims, TuckerOut* outs, int nouts, i
         if (d == 2 && t + 1 < outs[o].nterms) continue;
         jb.Y = d == 2 ? outs[o].Y : (double*)tm.Y2;
         jb.base = d == 2 ? outs[o].base : nullptr;
+        jb.comp = o;
         S.job[S.njobs++] = jb;
         if (S.njobs == kMaxJobs) {
           SETD_TRY(launch_slab_f64(S, s));
@@ -427,6 +428,7 @@ int setd::run_tucker_group(int d, const int* dims, TuckerOut* outs, int nouts, i
         }
       }
     }
+    if (diff && d == 2) return launch_slab_diff_f64(S, *diff, s);
     SETD_TRY(launch_slab_f64(S, s));
     if (d == 2) return SETD_OK;
     ModeJobs J;
@@ -694,11 +696,19 @@ int setd::step_with(setd_ctx* c, double* u, const GParams& gp, hipStream_t s, co
     }
     SETD_TRY(run_tucker_group(d, c->dims, outs, no, prec, s, c->i8_mem.p, c->i8_mem.bytes));
   }
-  // D = g(U_s) - G, the input of the next group.  The int8 form in the order
+  // D = g(U_s) - G, the input of the next group.  A 2D FP64 group of one pass
+  // over the slab forms it there (`diff`); the int8 form in the order
   // 3, 1, 2 writes only D's digits along mode 3 (the stage difference and
   // the slicing in one pass), unless the stage quantities are being recorded.
+  StageDiff diff;
+  const StageDiff* in_slab = nullptr;
   auto stage_diff = [&](const double* Us, void* Dbuf, TuckerOut* outs) -> int {
     const bool own = b.D2 == (void*)c->D && b.D3 == (void*)c->D;
+    if (prec == SETD_PREC_F64 && own && d == 2 && use_slab(d, c->dims, outs, nc)) {
+      diff = {Us, b.G, N, nc, gp};
+      in_slab = &diff;
+      return SETD_OK;
+    }
     if (prec == SETD_PREC_I8X4 && own && i8_emit() && i8_order312(d, c->dims, nc * T, c->i8_mem.bytes)) {
       const size_t slot = i8_slot_bytes(d, c->dims);
       void* dg[2];
@@ -724,7 +734,7 @@ int setd::step_with(setd_ctx* c, double* u, const GParams& gp, hipStream_t s, co
         o.term[t] = {D2c_(cc), c->bank[cc][e32][t], 4.0 * tau / 3.0 * S2.eta[t], c->Y1[cc][t], c->Y2[cc][t]};
     }
     SETD_TRY(stage_diff(b.U2, b.D2, outs));
-    SETD_TRY(run_tucker_group(d, c->dims, outs, nc, prec, s, c->i8_mem.p, c->i8_mem.bytes));
+    SETD_TRY(run_tucker_group(d, c->dims, outs, nc, prec, s, c->i8_mem.p, c->i8_mem.bytes, in_slab));
   }
   // 5., 6. D3 = g(U3) - G; U = W + 3tau/2 S_2(tau) D3
   {
@@ -738,7 +748,7 @@ int setd::step_with(setd_ctx* c, double* u, const GParams& gp, hipStream_t s, co
         o.term[t] = {D3c_(cc), c->bank[cc][ef2][t], 1.5 * tau * S2.eta[t], c->Y1[cc][t], c->Y2[cc][t]};
     }
     SETD_TRY(stage_diff(b.U3, b.D3, outs));
-    SETD_TRY(run_tucker_group(d, c->dims, outs, nc, prec, s, c->i8_mem.p, c->i8_mem.bytes));
+    SETD_TRY(run_tucker_group(d, c->dims, outs, nc, prec, s, c->i8_mem.p, c->i8_mem.bytes, in_slab));
   }
   return SETD_OK;
 }
