@@ -596,39 +596,77 @@ __global__ void __launch_bounds__(SUM ? 256 * kSlabTerms : 256, 2) slab_f64_kern
 }
 
 // The two-term pass over one slab of up to kSlabSumN x kSlabSumN whose tensor
-// is a component of a stage difference: every workgroup forms all of it in LDS
-// (it reads all of it anyway), which saves the kernel that formed it before: two
-// of the six of a 64^2 step, 43.0 -> 38.6 us.  Bound by latency (cold first
-// loads, the barriers between the phases).
+// is a component of a stage difference, or (FIRST) of F = K u + g(u): every
+// workgroup forms all of it in LDS (it reads all of it anyway), which saves the
+// kernels that formed them before: three of the six of a 64^2 step, 43.0 -> 36.2
+// us.  FIRST: the stencil reads u from LDS, its sums in the order of
+// gf_stencil_kernel; the first column block of the component's first job writes
+// G.  Bound by latency (cold first loads, the barriers between the phases).
+template <bool FIRST>
 __global__ void __launch_bounds__(256 * kSlabTerms, 2) slab_diff_f64_kernel(const SlabJobs J, const StageDiff sd,
                                                                             int64_t per_xcd) {
-  constexpr int LD = 66, kPer = kSlabSumN * kSlabSumN / (256 * kSlabTerms);
+  constexpr int LD = 66, kThreads = 256 * kSlabTerms, kPer = kSlabSumN * kSlabSumN / kThreads;
   __shared__ double Z[kSlabTerms * 16 * LD];
   __shared__ double X[kSlabSumN * kSlabSumN];
+  __shared__ double U[FIRST ? kSlabSumN * kSlabSumN : 1];
+  __shared__ double K[FIRST ? 6 * kSlabSumN : 1];   // lo, di, up of both directions
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t t = (uint32_t)remap_xcd(blockIdx.x, per_xcd);
   if (t >= (uint32_t)J.total) return;   // uniform over the workgroup
   const uint32_t jj = t / (uint32_t)J.tiles_per_job;
   const SlabJob& jb = J.job[jj];
   const uint32_t lt = t - jj * (uint32_t)J.tiles_per_job;   // its column block: one slab
-  const int nn = jb.n1 * jb.n2, comp = jb.comp;
+  const int n1 = jb.n1, n2 = jb.n2, nn = n1 * n2, comp = jb.comp;
   double u[kPer], v[kPer], g[kPer];
 #pragma unroll
   for (int k = 0; k < kPer; ++k) {
-    const int i = min((int)threadIdx.x + 256 * kSlabTerms * k, nn - 1);
+    const int i = min((int)threadIdx.x + kThreads * k, nn - 1);
     u[k] = sd.Us[i];
     v[k] = sd.Us[(sd.ncomp > 1 ? sd.N : 0) + i];
-    g[k] = sd.G[comp * sd.N + i];
+    if (!FIRST) g[k] = sd.G[comp * sd.N + i];
   }
+  if constexpr (FIRST) {
+    if (threadIdx.x < 6 * kSlabSumN) {
+      const int q = threadIdx.x / kSlabSumN, i = threadIdx.x % kSlabSumN, dir = q / 3, n = dir ? n2 : n1;
+      const int at = comp * 3 + dir, ic = min(i, n - 1);
+      const double* c = q % 3 == 0 ? sd.st.lo[at] : q % 3 == 1 ? sd.st.di[at] : sd.st.up[at];
+      const bool out = (q % 3 == 0 && i == 0) || (q % 3 == 2 && i + 1 >= n);   // zero past the boundary
+      const double x = c[ic];
+      K[threadIdx.x] = out ? 0.0 : x;
+    }
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+      const int i = (int)threadIdx.x + kThreads * k;
+      if (i < nn) U[i] = comp == 0 ? u[k] : v[k];
+    }
+    __syncthreads();
+  }
+  const bool write_g = FIRST && lt == 0 && (jj == 0 || J.job[jj - 1].comp != comp);
 #pragma unroll
   for (int k = 0; k < kPer; ++k) {
-    const int i = (int)threadIdx.x + 256 * kSlabTerms * k;
+    const int i = (int)threadIdx.x + kThreads * k;
     double r[2];
     reaction(sd.gp, u[k], sd.ncomp > 1 ? v[k] : 0.0, r[0], r[1]);
-    if (i < nn) X[i] = (comp == 0 ? r[0] : r[1]) - g[k];
+    const double gc = comp == 0 ? r[0] : r[1];
+    if (i >= nn) continue;
+    if constexpr (FIRST) {
+      const int i2 = i / n1, i1 = i - i2 * n1;
+      const double* k1 = K + i1;
+      const double* k2 = K + 3 * kSlabSumN + i2;
+      const double x = U[i];
+      // rounded as in gf_stencil_kernel
+      const double s1 = fma(k1[2 * kSlabSumN], U[i1 + 1 < n1 ? i + 1 : i],
+                            fma(k1[kSlabSumN], x, k1[0] * U[i1 > 0 ? i - 1 : i]));
+      const double s2 = fma(k2[2 * kSlabSumN], U[i2 + 1 < n2 ? i + n1 : i],
+                            fma(k2[0], U[i2 > 0 ? i - n1 : i], k2[kSlabSumN] * x));
+      X[i] = s1 + s2 + gc;
+      if (write_g) sd.G[comp * sd.N + i] = gc;
+    } else {
+      X[i] = gc - g[k];
+    }
   }
   __syncthreads();
-  const int nt1 = (jb.n1 + 15) >> 4;
+  const int nt1 = (n1 + 15) >> 4;
   const int w = ((wave & 3) + (int)(lt & 3)) & 3, term = wave >> 2;
   if (w >= nt1) {   // a wave without i_1 blocks only keeps the barriers
     for (int k = 0; k < 3; ++k) __syncthreads();
@@ -1127,7 +1165,8 @@ int launch_slab_diff_f64(SlabJobs& J, const StageDiff& diff, hipStream_t s) {
   J.tiles_per_job = J.nblk;
   J.total = J.tiles_per_job * J.njobs;
   const int64_t per = ceil_div(J.total, 8);
-  hipLaunchKernelGGL(slab_diff_f64_kernel, dim3((unsigned)(per * 8)), dim3(256 * kSlabTerms), 0, s, J, diff, per);
+  hipLaunchKernelGGL(diff.first ? slab_diff_f64_kernel<true> : slab_diff_f64_kernel<false>, dim3((unsigned)(per * 8)),
+                     dim3(256 * kSlabTerms), 0, s, J, diff, per);
   SETD_LAUNCHED();
   return SETD_OK;
 }

@@ -69,13 +69,16 @@ int launch_g(const double* u, int ncomp, int64_t N, const GParams& gp, double* G
 int launch_stage_d(const double* Us, const double* G, int ncomp, int64_t N, const GParams& gp, void* D,
                    DType dtype, hipStream_t s);
 // The stage difference D_c = g_c(Us) - G_c as the input of a group, formed
-// where it is read.
+// where it is read; or (first) the step's F_c = K_c Us + g_c(Us) with the
+// tridiagonal K, G_c = g_c(Us) being written besides.
 struct StageDiff {
   const double* Us;
-  const double* G;
+  double* G;
   int64_t N;   // points of a component
   int ncomp;
   GParams gp;
+  bool first;
+  StencilSet st;
 };
 // launch_slab_f64 (mode_f64.hip) for jobs of two terms on one slab of up to
 // kSlabSumN x kSlabSumN whose tensor is a component of `diff`.

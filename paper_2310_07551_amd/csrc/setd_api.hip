@@ -420,7 +420,7 @@ int setd::run_tucker_group(int d, const int* dims, TuckerOut* outs, int nouts, i
         if (d == 2 && t + 1 < outs[o].nterms) continue;
         jb.Y = d == 2 ? outs[o].Y : (double*)tm.Y2;
         jb.base = d == 2 ? outs[o].base : nullptr;
-        jb.comp = o;
+        jb.comp = diff ? o / (nouts / diff->ncomp) : 0;
         S.job[S.njobs++] = jb;
         if (S.njobs == kMaxJobs) {
           SETD_TRY(launch_slab_f64(S, s));
@@ -668,8 +668,12 @@ int setd::step_with(setd_ctx* c, double* u, const GParams& gp, hipStream_t s, co
   auto Fc_ = [&](int cc) { return (void*)((char*)b.F + cc * N * es); };
   auto D2c_ = [&](int cc) { return (void*)((char*)b.D2 + cc * N * es); };
   auto D3c_ = [&](int cc) { return (void*)((char*)b.D3 + cc * N * es); };
-  // 1. G, F
-  SETD_TRY(compute_gf(c, u, gp, s, b.G, b.F));
+  // 1. G, F: a 2D FP64 step whose groups are one pass over the slab forms F, G
+  // and the stage differences there, unless the stage quantities are recorded
+  const bool own = b.D2 == (void*)c->D && b.D3 == (void*)c->D;
+  const bool in_slab = prec == SETD_PREC_F64 && own && d == 2 && T == 2 && c->dims[0] <= kSlabSumN && c->dims[1] <= kSlabSumN;
+  StageDiff diff{u, b.G, N, nc, gp, true, c->st};
+  if (!in_slab || !c->tridiag) SETD_TRY(compute_gf(c, u, gp, s, b.G, b.F));
   const int e21 = bank_index(SETD_STAGE_2, 1), e31 = bank_index(SETD_STAGE_3, 1), e32 = bank_index(SETD_STAGE_3, 2),
             ef1 = bank_index(SETD_STAGE_F, 1), ef2 = bank_index(SETD_STAGE_F, 2);
   const Splitting& S1 = c->sp[1];
@@ -694,19 +698,16 @@ int setd::step_with(setd_ctx* c, double* u, const GParams& gp, hipStream_t s, co
                        c->Y2[cc][k * T + t]};
       }
     }
-    SETD_TRY(run_tucker_group(d, c->dims, outs, no, prec, s, c->i8_mem.p, c->i8_mem.bytes));
+    SETD_TRY(run_tucker_group(d, c->dims, outs, no, prec, s, c->i8_mem.p, c->i8_mem.bytes,
+                              in_slab && c->tridiag ? &diff : nullptr));
   }
-  // D = g(U_s) - G, the input of the next group.  A 2D FP64 group of one pass
-  // over the slab forms it there (`diff`); the int8 form in the order
+  // D = g(U_s) - G, the input of the next group.  The int8 form in the order
   // 3, 1, 2 writes only D's digits along mode 3 (the stage difference and
   // the slicing in one pass), unless the stage quantities are being recorded.
-  StageDiff diff;
-  const StageDiff* in_slab = nullptr;
   auto stage_diff = [&](const double* Us, void* Dbuf, TuckerOut* outs) -> int {
-    const bool own = b.D2 == (void*)c->D && b.D3 == (void*)c->D;
-    if (prec == SETD_PREC_F64 && own && d == 2 && use_slab(d, c->dims, outs, nc)) {
-      diff = {Us, b.G, N, nc, gp};
-      in_slab = &diff;
+    if (in_slab) {
+      diff.Us = Us;
+      diff.first = false;
       return SETD_OK;
     }
     if (prec == SETD_PREC_I8X4 && own && i8_emit() && i8_order312(d, c->dims, nc * T, c->i8_mem.bytes)) {
@@ -734,7 +735,7 @@ int setd::step_with(setd_ctx* c, double* u, const GParams& gp, hipStream_t s, co
         o.term[t] = {D2c_(cc), c->bank[cc][e32][t], 4.0 * tau / 3.0 * S2.eta[t], c->Y1[cc][t], c->Y2[cc][t]};
     }
     SETD_TRY(stage_diff(b.U2, b.D2, outs));
-    SETD_TRY(run_tucker_group(d, c->dims, outs, nc, prec, s, c->i8_mem.p, c->i8_mem.bytes, in_slab));
+    SETD_TRY(run_tucker_group(d, c->dims, outs, nc, prec, s, c->i8_mem.p, c->i8_mem.bytes, in_slab ? &diff : nullptr));
   }
   // 5., 6. D3 = g(U3) - G; U = W + 3tau/2 S_2(tau) D3
   {
@@ -748,7 +749,7 @@ int setd::step_with(setd_ctx* c, double* u, const GParams& gp, hipStream_t s, co
         o.term[t] = {D3c_(cc), c->bank[cc][ef2][t], 1.5 * tau * S2.eta[t], c->Y1[cc][t], c->Y2[cc][t]};
     }
     SETD_TRY(stage_diff(b.U3, b.D3, outs));
-    SETD_TRY(run_tucker_group(d, c->dims, outs, nc, prec, s, c->i8_mem.p, c->i8_mem.bytes, in_slab));
+    SETD_TRY(run_tucker_group(d, c->dims, outs, nc, prec, s, c->i8_mem.p, c->i8_mem.bytes, in_slab ? &diff : nullptr));
   }
   return SETD_OK;
 }
