@@ -170,10 +170,16 @@ __device__ __forceinline__ void add_term(d4 (&acc)[TI][TO], const double* __rest
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       const int p = 8 * nfull + 2 * g + j;
-      const double* xp = x0 + ps * (min(p, n - 1) - 2 * g);   // xo holds the lane's 2 g
+      const char* xp = (const char*)(x0 + ps * (min(p, n - 1) - 2 * g));   // xo holds the lane's 2 g
+      if constexpr (V) {
+        typedef double dv __attribute__((ext_vector_type(TO), aligned(8)));
+        const dv v = *(const dv*)(xp + xo[0]);
 #pragma unroll
-      for (int o = 0; o < TO; ++o)
-        xr[D - 1][o][j] = *(const double*)((const char*)(V ? xp + o : xp) + xo[V ? 0 : o]);
+        for (int o = 0; o < TO; ++o) xr[D - 1][o][j] = v[o];
+      } else {
+#pragma unroll
+        for (int o = 0; o < TO; ++o) xr[D - 1][o][j] = *(const double*)(xp + xo[o]);
+      }
 #pragma unroll
       for (int o = 0; o < TO; ++o) xr[D - 1][o][j] = p < n ? xr[D - 1][o][j] : 0.0;
     }
@@ -358,8 +364,11 @@ __device__ __forceinline__ void mode_tile(const ModeJob& jb, uint32_t lt, int la
   }
 }
 
-// Ring depth: more chunks in flight where a chunk is only a few products.
-constexpr int ring_depth(int ti, int to) { return ti * to <= 2 ? 4 : ti * to <= 4 ? 3 : 2; }
+// Ring depth: more chunks in flight where a chunk is only a few products; 1 x 4
+// tiles have two chunks at most and hide their latency with waves.
+constexpr int ring_depth(int ti, int to) {
+  return ti == 1 && to == 4 ? 1 : ti * to <= 2 ? 4 : ti * to <= 4 ? 3 : 2;
+}
 // LDS of a workgroup whose waves split contractions: 4 / KS tiles, KS parts each.
 constexpr int red_size(int ti, int to, int ks) { return ks > 1 ? 4 * ti * to * 64 : 1; }
 
@@ -915,17 +924,25 @@ namespace {
 bool aligned(const void* p, uintptr_t a) { return ((uintptr_t)p % a) == 0; }
 
 // Tile of one launch: ti x to blocks of 16 (i x the other index) per wave, ks
-// waves per tile.  rate: share of the matrix rate that the products of its
-// waves reach (1 x 1 tiles wait for their operands); block: cycles per block
-// that loading and storing it adds to a wave (fitted to sweeps of all tiles
-// at 64^2 .. 600^2 and 64^3 .. 256^3).
+// waves per tile (1 x 4: modes >= 2 of up to kShortN, bound by memory: few
+// registers, so that six waves share a SIMD; 1024 x 2 x 3200, mode 2, 46 us
+// against 82 with 2 x 2, 1024 x 16 x 400 18.4 against 23.4).  rate: share of the matrix rate that the products of its
+// waves reach (1 x 1 tiles wait for their operands); rate_long: the same for n >
+// kLongN, where the matrix (8 n^2 bytes) is past the 4 MB of an XCD's L2 and
+// every tile reads it from further away, the smaller the tile the oftener (2048
+// x 4096, mode 1: 2 x 2 tiles with 4 waves 732 us, 4 x 4 483); block: cycles per
+// block that loading and storing it adds to a wave (fitted to sweeps of all
+// tiles at 64^2 .. 600^2, 64^3 .. 256^3 and up to 4096 in one direction).
 struct TileCfg {
   int ti, to, ks;
-  double rate, block;
+  double rate, rate_long, block;
 };
-constexpr TileCfg kTiles[] = {{1, 1, 4, .50, 550}, {2, 2, 4, .92, 550}, {2, 2, 2, .86, 600}, {2, 2, 1, .84, 700},
-                              {4, 2, 4, .92, 550}, {4, 2, 2, .92, 600}, {4, 2, 1, .90, 700}, {5, 2, 4, .92, 550},
-                              {5, 2, 1, .92, 700}, {7, 1, 4, .92, 550}, {7, 2, 1, .92, 700}, {4, 4, 1, .94, 700}};
+constexpr int kLongN = 640, kShortN = 16;
+constexpr TileCfg kTiles[] = {{1, 1, 4, .50, .36, 550}, {1, 4, 1, .84, .70, 700}, {2, 2, 4, .92, .66, 550},
+                              {2, 2, 2, .86, .68, 600}, {2, 2, 1, .84, .70, 700}, {4, 2, 4, .92, .80, 550},
+                              {4, 2, 2, .92, .84, 600}, {4, 2, 1, .90, .85, 700}, {5, 2, 4, .92, .80, 550},
+                              {5, 2, 1, .92, .75, 700}, {7, 1, 4, .92, .60, 550}, {7, 2, 1, .92, .72, 700},
+                              {4, 4, 1, .94, .94, 700}};
 
 TileCfg env_tile(const char* name, TileCfg def) {
   const char* s = std::getenv(name);
@@ -948,21 +965,37 @@ int64_t tile_count(const ModeJobs& J, bool mode1, const TileCfg& t) {
 
 // The tile whose launch should take least time: rounds of 1024 SIMDs (a
 // partial one counts whole while there are few), each as long as one wave, 64
-// cycles per MFMA.  Measured against each other at the two ends: 300^2, 4
-// jobs of mode 1: 2 x 2 tiles with 4 waves each 9.2 us, 4 x 4 41.9; 256^3, 6
-// jobs of 3 terms: 4 x 4 2.17 ms, 4 x 2 2.27, 2 x 2 with 4 waves 3.4.
+// cycles per MFMA, and the part of a wave that the launch begins and ends with.
+// A launch with a round of 4 x 4 tiles fills the chip: that part is small, and
+// waves that split a contraction add only its parts (128 x 65536, mode 1: 4 x 4
+// 43 us, 4 x 2 53; 64 x 99328: 4 x 4 26, 4 x 2 of two waves 35).  Mode 1 with n a
+// multiple of 16: every row of X starts at a line, so that the half lines of a
+// load fall into the same half of the L1's banks, which tiles with little of i to
+// reuse them for feel (224 x 27648: 2 x 2 70 us, 7 x 2 55; modes >= 2 of that size
+// 51 and 59).  4 x 4 tiles, two waves to a SIMD, run in pairs of rounds (230 x
+// 46200, mode 1, 2.8 rounds: 124 us, as long as 4; 2 x 2 97).  Measured against each other at the two ends: 300^2, 4 jobs of mode
+// 1: 2 x 2 tiles with 4 waves each 9.2 us, 4 x 4 41.9; 256^3, 6 jobs of 3 terms: 4
+// x 4 2.17 ms, 4 x 2 2.27, 2 x 2 with 4 waves 3.4.
 TileCfg choose_tile(const ModeJobs& J, bool mode1) {
+  const bool full = tile_count(J, mode1, TileCfg{4, 4, 1, 0, 0, 0}) >= 1024;
+  bool wide = !mode1;   // 1 x 4
+  for (int j = 0; j < J.njobs; ++j) wide = wide && J.job[j].n <= kShortN;
   TileCfg best = kTiles[0];
   double bt = 1e300;
   for (const TileCfg& t : kTiles) {
+    if ((t.ti == 1 && t.to == 4 && !wide) || (full && t.ks > 1)) continue;
     const double w = (double)tile_count(J, mode1, t) * t.ks / 1024.0;
     double wave = 0.0;
     for (int j = 0; j < J.njobs; ++j) {
       const ModeJob& jb = J.job[j];
       const double chunks = (double)jb.nterms * ceil_div(jb.n, 8) / t.ks;
-      wave = std::max(wave, t.ti * t.to * (chunks * 128.0 / t.rate + t.block * (jb.base ? 1.6 : 1.0)));
+      const double banks = mode1 && t.ti <= 2 && jb.n > 32 && jb.n % 16 == 0 ? 0.7 : 1.0;
+      const double rate = banks * (jb.n > kLongN ? t.rate_long : t.rate);
+      wave = std::max(wave, t.ti * t.to * (chunks * 128.0 / rate + t.block * (jb.base ? 1.6 : 1.0)));
     }
-    const double time = ((w < 6.0 ? std::ceil(w) : w) + 0.3) * wave;
+    const bool pairs = t.ti * t.to == 16 && w > 1.0;
+    const double rounds = w >= 6.0 ? w : pairs ? 2.0 * std::ceil(w / 2.0) : std::ceil(w);
+    const double time = (rounds + (full ? 0.1 : 0.3)) * wave;
     if (time < bt) {
       bt = time;
       best = t;
@@ -995,11 +1028,12 @@ template <bool M1, bool RAW>
 int launch_cfg(const ModeJobs& J, const TileCfg& t, hipStream_t s) {
 #define SETD_TILE(TI_, TO_, KS_) \
   if (t.ti == TI_ && t.to == TO_ && t.ks == KS_) {                                              \
-    if constexpr (!M1 && !RAW && KS_ == 1 && TI_ <= 5)                                         \
+    if constexpr (!M1 && KS_ == 1 && TI_ <= 5)                                                  \
       if (vector_columns(J, TO_)) return launch_tile<M1, RAW, TI_, TO_, KS_, uint32_t, true>(J, s); \
     return launch_tile<M1, RAW, TI_, TO_, KS_, uint32_t>(J, s);                                \
   }
   SETD_TILE(1, 1, 4)
+  SETD_TILE(1, 4, 1)
   SETD_TILE(2, 2, 4)
   SETD_TILE(2, 2, 2)
   SETD_TILE(2, 2, 1)
@@ -1082,7 +1116,7 @@ int launch_modeB_f64(ModeJobs& J, hipStream_t s, bool raw) {
     big = big || jb.na > (int64_t(1) << 26) ||
           (jb.nb > 1 && (ceil_div(128, jb.na) + 1) * jb.na * jb.n > (int64_t(1) << 28));
   }
-  const TileCfg cfg = big ? TileCfg{4, 2, 1, 0.0, 0.0} : env_tile("SETD_TILE_MODEB", choose_tile(J, false));
+  const TileCfg cfg = big ? TileCfg{4, 2, 1, 0, 0, 0} : env_tile("SETD_TILE_MODEB", choose_tile(J, false));
   if (lds) finish_panels(J, false);
   else finish_tiles(J, false, cfg);
   if (J.total_tiles == 0) return SETD_OK;
