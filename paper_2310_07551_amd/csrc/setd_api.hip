@@ -283,10 +283,17 @@ bool setd::i8_order312(int d, const int* dims, int nchains, size_t i8bytes) {
 bool setd::i8_emit() { return i8_emit_on(); }
 
 namespace {
-// Slabs of 32 rows or fewer leave two of a workgroup's four waves without
-// work; on a small tensor that costs less than a launch (phi_1 group of a
-// step: 32^3 9 us against 14 for two products, 20 x 100 x 100 53 against 49).
-bool slab_rows(int64_t n1, int64_t N) { return n1 > 32 || N <= (1 << 17); }
+// Slabs that the pass is made for, any on a small tensor, where a launch saved
+// is worth more.  32 rows or fewer leave two of a workgroup's four waves without
+// work (phi_1 group of a step: 32^3 9 us against 14 for two products, 20 x 100 x
+// 100 53 against 49).  Fewer than 8 columns fill less than half of a tile (a step
+// of 250 x 3 x 1000 1.79 ms against 1.20).  Many columns are a long contraction
+// by the narrow tiles of a slab of few rows (a step of 64 x 1024 x 64 5.2 ms
+// against 4.4, 40 x 1000 x 40 2.8 against 2.0, 200 x 1000 x 20 5.1 against 4.8;
+// 256 x 1024 x 16 5.1 against 5.3, 64 x 256 x 256 2.4 against 2.8).
+bool slab_shape(int64_t n1, int64_t n2, int64_t N) {
+  return N <= (1 << 17) || (n1 > 32 && n2 >= 8 && n2 <= 4 * n1);
+}
 
 // Whether an FP64 group runs modes 1 and 2 as one pass over slabs.  d = 3: n1
 // up to 256 (phi_1 group of a step, the two products apart against the pass:
@@ -307,7 +314,7 @@ bool use_slab(int d, const int* dims, const TuckerOut* outs, int nouts) {
 
 bool setd::use_slab_3d(const int* dims) {
   const bool panels = dims[0] >= 192 && dims[0] % 64 == 0 && dims[1] >= 192 && dims[1] <= 256 && dims[1] % 64 == 0;
-  return dims[0] <= kSlabMaxN1 && !panels && slab_rows(dims[0], (int64_t)dims[0] * dims[1] * dims[2]);
+  return dims[0] <= kSlabMaxN1 && !panels && slab_shape(dims[0], dims[1], (int64_t)dims[0] * dims[1] * dims[2]);
 }
 
 int setd::run_tucker_group(int d, const int* dims, TuckerOut* outs, int nouts, int prec, hipStream_t s,
@@ -927,7 +934,7 @@ bool raw_slab(const int64_t* dims, int64_t nb, bool own_ws) {
   if (dims[0] > kSlabMaxN1) return false;
   const int64_t c = (ceil_div(dims[0], 8) + ceil_div(dims[1], 8)) * ceil_div(dims[0], 64);
   if (nb * ceil_div(dims[1], 16) <= 64) return c <= (own_ws ? 180 : 50);
-  return dims[1] >= 8 && slab_rows(dims[0], nb * dims[0] * dims[1]);
+  return dims[1] >= 8 && slab_shape(dims[0], dims[1], nb * dims[0] * dims[1]);
 }
 
 int tucker_raw(const double* V, double* W, int d, const int64_t* dims, int64_t N, const double* const* M,
