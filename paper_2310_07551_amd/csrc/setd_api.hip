@@ -927,20 +927,22 @@ constexpr int64_t kRawElems = int64_t(1) << 23;
 
 // Modes 1 and 2 as one pass over slabs, which needs no intermediate.  A few
 // slabs run on a few workgroups (about 4.5 + 0.13 c us, c = chunks of both
-// contractions x blocks of 64 rows), against two launches (10 us) and, without
-// a workspace from the caller, an allocation (18 us): 64^2 9 us a call (40
-// with packing and two products), 128^2 10 (40), 200^2 29 by two products.
-bool raw_slab(const int64_t* dims, int64_t nb, bool own_ws) {
+// contractions x blocks of 64 rows), against two launches (8 to 10 us) and, where
+// these are all the modes and the caller gives no workspace, an allocation (18
+// us): 64^2 9 us a call (25 by two products), 128^2 10 (25), 250 x 100 23 (25),
+// 200^2 29 by two products.  The choice is the same with a workspace (128^2 10 us,
+// 8.6 by two products; 250 x 100 23, 8.4), so that every entry gives the same bits.
+bool raw_slab(const int64_t* dims, int64_t nb, bool all) {
   if (dims[0] > kSlabMaxN1) return false;
   const int64_t c = (ceil_div(dims[0], 8) + ceil_div(dims[1], 8)) * ceil_div(dims[0], 64);
-  if (nb * ceil_div(dims[1], 16) <= 64) return c <= (own_ws ? 180 : 50);
+  if (nb * ceil_div(dims[1], 16) <= 64) return c <= (all ? 180 : 50);
   return dims[1] >= 8 && slab_shape(dims[0], dims[1], nb * dims[0] * dims[1]);
 }
 
 int tucker_raw(const double* V, double* W, int d, const int64_t* dims, int64_t N, const double* const* M,
                const int* modes, int nm, double alpha, double beta, void* ws, hipStream_t s) {
   const bool slab = nm >= 2 && modes[0] == 0 && modes[1] == 1 &&
-                    raw_slab(dims, N / (dims[0] * dims[1]), ws == nullptr);
+                    raw_slab(dims, N / (dims[0] * dims[1]), nm == 2);
   const int nops = slab ? nm - 1 : nm;
   const int64_t fb = round_up(N * 8, 256);
   void* own = nullptr;
