@@ -1125,11 +1125,13 @@ int setd_tucker_apply(const double* V, double* W, int d, const int64_t* dims, co
   int modes[8], nm = 0;
   for (int mu = 0; mu < d; ++mu)
     if (M[mu] != nullptr) modes[nm++] = mu;
-  // a matrix inside W has to be packed before W is written
-  bool in_w = false;
-  for (int k = 0; k < nm; ++k)
-    in_w = in_w || overlap(M[modes[k]], (size_t)dims[modes[k]] * dims[modes[k]] * 8, W, N * 8);
-  if (prec == SETD_PREC_F64 && nm > 0 && N <= kRawElems && !in_w)
+  // a matrix inside W or the workspace has to be packed before that is written
+  bool inside = false;
+  for (int k = 0; k < nm; ++k) {
+    const size_t mb = (size_t)dims[modes[k]] * dims[modes[k]] * 8;
+    inside = inside || overlap(M[modes[k]], mb, W, N * 8) || (ws != nullptr && overlap(M[modes[k]], mb, ws, ws_bytes));
+  }
+  if (prec == SETD_PREC_F64 && nm > 0 && N <= kRawElems && !inside)
     return tucker_raw(V, W, d, dims, N, M, modes, nm, alpha, beta, ws, s);
   // the workspace first, so that a failed allocation leaves W untouched
   void* wsp = ws;

@@ -39,3 +39,22 @@ def test_same_bits(dims):
             assert rel_err(host(Wa, dims), alpha * ref + beta * W0) < 1e-13
             assert torch().equal(Wa, Wb), (dims, mask, "workspace")
             assert torch().equal(Wa, Wc), (dims, mask, "noalloc")
+
+
+@pytest.mark.parametrize("dims", [(40, 30, 20), (300, 70), (24, 24, 24, 8)])
+def test_matrices_inside_the_workspace(dims):
+    """Matrices that lie where a call keeps its intermediates are used as they
+    were before the call."""
+    T = wl.random_tensor(dims, 1)
+    Ls = [wl.random_matrix(n, 3 + k, scale=0.3) for k, n in enumerate(dims)]
+    ws = torch().zeros(setd.tucker_workspace_bytes(dims) // 8 + 1, dtype=torch().float64, device="cuda")
+    mats, at = [], 0
+    N = int(np.prod(dims))
+    for L in Ls:   # one after another from the start of the first intermediate
+        mats.append(ws[at:at + L.size])
+        mats[-1].copy_(dev(L))
+        at += L.size
+    assert at <= 2 * N
+    W = torch().empty(N, dtype=torch().float64, device="cuda")
+    setd.tucker_apply(dev(T), W, dims, mats, workspace=ws)
+    assert rel_err(host(W, dims), oracle.tucker(T, Ls)) < 1e-13
