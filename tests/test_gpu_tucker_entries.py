@@ -41,7 +41,7 @@ def test_same_bits(dims):
             assert torch().equal(Wa, Wc), (dims, mask, "noalloc")
 
 
-@pytest.mark.parametrize("dims", [(40, 30, 20), (300, 70), (24, 24, 24, 8)])
+@pytest.mark.parametrize("dims", [(40, 30, 20), (60, 50, 40), (24, 24, 24, 8)])
 def test_matrices_inside_the_workspace(dims):
     """Matrices that lie where a call keeps its intermediates are used as they
     were before the call."""
