@@ -131,8 +131,11 @@ int setd_tucker_apply(const double* V, double* W, int d, const int64_t* dims,
                       void* ws, size_t ws_bytes, void* stream);
 size_t setd_tucker_workspace_bytes(int d, const int64_t* dims, int prec);
 /* Gives back what the library keeps on the current device between calls:
- * workspaces, and up to 512 MiB of destroyed contexts' memory (which an
- * allocation that would fail gives back by itself). */
+ * unused memory of the device's stream-ordered pool, the workspace of phi builds
+ * (up to 256 MiB), and up to 512 MiB that destroyed contexts and the set-up of
+ * live ones no longer use.  An allocation of the library that would fail gives
+ * all of it back by itself and tries again; other allocations of the program
+ * cannot reach it without this call. */
 int setd_release_workspace(void);
 
 /*

@@ -120,6 +120,15 @@ __device__ __forceinline__ int find_job_list(const int64_t* begins, int njobs, i
 
 enum class DType : int { F64 = 0, F32 = 1 };
 
+// ---- device memory (setd_api.hip) ----
+// hipMalloc and hipMallocAsync on the current device.  One that would fail first
+// gives back what the library keeps there without needing it: blocks of destroyed
+// objects, the idle workspace of phi builds (idle_phi = false: the caller holds
+// it), unused memory of the stream-ordered pool.  The error of a failed attempt
+// is cleared.
+int device_malloc(void** p, size_t bytes, bool idle_phi = true);
+int device_malloc_async(void** p, size_t bytes, hipStream_t s);
+
 // ---- kernel timing (setd_profile_*), implemented in setd_api.hip ----
 enum ProfClass : int {
   kProfMode1F64 = 0,

@@ -260,7 +260,7 @@ __global__ void top_block_kernel(d2* __restrict__ W, int64_t nn, int64_t stride,
 
 // Workspace of the builds: one buffer per device of at most kPoolBytes, kept
 // between calls (allocating and freeing it cost more than a small build) until
-// setd_release_workspace.  A call owns it from its first launch to its final
+// setd_release_workspace or a failing allocation.  A call owns it from its first launch to its final
 // synchronisation; a call that finds it taken, or needs more, allocates its own.
 constexpr size_t kPoolBytes = (size_t)256 << 20;
 constexpr int kMaxDevices = 64;
@@ -287,14 +287,14 @@ class Workspace {
           if (pool.p) (void)hipFree(pool.p);
           pool.p = nullptr;
           pool.bytes = 0;
-          SETD_HIP(hipMalloc(&pool.p, bytes));
+          SETD_TRY(device_malloc(&pool.p, bytes, false));
           pool.bytes = bytes;
         }
         p = (char*)pool.p;
         return SETD_OK;
       }
     }
-    SETD_HIP(hipMalloc(&own_, bytes));
+    SETD_TRY(device_malloc(&own_, bytes));
     p = (char*)own_;
     return SETD_OK;
   }
@@ -407,9 +407,11 @@ int build_chunk(const double* A, int n, const double* c, int E, int p, double an
 
 }  // namespace
 
-int phi_release_workspace(int dev) {
+int phi_release_workspace(int dev, bool wait) {
   if (dev < 0 || dev >= kMaxDevices) return SETD_OK;
-  std::lock_guard<std::mutex> lk(g_pool[dev].mu);
+  std::unique_lock<std::mutex> lk(g_pool[dev].mu, std::defer_lock);
+  if (wait) lk.lock();
+  else if (!lk.try_lock()) return SETD_OK;
   if (g_pool[dev].p) SETD_HIP(hipFree(g_pool[dev].p));
   g_pool[dev].p = nullptr;
   g_pool[dev].bytes = 0;

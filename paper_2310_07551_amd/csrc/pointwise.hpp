@@ -96,7 +96,8 @@ int launch_norms(const double* x, const double* y, int64_t n, double* ws, hipStr
 // blocks phi_0..phi_p(c_j A) are written to out + (j (p+1) + k) n^2 (device
 // n x n column-major).  Synchronises s.
 int phi_batch(const double* A, int n, const double* c, int nentries, int p, double* out, hipStream_t s);
-// Frees the workspace that the builds keep on a device.
-int phi_release_workspace(int dev);
+// Frees the workspace that the builds keep on a device; wait: also if a build is
+// using it now, once that has ended (else it stays).
+int phi_release_workspace(int dev, bool wait = true);
 
 }  // namespace setd

@@ -189,6 +189,41 @@ std::vector<void*> drop_kept(int dev, size_t limit) {
 }
 }  // namespace
 
+namespace {
+// The result of alloc(), tried again without what is kept if it fails.
+template <class F>
+hipError_t alloc_or_give_back(F alloc, bool idle_phi) {
+  hipError_t e = alloc();
+  if (e == hipSuccess) return e;
+  (void)hipGetLastError();
+  int dev = 0;
+  hipMemPool_t pool;
+  if (hipGetDevice(&dev) == hipSuccess) {
+    (void)device_release_kept(dev);
+    if (idle_phi) (void)phi_release_workspace(dev, false);
+    if (hipDeviceGetDefaultMemPool(&pool, dev) == hipSuccess) (void)hipMemPoolTrimTo(pool, 0);
+  }
+  e = alloc();
+  if (e != hipSuccess) (void)hipGetLastError();
+  return e;
+}
+
+int alloc_result(hipError_t e, const char* what, size_t bytes, void** p) {
+  if (e == hipSuccess) return SETD_OK;
+  *p = nullptr;
+  set_error("%s(%zu) failed: %s", what, bytes, hipGetErrorString(e));
+  return e == hipErrorOutOfMemory ? SETD_ENOMEM : SETD_EHIP;
+}
+}  // namespace
+
+int setd::device_malloc(void** p, size_t bytes, bool idle_phi) {
+  return alloc_result(alloc_or_give_back([&] { return hipMalloc(p, bytes); }, idle_phi), "hipMalloc", bytes, p);
+}
+
+int setd::device_malloc_async(void** p, size_t bytes, hipStream_t s) {
+  return alloc_result(alloc_or_give_back([&] { return hipMallocAsync(p, bytes, s); }, true), "hipMallocAsync", bytes, p);
+}
+
 int setd::device_alloc(size_t bytes, void** p, size_t* capacity, int* dev) {
   *p = nullptr;
   SETD_HIP(hipGetDevice(dev));
@@ -207,17 +242,8 @@ int setd::device_alloc(size_t bytes, void** p, size_t* capacity, int* dev) {
       return SETD_OK;
     }
   }
-  hipError_t e = hipMalloc(p, bytes);
-  if (e != hipSuccess) {   // once more without the kept blocks
-    (void)hipGetLastError();
-    SETD_TRY(device_release_kept(*dev));
-    e = hipMalloc(p, bytes);
-  }
-  if (e != hipSuccess) {
-    *p = nullptr;
-    set_error("hipMalloc(%zu) failed: %s", bytes, hipGetErrorString(e));
-    return SETD_ENOMEM;
-  }
+  const int rc = device_malloc(p, bytes);
+  if (rc != SETD_OK) return SETD_ENOMEM;
   *capacity = bytes;
   return SETD_OK;
 }
@@ -946,7 +972,7 @@ int tucker_raw(const double* V, double* W, int d, const int64_t* dims, int64_t N
   const int nops = slab ? nm - 1 : nm;
   const int64_t fb = round_up(N * 8, 256);
   void* own = nullptr;
-  if (nops > 1 && ws == nullptr) SETD_HIP(hipMallocAsync(&own, std::min(nops - 1, 2) * fb, s));
+  if (nops > 1 && ws == nullptr) SETD_TRY(device_malloc_async(&own, std::min(nops - 1, 2) * fb, s));
   char* q = (char*)round_up((int64_t)(uintptr_t)(own ? own : ws), 256);
   double* buf[2] = {(double*)q, (double*)(q + fb)};
   // beta: the last product adds W, scaled first unless beta is 1
@@ -1137,7 +1163,7 @@ int setd_tucker_apply(const double* V, double* W, int d, const int64_t* dims, co
   void* wsp = ws;
   bool own = false;
   if (nm > 0 && wsp == nullptr) {
-    SETD_HIP(hipMallocAsync(&wsp, need, s));
+    SETD_TRY(device_malloc_async(&wsp, need, s));
     own = true;
   }
   // beta handling: base = W when beta == 1, none when beta == 0, else scale W first
@@ -1449,7 +1475,7 @@ int setd_field_norms(const double* x, const double* y, int64_t n, double* out, v
   }
   hipStream_t s = (hipStream_t)stream;
   void* ws = nullptr;
-  SETD_HIP(hipMallocAsync(&ws, norm_workspace_bytes(), s));
+  SETD_TRY(device_malloc_async(&ws, norm_workspace_bytes(), s));
   int rc = launch_norms(x, y, n, (double*)ws, s);
   double h[4] = {0, 0, 0, 0};
   if (rc == SETD_OK) {
