@@ -341,11 +341,15 @@ int setd_etd_adjoint_step_recorded(setd_ctx* ctx, const double* u, const double*
  * fastest.  Synchronises `stream`.
  * setd_batch_set_tiles fixes them instead: cfg (host) = {tm, tn, cap} for
  * mode 1 followed by {tm, tn, cap} for modes >= 2 (cap = largest number of
- * workgroups of a launch, 0 = one per tile).
- * setd_batch_info (host, SETD_BATCH_INFO entries): the six tile values of the
- * phi_1 group as for setd_batch_set_tiles, whether they were tuned or set, launches per
+ * workgroups of a launch, 0 = one per tile): one tile for both groups, its
+ * contraction on one wave.
+ * setd_batch_info (host, SETD_BATCH_INFO entries): the six tile values as for
+ * setd_batch_set_tiles, whether they were tuned or set, launches per
  * step (0 before the first step), the length of u, and the number of
- * distinct packed matrix sets.
+ * distinct packed matrix sets.  The tile values are those of the phi_1 group; a
+ * tuned choice has the waves per tile and the phi_2 groups' tile in the bits of
+ * the caps from 2^24 on, so that setd_batch_set_tiles of a batch of the same
+ * instances takes the whole choice again.
  */
 typedef struct setd_batch setd_batch;
 #define SETD_BATCH_INFO 10

@@ -589,6 +589,48 @@ int tune(setd_batch* B, hipStream_t s) {
 
 bool valid_tile(int tm, int tn) { return (tm == 2 || tm == 4) && (tn == 2 || tn == 4); }
 
+// The {tm, tn, cap} of setd_batch_set_tiles and setd_batch_info holds more than
+// one unsplit tile for both groups: above the low kCapBits of cap stands 0, or 1 +
+// 3 k + log2 of the waves per tile of the phi_1 group, k the candidate of the
+// phi_2 groups, so that a stored choice is set again whole.
+constexpr int kCapBits = 24, kCands = (int)(sizeof(kCand) / sizeof(kCand[0]));
+
+int find_cand(int ti, int to, int ks) {
+  for (int k = 0; k < kCands; ++k)
+    if (kCand[k][0] == ti && kCand[k][1] == to && kCand[k][2] == ks) return k;
+  return -1;
+}
+
+// c[0], c[1] as {blocks of i, of the other index}.
+int find_choice(const int* c, bool mode1, int ks) { return find_cand(c[mode1 ? 0 : 1], c[mode1 ? 1 : 0], ks); }
+
+void set_choice(const int* cfg, bool mode1, TileChoice (&tiles)[2]) {
+  int* a = mode1 ? tiles[0].mode1 : tiles[0].modeB;
+  int* b = mode1 ? tiles[1].mode1 : tiles[1].modeB;
+  for (int* t : {a, b}) {
+    std::copy(cfg, cfg + 3, t);
+    t[3] = 1;
+  }
+  const int code = cfg[2] >> kCapBits;
+  if (code < 1 || code > 3 * kCands) return;
+  const int ks = 1 << (code - 1) % 3;
+  const int* k = kCand[(code - 1) / 3];
+  if (find_choice(cfg, mode1, ks) < 0) return;   // a cap, if a very large one
+  a[2] = b[2] = cfg[2] & ((1 << kCapBits) - 1);
+  a[3] = ks;
+  b[0] = k[mode1 ? 0 : 1];
+  b[1] = k[mode1 ? 1 : 0];
+  b[3] = k[2];
+}
+
+void get_choice(const TileChoice (&tiles)[2], bool mode1, int64_t* out) {
+  const int* a = mode1 ? tiles[0].mode1 : tiles[0].modeB;
+  const int* b = mode1 ? tiles[1].mode1 : tiles[1].modeB;
+  std::copy(a, a + 3, out);
+  if (a[3] == 1 && std::equal(b, b + 4, a)) return;
+  out[2] |= (int64_t)(1 + 3 * find_choice(b, mode1, b[3]) + (a[3] == 4 ? 2 : a[3] - 1)) << kCapBits;
+}
+
 }  // namespace
 
 extern "C" {
@@ -788,8 +830,8 @@ int setd_batch_set_tiles(setd_batch* B, const int* cfg) {
   SETD_CHECK_ARG(B != nullptr && cfg != nullptr, "batch and cfg must be non-NULL");
   SETD_CHECK_ARG(valid_tile(cfg[0], cfg[1]) && valid_tile(cfg[3], cfg[4]), "tiles must be 2 or 4 on each side");
   SETD_CHECK_ARG(cfg[2] >= 0 && cfg[5] >= 0, "grid caps must be >= 0");
-  for (TileChoice& t : B->tiles)
-    t = {{cfg[0], cfg[1], cfg[2], 1}, {cfg[3], cfg[4], cfg[5], 1}};
+  set_choice(cfg, true, B->tiles);
+  set_choice(cfg + 3, false, B->tiles);
   B->tuned = true;
   B->plan_u = nullptr;
   drop_graph(B);
@@ -799,10 +841,8 @@ int setd_batch_set_tiles(setd_batch* B, const int* cfg) {
 int setd_batch_info(const setd_batch* B, int64_t* info) {
   clear_error();
   SETD_CHECK_ARG(B != nullptr && info != nullptr, "batch and info must be non-NULL");
-  for (int k = 0; k < 3; ++k) {
-    info[k] = B->tiles[0].mode1[k];
-    info[3 + k] = B->tiles[0].modeB[k];
-  }
+  get_choice(B->tiles, true, info);
+  get_choice(B->tiles, false, info + 3);
   info[6] = B->tuned ? 1 : 0;
   info[7] = (int64_t)B->plan.size();
   info[8] = B->total;
