@@ -211,7 +211,7 @@ struct ModeList {
   int64_t total;         // tiles
   bool mode1;
   int ti, to, ks;        // tile: 16 ti of i, 16 to of the other index, ks waves
-  int64_t grid_cap;      // maximum number of waves (0: one per tile)
+  int64_t grid_cap;      // maximum number of workgroups (0: all)
   double flops, bytes;   // algorithmic work, for the kernel timing
 };
 int launch_list_f64(const ModeList& L, hipStream_t s);

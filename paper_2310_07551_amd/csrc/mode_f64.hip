@@ -1221,9 +1221,9 @@ int launch_list_f64(const ModeList& L, hipStream_t s) {
   if (L.total == 0) return SETD_OK;
   const int64_t groups = round_up(ceil_div(L.total, 4 / L.ks), 8 * kListRun);
   // a multiple of 8 blocks, so that block b stays on XCD b % 8 through the
-  // whole loop; at most `grid_cap` waves (0: all)
+  // whole loop; at most `grid_cap` of them, rounded up (0: all)
   int64_t nblk = groups;
-  if (L.grid_cap > 0 && nblk * 4 > L.grid_cap) nblk = round_up(ceil_div(L.grid_cap, 4), 8);
+  if (L.grid_cap > 0 && nblk > L.grid_cap) nblk = round_up(L.grid_cap, 8);
   const dim3 grid((unsigned)nblk);
   ProfScope prof(s, L.mode1 ? kProfMode1F64 : kProfModeBF64, L.flops, L.bytes);
   const int key = 100 * L.ti + 10 * L.to + L.ks;
