@@ -185,6 +185,12 @@ inline bool vector_columns(const ModeJobs& J, int to) {
   return true;
 }
 
+// Whether a grid, of fewer than 2^32 threads, holds `tiles` tiles of ks waves in
+// workgroups of four.
+inline bool fits_grid(int64_t tiles, int ks) {
+  return round_up(ceil_div(tiles, 4 / ks), 8) * 256 < (int64_t(1) << 32);
+}
+
 // Mode-product launchers (implemented in mode_f64.hip / mode_lp.hip).
 // `jobs` is filled by the caller except for the tile fields, which the
 // launcher computes.  All jobs of one launch share regime (mode 1 or not).

@@ -980,11 +980,13 @@ TileCfg choose_tile(const ModeJobs& J, bool mode1) {
   const bool full = tile_count(J, mode1, TileCfg{4, 4, 1, 0, 0, 0}) >= 1024;
   bool wide = !mode1;   // 1 x 4
   for (int j = 0; j < J.njobs; ++j) wide = wide && J.job[j].n <= kShortN;
-  TileCfg best = kTiles[0];
+  TileCfg best{4, 4, 1, 0, 0, 0};
   double bt = 1e300;
   for (const TileCfg& t : kTiles) {
     if ((t.ti == 1 && t.to == 4 && !wide) || (full && t.ks > 1)) continue;
-    const double w = (double)tile_count(J, mode1, t) * t.ks / 1024.0;
+    const int64_t tiles = tile_count(J, mode1, t);
+    if (!fits_grid(tiles, t.ks)) continue;
+    const double w = (double)tiles * t.ks / 1024.0;
     double wave = 0.0;
     for (int j = 0; j < J.njobs; ++j) {
       const ModeJob& jb = J.job[j];
@@ -1116,14 +1118,17 @@ int launch_modeB_f64(ModeJobs& J, hipStream_t s, bool raw) {
     big = big || jb.na > (int64_t(1) << 26) ||
           (jb.nb > 1 && (ceil_div(128, jb.na) + 1) * jb.na * jb.n > (int64_t(1) << 28));
   }
-  const TileCfg cfg = big ? TileCfg{4, 2, 1, 0, 0, 0} : env_tile("SETD_TILE_MODEB", choose_tile(J, false));
+  TileCfg cfg = big ? TileCfg{4, 2, 1, 0, 0, 0} : env_tile("SETD_TILE_MODEB", choose_tile(J, false));
+  if (big && !fits_grid(tile_count(J, false, cfg), 1)) cfg = TileCfg{4, 4, 1, 0, 0, 0};
   if (lds) finish_panels(J, false);
   else finish_tiles(J, false, cfg);
   if (J.total_tiles == 0) return SETD_OK;
   // the two kernels are timed as separate classes
   ProfScope prof(s, lds ? kProfModeBPanelF64 : kProfModeBF64, fl, by);
-  if (big && !lds)
+  if (big && !lds) {
+    if (cfg.to == 4) return launch_tile<false, false, 4, 4, 1, uint64_t>(J, s);   // raw tensors are not that large
     return raw ? launch_tile<false, true, 4, 2, 1, uint64_t>(J, s) : launch_tile<false, false, 4, 2, 1, uint64_t>(J, s);
+  }
   if (!lds) return raw ? launch_cfg<false, true>(J, cfg, s) : launch_cfg<false, false>(J, cfg, s);
   const int64_t per = ceil_div(J.total_tiles, 8);
   hipLaunchKernelGGL(modeB_lds_kernel, dim3((unsigned)(per * 8)), dim3(64 * kLdsWaves), 0, s, J, per, kLdsReps);

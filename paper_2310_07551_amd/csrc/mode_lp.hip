@@ -712,6 +712,15 @@ struct TileF32 {
 constexpr TileF32 kTilesF32[] = {{1, 1, .50, .50}, {2, 2, .80, .80}, {4, 2, .85, .90}, {4, 4, .92, .98},
                                  {5, 2, .88, .88}, {5, 4, .95, .87}, {7, 2, .93, .92}, {8, 2, .92, .97}};
 
+int64_t tile_count(const ModeJobs& J, bool mode1, const TileF32& t) {
+  int64_t w = 0;
+  for (int j = 0; j < J.njobs; ++j) {
+    const ModeJob& jb = J.job[j];
+    w += ceil_div(jb.n, 16 * t.ti) * ceil_div(mode1 ? jb.nb : jb.na * jb.nb, 16 * t.to);
+  }
+  return w;
+}
+
 // The tile whose launch should take least time, by the model of the FP64
 // kernels (a chunk of 16 p is four MFMAs of 32 cycles per block); overridable
 // with SETD_TILE_F32_MODE1 / SETD_TILE_F32_MODEB ("4x2" etc.).
@@ -721,17 +730,18 @@ TileF32 tile_f32(const ModeJobs& J, bool mode1) {
   if (e && std::sscanf(e, "%dx%d", &a, &b) == 2)
     for (const TileF32& t : kTilesF32)
       if (t.ti == a && t.to == b) return t;
-  TileF32 best = kTilesF32[0];
+  TileF32 best = kTilesF32[3];   // 4 x 4
   double bt = 1e300;
   for (const TileF32& t : kTilesF32) {
-    double w = 0.0, wave = 0.0;
+    const int64_t tiles = tile_count(J, mode1, t);
+    if (!fits_grid(tiles, 1)) continue;
+    const double w = (double)tiles / 1024.0;
+    double wave = 0.0;
     for (int j = 0; j < J.njobs; ++j) {
       const ModeJob& jb = J.job[j];
-      w += (double)ceil_div(jb.n, 16 * t.ti) * ceil_div(mode1 ? jb.nb : jb.na * jb.nb, 16 * t.to);
       wave = std::max(wave, t.ti * t.to * ((double)jb.nterms * ceil_div(jb.n, 16) * 128.0 / (mode1 ? t.rate1 : t.rateB) +
                                            700.0 * (jb.base ? 1.6 : 1.0)));
     }
-    w /= 1024.0;
     const double time = ((w < 6.0 ? std::ceil(w) : w) + 0.3) * wave;
     if (time < bt) {
       bt = time;
@@ -822,10 +832,13 @@ int launch_modeB_f32c(ModeJobs& J, DType out, hipStream_t s) {
   double fl = 0.0, by = 0.0;
   if (prof_on()) job_work(J, 4, out == DType::F64 ? 8 : 4, 4, fl, by);
   const bool big = big_tiles(J);
-  const TileF32 cfg = big ? kTilesF32[2] : tile_f32(J, false);
+  const TileF32 cfg = big ? kTilesF32[fits_grid(tile_count(J, false, kTilesF32[2]), 1) ? 2 : 3] : tile_f32(J, false);
   finish_tiles_f32(J, false, cfg);
   if (J.total_tiles == 0) return SETD_OK;
   ProfScope prof(s, kProfModeBLP, fl, by);
+  if (big && cfg.to == 4)
+    return out == DType::F32 ? launch_tile_f32<false, false, 4, 4, uint64_t, float>(J, s)
+                             : launch_tile_f32<false, false, 4, 4, uint64_t, double>(J, s);
   if (big)
     return out == DType::F32 ? launch_tile_f32<false, false, 4, 2, uint64_t, float>(J, s)
                              : launch_tile_f32<false, false, 4, 2, uint64_t, double>(J, s);
@@ -847,17 +860,18 @@ TileF32 tile_bf16(const ModeJobs& J, bool mode1, int np) {
   if (e && std::sscanf(e, "%dx%d", &a, &b) == 2)
     for (const TileF32& t : kTilesBf16)
       if (t.ti == a && t.to == b) return t;
-  TileF32 best = kTilesBf16[0];
+  TileF32 best = kTilesBf16[3];   // 4 x 4
   double bt = 1e300;
   for (const TileF32& t : kTilesBf16) {
-    double w = 0.0, wave = 0.0;
+    const int64_t tiles = tile_count(J, mode1, t);
+    if (!fits_grid(tiles, 1)) continue;
+    const double w = (double)tiles / 1024.0;
+    double wave = 0.0;
     for (int j = 0; j < J.njobs; ++j) {
       const ModeJob& jb = J.job[j];
-      w += (double)ceil_div(jb.n, 16 * t.ti) * ceil_div(mode1 ? jb.nb : jb.na * jb.nb, 16 * t.to);
       wave = std::max(wave, t.ti * t.to * ((double)jb.nterms * ceil_div(jb.n, 32) * (np == 3 ? 112.0 : 64.0) / t.rate1 +
                                            700.0 * (jb.base ? 1.6 : 1.0)));
     }
-    w /= 1024.0;
     const double time = ((w < 6.0 ? std::ceil(w) : w) + 0.3) * wave;
     if (time < bt) {
       bt = time;
@@ -891,6 +905,7 @@ int launch_bf16(const ModeJobs& J, const TileF32& t, hipStream_t s) {
 
 template <int NP, typename T>
 int launch_modeB_bf16(const ModeJobs& J, const TileF32& t, bool big, bool vec, bool sum, hipStream_t s) {
+  if (big && t.to == 4) return launch_tile_bf16<NP, false, false, true, 4, 4, uint64_t, T>(J, s);
   if (big) return launch_tile_bf16<NP, false, false, true, 4, 2, uint64_t, T>(J, s);
   if (vec) return sum ? launch_bf16<NP, false, true, true, T>(J, t, s) : launch_bf16<NP, false, true, false, T>(J, t, s);
   return sum ? launch_bf16<NP, false, false, true, T>(J, t, s) : launch_bf16<NP, false, false, false, T>(J, t, s);
@@ -919,7 +934,8 @@ int launch_modeB_lp(ModeJobs& J, int prec, DType out, hipStream_t s) {
   if (prec == SETD_PREC_F32) return launch_modeB_f32c(J, out, s);
   if (J.njobs == 0) return SETD_OK;
   const bool x3 = prec == SETD_PREC_BF16X3, big = big_tiles(J);
-  const TileF32 cfg = big ? kTilesBf16[2] : tile_bf16(J, false, x3 ? 3 : 2);
+  const TileF32 cfg =
+      big ? kTilesBf16[fits_grid(tile_count(J, false, kTilesBf16[2]), 1) ? 2 : 3] : tile_bf16(J, false, x3 ? 3 : 2);
   finish_tiles_f32(J, false, cfg);
   if (J.total_tiles == 0) return SETD_OK;
   double fl = 0.0, by = 0.0;
