@@ -704,13 +704,15 @@ bool big_tiles(const ModeJobs& J) {
 // with 4 x 2 (8 tiles of i); 200^3 (13 tiles) mode 1 0.64 ms with 7 x 2, 0.68
 // with 5 x 4, 0.76 with 4 x 4, modes >= 2 0.61, 0.73 and 0.72; 150^3 (10 tiles)
 // modes >= 2 0.25 ms with 5 x 2, 0.29 with 5 x 4; 500 x 400, 6 jobs 38 us with
-// 1 x 1, 96 with 4 x 4.
+// 1 x 1, 96 with 4 x 4.  1 x 4 for modes >= 2 of one block of i, bound by memory: a
+// whole operator on mode 2 of 1024 x 2 x 3200 61 us, 114 with 1 x 1.
 struct TileF32 {
   int ti, to;
   double rate1, rateB;
 };
 constexpr TileF32 kTilesF32[] = {{1, 1, .50, .50}, {2, 2, .80, .80}, {4, 2, .85, .90}, {4, 4, .92, .98},
-                                 {5, 2, .88, .88}, {5, 4, .95, .87}, {7, 2, .93, .92}, {8, 2, .92, .97}};
+                                 {5, 2, .88, .88}, {5, 4, .95, .87}, {7, 2, .93, .92}, {8, 2, .92, .97},
+                                 {1, 4, .50, .80}};
 
 int64_t tile_count(const ModeJobs& J, bool mode1, const TileF32& t) {
   int64_t w = 0;
@@ -730,9 +732,12 @@ TileF32 tile_f32(const ModeJobs& J, bool mode1) {
   if (e && std::sscanf(e, "%dx%d", &a, &b) == 2)
     for (const TileF32& t : kTilesF32)
       if (t.ti == a && t.to == b) return t;
+  bool wide = !mode1;   // 1 x 4: modes >= 2 of one block of i
+  for (int j = 0; j < J.njobs; ++j) wide = wide && J.job[j].n <= 16;
   TileF32 best = kTilesF32[3];   // 4 x 4
   double bt = 1e300;
   for (const TileF32& t : kTilesF32) {
+    if (t.ti == 1 && t.to == 4 && !wide) continue;
     const int64_t tiles = tile_count(J, mode1, t);
     if (!fits_grid(tiles, 1)) continue;
     const double w = (double)tiles / 1024.0;
@@ -772,6 +777,7 @@ int launch_f32(const ModeJobs& J, const TileF32& t, hipStream_t s) {
 #define SETD_TILE(TI_, TO_) \
   if (t.ti == TI_ && t.to == TO_) return launch_tile_f32<M1, V && (TO_ > 1), TI_, TO_, uint32_t, T>(J, s);
   SETD_TILE(1, 1)
+  SETD_TILE(1, 4)
   SETD_TILE(2, 2)
   SETD_TILE(4, 2)
   SETD_TILE(4, 4)
