@@ -226,11 +226,10 @@ int launch_list_f64(const ModeList& L, hipStream_t s);
 // once, output written once, base read once; es = element sizes in bytes).
 void job_work(const ModeJobs& J, int es_in, int es_out, int es_mat, double& flops, double& bytes);
 
-// Matrix packing (pointwise.hip); zero outside n x n.
-// FP64, any mode: scale * M (or its transpose) in the matrix cores' operand
-// order (mode_f64.hip).  FP32 and bf16:
-//   rowmajor:       out[i*ldp + p] = scale*M[i + n p]   (mode-1 operand)
-//   not rowmajor:   out[i + ldp*p] = scale*M[i + n p]   (modes >= 2 operand)
+// Matrix packing (pointwise.hip): scale * M (FP64: or its transpose) tile by tile
+// in the matrix cores' operand order, zero outside n x n.  FP64 and bf16 have one
+// order for every mode, FP32 one for mode 1 and one for modes >= 2 (mode_f64.hip,
+// mode_lp.hip).
 int pack_matrix_f64(const double* M, int n, double scale, bool trans, double* out, hipStream_t s);
 // Several FP64 matrices of one size: src + coef * src2 (src2 nullable).
 struct PackJob {

@@ -42,9 +42,9 @@
 // small grids the latency of one wave (about 2 us besides its products), so
 // that the tile is chosen per launch (choose_tile).  Steps of two components
 // against kernels with one fixed tile per contraction length and vector
-// accesses for aligned sizes only: 64^2 107 -> 52 us, 300^2 595 -> 112 us
-// (the last mode alone 151 -> 20 and 9 us), 100^3 739 -> 559 us, 128^3 1060
-// -> 893 us, 256^3 11.93 -> 11.69 ms.
+// accesses for aligned sizes only: 300^2 595 -> 109 us (the last mode alone
+// 151 -> 20 and 9 us), and with the one-pass kernels below 64^2 107 -> 36 us,
+// 100^3 739 -> 538 us, 128^3 1060 -> 884 us, 256^3 11.93 -> 11.72 ms.
 #include "common.hpp"
 #include "pointwise.hpp"
 
@@ -882,7 +882,8 @@ __global__ void __launch_bounds__(512, 1) modeB_lds_kernel(const ModeJobs J, int
       }
     }
     __builtin_amdgcn_s_setprio(0);
-    // epilogue as in modeB_tile (TM = TN = 4, every row and column in range)
+    // epilogue: lane (g, l) owns a = a0 + 4 g + 16 r + (0..3) of the columns
+    // i0 + 4 l + u, every row and column in range
     double* __restrict__ Y = (double*)jb.Y;
     const double* __restrict__ base = (const double*)jb.base;
 #pragma unroll

@@ -133,10 +133,9 @@ int push(ModeJobs& J, const ModeJob& jb, const LaunchKind& k, hipStream_t s) {
   return SETD_OK;
 }
 
-// Packs a matrix for the mode kernels of the given arithmetic: FP64 in one
-// operand order for every mode; FP32 row-major for mode 1 and column-major for
-// modes >= 2; bf16 row-major.
 }  // namespace
+
+// Packs a matrix for the mode kernels of the given arithmetic (common.hpp).
 
 int setd::pack_for(int prec, const double* M, int n, double scale, int mu, void* out, hipStream_t s) {
   if (prec == SETD_PREC_F64) return pack_matrix_f64(M, n, scale, false, (double*)out, s);
@@ -945,10 +944,14 @@ int noalloc_scratch(void** out) {
 
 namespace {
 
-// FP64 Tucker operator with the matrices read as they are given: packing pays
-// when a matrix is used again, or by many tiles (256^3; the LDS panel kernels
-// need it).  At 150^3 the three packing launches took 13 of 118 us, at 64^2
-// half of the four launches.
+// FP64 Tucker operators of up to kRawElems entries read their matrices as they are
+// given: a matrix used once does not pay for its packing at any size measured, with
+// the caller's workspace us raw / packed: 128^2 10 / 14, 600^2 30 / 37, 1024^2 77 /
+// 84, 2048^2 497 / 522, 2048 x 4096 1436 / 1497, 64 x 4096 47 / 113, 100^3 34 / 43,
+// 150^3 75 / 84, 200^3 212 / 211; the worst 250 x 500 x 50 227 / 206.  The line is as
+// far as that was measured in every shape, not where packing begins to pay: 204^3
+// takes 226 / 249, 250^3 441 / 434, 256^3 434 / 759 (its panel kernels, for one
+// operator, run on half the chip).
 constexpr int64_t kRawElems = int64_t(1) << 23;
 
 // Modes 1 and 2 as one pass over slabs, which needs no intermediate.  A few
