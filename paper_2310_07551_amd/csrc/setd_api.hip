@@ -955,16 +955,18 @@ namespace {
 constexpr int64_t kRawElems = int64_t(1) << 23;
 
 // Modes 1 and 2 as one pass over slabs, which needs no intermediate.  A few
-// slabs run on a few workgroups (about 4.5 + 0.13 c us, c = chunks of both
+// slabs run on a few workgroups (about 4.5 + 0.1 c us, c = chunks of both
 // contractions x blocks of 64 rows), against two launches (8 to 10 us) and, where
-// these are all the modes and the caller gives no workspace, an allocation (18
-// us): 64^2 9 us a call (25 by two products), 128^2 10 (25), 250 x 100 23 (25),
-// 200^2 29 by two products.  The choice is the same with a workspace (128^2 10 us,
-// 8.6 by two products; 250 x 100 23, 8.4), so that every entry gives the same bits.
+// these are all the modes and the caller gives no workspace, an allocation (16 to
+// 20 us).  The choice is by the sizes alone, so that every entry gives the same
+// bits; the line is where the pass is as far above the one as below the other (us:
+// the pass / two products with a workspace, without one 24 to 30 by the process:
+// 64^2 4.9 / 7.5, 128^2 10 / 8.6, 150^2 14.5 / 8.6, 168^2 15.2 / 8.7, 192^2 17.4 /
+// 9.0, 250 x 100 23 / 8.5).
 bool raw_slab(const int64_t* dims, int64_t nb, bool all) {
   if (dims[0] > kSlabMaxN1) return false;
   const int64_t c = (ceil_div(dims[0], 8) + ceil_div(dims[1], 8)) * ceil_div(dims[0], 64);
-  if (nb * ceil_div(dims[1], 16) <= 64) return c <= (all ? 180 : 50);
+  if (nb * ceil_div(dims[1], 16) <= 64) return c <= (all ? 128 : 50);
   return dims[1] >= 8 && slab_shape(dims[0], dims[1], nb * dims[0] * dims[1]);
 }
 
